@@ -77,43 +77,12 @@ __global__ __launch_bounds__(RB) void k_stats(const cpx<T> *__restrict__ psi, ui
     }
 }
 
-// Combine per-workgroup partials in workgroup order (Neumaier).
-// Combine per-workgroup partial rows (16 doubles each) in row order with
-// Neumaier's summation, quantity q = 0..nq-1.  256 threads: 16 row segments
-// per quantity are summed in parallel, then the segment sums and their
-// compensations are combined in segment order (a fixed order: the result
-// does not depend on timing).
-__global__ __launch_bounds__(256) void k_combine(const double *__restrict__ part, int nblocks, int nq,
-                                                 double *__restrict__ out) {
-    __shared__ double ss[16][16], cc[16][16];
-    const int q = threadIdx.x & 15, seg = threadIdx.x >> 4;
-    const int per = (nblocks + 15) / 16;
-    const int b0 = seg * per, b1 = b0 + per < nblocks ? b0 + per : nblocks;
-    double s = 0.0, c = 0.0;
-    if (q < nq) {
-        for (int b = b0; b < b1; b++) {
-            const double x = part[(uint64_t)b * 16 + q];
-            const double t = s + x;
-            if (fabs(s) >= fabs(x)) c += (s - t) + x;
-            else c += (x - t) + s;
-            s = t;
-        }
-    }
-    ss[seg][q] = s;
-    cc[seg][q] = c;
-    __syncthreads();
-    if (threadIdx.x < nq) {
-        double S = 0.0, C = 0.0;
-        for (int g = 0; g < 16; g++) {
-            const double x = ss[g][threadIdx.x];
-            const double t = S + x;
-            if (fabs(S) >= fabs(x)) C += (S - t) + x;
-            else C += (x - t) + S;
-            S = t;
-            C += cc[g][threadIdx.x];
-        }
-        out[threadIdx.x] = S + C;
-    }
+// Combine per-workgroup partial rows (16 doubles each), quantity q =
+// 0..nq-1, in a fixed order.
+__global__ __launch_bounds__(CMB_THREADS) void k_combine(const double *__restrict__ part, int nblocks, int nq,
+                                                         double *__restrict__ out) {
+    __shared__ double red[2 * 64 * 16];
+    combine_rows_wg(part, nblocks, nq, out, red);
 }
 
 static void stats_grid(int n, int *nblocks, uint64_t *chunk) {
@@ -136,7 +105,7 @@ static sv_status stats_typed(sv_state *st, const void *psi, double *host16) {
     hipLaunchKernelGGL((k_stats<T, FULL>), dim3(nb), dim3(RB), 0, st->stream, (const cpx<T> *)psi,
                        chunk, std::ldexp(1.0, st->n), part);
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, st->stream, part, nb, FULL ? NSTAT + 1 : 1, res);
+    hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, nb, FULL ? NSTAT + 1 : 1, res);
     SV_HIP(hipGetLastError());
     SV_HIP(hipMemcpyAsync(host16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, st->stream));
     SV_HIP(hipStreamSynchronize(st->stream));
@@ -183,7 +152,7 @@ sv_status batch_stats_enqueue(sv_state *st, double *part, double *res) {
         hipLaunchKernelGGL((k_stats<double, true>), dim3(nb), dim3(RB), 0, st->stream,
                            (const cpx<double> *)st->data, chunk, std::ldexp(1.0, st->n), part);
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, st->stream, part, nb, NSTAT + 1, res);
+    hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, nb, NSTAT + 1, res);
     SV_HIP(hipGetLastError());
     return SV_OK;
 }
@@ -340,7 +309,7 @@ sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, const double *host
         hipLaunchKernelGGL(k_pair_stats<double>, dim3(nb), dim3(RB), 0, s, (const cpx<double> *)a->data,
                            (const cpx<double> *)b->data, chunk, thr, nbins, part, hist);
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, s, part, nb, NPAIR + 1, res);
+    hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, s, part, nb, NPAIR + 1, res);
     SV_HIP(hipGetLastError());
     SV_HIP(hipMemcpyAsync(sums16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
     if (nbins > 0)
@@ -660,7 +629,7 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
         double *part = (double *)(w + o_part), *res = (double *)(w + o_res);
         hipLaunchKernelGGL((k_stats_weights<S>), dim3((unsigned)ng), dim3(RB), 0, s, src, bs, sb, nb,
                            std::ldexp(1.0, n), part, bsum, sub);
-        hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, s, part, (int)ng, NSTAT + 1, res);
+        hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, s, part, (int)ng, NSTAT + 1, res);
         SV_HIP(hipGetLastError());
         SV_HIP(hipMemcpyAsync(stats16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
         if (k == 0) {
@@ -880,7 +849,7 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
         hipLaunchKernelGGL(k_ce<double>, dim3((unsigned)nb), dim3(RB), 0, st->stream,
                            (const cpx<double> *)psi, dev_samples, k, per, part);
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, st->stream, part, (int)nb, 2, res);
+    hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, (int)nb, 2, res);
     double r[2];
     SV_HIP(hipMemcpyAsync(r, res, 2 * sizeof(double), hipMemcpyDeviceToHost, st->stream));
     SV_HIP(hipStreamSynchronize(st->stream));

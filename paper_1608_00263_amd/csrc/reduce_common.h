@@ -53,6 +53,54 @@ __device__ __forceinline__ void block_sum(V (&v)[NV], V *red /* LDS, 4*NV */) {
     __syncthreads();
 }
 
+// Combines n partial rows of 16 doubles each, quantity q = 0..nq-1, by a
+// workgroup of CMB_THREADS threads: 64 segments of the rows are summed in
+// parallel (Neumaier, eight rows loaded before they are added), then the
+// segments pairwise in a fixed tree with the rounding errors carried along.
+// The order is fixed, so the result does not depend on timing.  A workgroup's
+// time here is the latency of its loads: 16 segments with one load in flight
+// took 63 us for 2048 rows; red holds 2 * 64 * 16 doubles of LDS.
+constexpr int CMB_THREADS = 1024;
+
+__device__ __forceinline__ void neumaier_add(double &s, double &c, double x) {
+    const double t = s + x;
+    if (fabs(s) >= fabs(x)) c += (s - t) + x;
+    else c += (x - t) + s;
+    s = t;
+}
+
+__device__ __forceinline__ void combine_rows_wg(const double *part, int n, int nq, double *out, double *red) {
+    const int q = threadIdx.x & 15, seg = threadIdx.x >> 4;
+    const int per = (n + 63) / 64;
+    const int b0 = seg * per, b1 = b0 + per < n ? b0 + per : n;
+    double s = 0.0, c = 0.0;
+    if (q < nq) {
+        for (int b = b0; b < b1; b += 8) {
+            double x[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) x[j] = b + j < b1 ? part[(uint64_t)(b + j) * 16 + q] : 0.0;
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (b + j < b1) neumaier_add(s, c, x[j]);
+        }
+    }
+    double *ss = red, *cc = red + 64 * 16;
+    ss[threadIdx.x] = s;
+    cc[threadIdx.x] = c;
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) {
+        __syncthreads();
+        if (seg < h) {
+            const int o = threadIdx.x + h * 16;
+            double cs = cc[threadIdx.x] + cc[o], sv = ss[threadIdx.x];
+            neumaier_add(sv, cs, ss[o]);
+            ss[threadIdx.x] = sv;
+            cc[threadIdx.x] = cs;
+        }
+    }
+    if (threadIdx.x < nq) out[threadIdx.x] = ss[threadIdx.x] + cc[threadIdx.x];
+}
+
 constexpr int NSTAT = 13;   // S, sum p ln p, sum ln p, sum u^k (k = 1..10)
 
 // Natural logarithm of a positive finite double, to a few units in the last
