@@ -83,7 +83,7 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 // statistics chunk written as a partial row of the instance.
 template <int VB>
 __device__ __forceinline__ void run_item(const BRound &R, const BInst &I, uint64_t chunk, int lane, int wave,
-                                         double *red, unsigned long long *zred) {
+                                         double *red, unsigned long long *zred, LnEntry *tab) {
     if (R.vb > 0) {
 #pragma unroll 1
         for (int i = 0; i < R.tpi / 4; i++) {
@@ -98,6 +98,8 @@ __device__ __forceinline__ void run_item(const BRound &R, const BInst &I, uint64
 #pragma unroll
     for (int q = 0; q < NSTAT; q++) acc[q] = 0.0;
     unsigned zeros = 0;
+    load_ln_table(tab);
+    __syncthreads();
     const double Nd = ldexp(1.0, I.n);
     const gptr<cpx<float>> src =
         (gptr<cpx<float>>)(reinterpret_cast<cpx<float> *>(I.psi) + (chunk << I.stat_bits));
@@ -110,9 +112,12 @@ __device__ __forceinline__ void run_item(const BRound &R, const BInst &I, uint64
             buf[v].re = src[j0 + v * BLOCK].re;
             buf[v].im = src[j0 + v * BLOCK].im;
         }
+        double p[UNR];
 #pragma unroll
-        for (int v = 0; v < UNR; v++) stat_add(acc, zeros, prob_of(buf[v]), Nd);
+        for (int v = 0; v < UNR; v++) p[v] = prob_of(buf[v]);
+        stat_add_n<UNR>(acc, zeros, p, Nd, tab);
     }
+    stat_finish(acc, Nd);
     block_sum<double, NSTAT>(acc, red);
     zeros = wave_sum(zeros);
     if (lane == 0) zred[threadIdx.x >> 6] = zeros;
@@ -142,12 +147,13 @@ __global__ __launch_bounds__(BLOCK) void k_batch_round(const BRound *__restrict_
                                                        const BInst *__restrict__ insts) {
     __shared__ double red[4 * NSTAT];
     __shared__ unsigned long long zred[4];
+    __shared__ LnEntry tab[LN_BINS];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t item = item0 + blockIdx.x;
     const BRound &R = rounds[item_round[item]];
     const BInst I = insts[R.inst];
-    run_item<VB>(R, I, item - R.first, lane, wave, red, zred);
+    run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab);
 }
 
 // One workgroup per instance.  (One thread per quantity walking the rows took
@@ -171,6 +177,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_persistent(const BRound *__rest
     __shared__ int s_flag;
     __shared__ double red[4 * NSTAT];
     __shared__ unsigned long long zred[4];
+    __shared__ LnEntry tab[LN_BINS];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (;;) {
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_persistent(const BRound *__rest
         __threadfence();   // acquire for every wave of the workgroup
         if (!__builtin_amdgcn_readfirstlane(s_flag)) continue;   // item given up (error raised)
         const BInst I = insts[inst];
-        run_item<VB>(R, I, item - R.first, lane, wave, red, zred);
+        run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab);
         __threadfence();   // release this item's writes
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -34,43 +34,66 @@ __global__ __launch_bounds__(RB) void k_probs(const cpx<T> *__restrict__ psi, ui
 // zero count; u = N p
 // ---------------------------------------------------------------------------
 
+// Bound by HBM once an amplitude takes about 45 VALU issues (the table
+// logarithm and the shared powers of stat_add; it was FP64-bound at about 75).
+// The next UNR amplitudes of a thread are loaded before the current ones are
+// used.  chunk is a multiple of RB * UNR or, for the smallest states, less.
 template <typename T, bool FULL>
 __global__ __launch_bounds__(RB) void k_stats(const cpx<T> *__restrict__ psi, uint64_t chunk,
                                               double Nd, double *__restrict__ part) {
     __shared__ double red[4 * NSTAT];
     __shared__ unsigned zred[4];
+    __shared__ LnEntry tab[FULL ? LN_BINS : 1];
+    constexpr int UNR = 4;
+    const uint64_t start = (uint64_t)blockIdx.x * chunk;
+    const uint64_t end = start + chunk, main_end = end - chunk % (RB * UNR);
+    uint64_t j0 = start + threadIdx.x;
+    cpx<T> buf[UNR], nxt[UNR];
+    if (j0 < main_end) {
+#pragma unroll
+        for (int u = 0; u < UNR; u++) buf[u] = psi[j0 + (uint64_t)u * RB];
+    }
+    if (FULL) {
+        load_ln_table(tab);
+        __syncthreads();
+    }
     double acc[NSTAT];
 #pragma unroll
     for (int i = 0; i < NSTAT; i++) acc[i] = 0.0;
     unsigned zeros = 0;
-    const uint64_t start = (uint64_t)blockIdx.x * chunk;
-    // UNR loads in flight per thread before any use over the whole multiple
-    // of RB * UNR (all of the chunk once the state has 2^12 amplitudes),
-    // then one amplitude per thread and step over the rest
-    constexpr int UNR = 8;
-    const uint64_t end = start + chunk, main_end = end - chunk % (RB * UNR);
-    for (uint64_t j0 = start + threadIdx.x; j0 < main_end; j0 += RB * UNR) {
-        cpx<T> buf[UNR];
+    for (; j0 < main_end; j0 += RB * UNR) {
+        const uint64_t jn = j0 + RB * UNR < main_end ? j0 + RB * UNR : j0;
 #pragma unroll
-        for (int u = 0; u < UNR; u++) buf[u] = psi[j0 + (uint64_t)u * RB];
+        for (int u = 0; u < UNR; u++) nxt[u] = psi[jn + (uint64_t)u * RB];
+        double p[UNR];
 #pragma unroll
-        for (int u = 0; u < UNR; u++) {
-            const double p = prob_of(buf[u]);
-            if (FULL) stat_add(acc, zeros, p, Nd);
-            else acc[0] += p;
+        for (int u = 0; u < UNR; u++) p[u] = prob_of(buf[u]);
+        if constexpr (FULL) {
+            stat_add_n<UNR>(acc, zeros, p, Nd, tab);
+        } else {
+#pragma unroll
+            for (int u = 0; u < UNR; u++) acc[0] += p[u];
         }
+#pragma unroll
+        for (int u = 0; u < UNR; u++) buf[u] = nxt[u];
     }
     for (uint64_t j = main_end + threadIdx.x; j < end; j += RB) {
         const double p = prob_of(psi[j]);
-        if (FULL) stat_add(acc, zeros, p, Nd);
+        if (FULL) stat_add(acc, zeros, p, Nd, tab);
         else acc[0] += p;
     }
-    block_sum<double, NSTAT>(acc, red);
+    stat_finish(acc, Nd);
+    if constexpr (FULL) {
+        block_sum<double, NSTAT>(acc, red);
+    } else {
+        double s1[1] = {acc[0]};
+        block_sum<double, 1>(s1, red);
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     zeros = wave_sum(zeros);
     if (lane == 0) zred[wave] = zeros;
     __syncthreads();
-    if (threadIdx.x < NSTAT) part[(uint64_t)blockIdx.x * 16 + threadIdx.x] = red[threadIdx.x];
+    if (threadIdx.x < (FULL ? NSTAT : 1)) part[(uint64_t)blockIdx.x * 16 + threadIdx.x] = red[threadIdx.x];
     if (threadIdx.x == NSTAT) {
         const unsigned long long z = (unsigned long long)zred[0] + zred[1] + zred[2] + zred[3];
         part[(uint64_t)blockIdx.x * 16 + NSTAT] = (double)z;
@@ -85,11 +108,14 @@ __global__ __launch_bounds__(CMB_THREADS) void k_combine(const double *__restric
     combine_rows_wg(part, nblocks, nq, out, red);
 }
 
+constexpr uint64_t STATS_BLOCKS = 2048;
 static void stats_grid(int n, int *nblocks, uint64_t *chunk) {
     const uint64_t N = 1ull << n;
-    uint64_t nb = N >> 12;
+    // four amplitudes per thread at least; 2^21 amplitudes fill the chip's
+    // 2048 workgroup slots
+    uint64_t nb = N >> 10;
     if (nb < 1) nb = 1;
-    if (nb > 2048) nb = 2048;
+    if (nb > STATS_BLOCKS) nb = STATS_BLOCKS;
     *nblocks = (int)nb;
     *chunk = N / nb;
 }
@@ -392,6 +418,9 @@ __global__ __launch_bounds__(RB) void k_stats_weights(const S *__restrict__ src,
 #pragma unroll
     for (int i = 0; i < NSTAT; i++) acc[i] = 0.0;
     unsigned zeros = 0;
+    __shared__ LnEntry tab[LN_BINS];
+    load_ln_table(tab);
+    __syncthreads();
     constexpr int UNR = 8;   // loads in flight per lane
     for (uint64_t b = blockIdx.x; b < nbk; b += gridDim.x) {
       for (int j = wave; j < nsub; j += RB / 64) {
@@ -402,17 +431,18 @@ __global__ __launch_bounds__(RB) void k_stats_weights(const S *__restrict__ src,
             S buf[UNR];
 #pragma unroll
             for (int u = 0; u < UNR; u++) buf[u] = src[start + e0 + (uint64_t)u * 64];
+            double p[UNR];
 #pragma unroll
             for (int u = 0; u < UNR; u++) {
-                const double p = prob_of(buf[u]);
-                w += weight_of(p);
-                stat_add(acc, zeros, p, Nd);
+                p[u] = prob_of(buf[u]);
+                w += weight_of(p[u]);
             }
+            stat_add_n<UNR>(acc, zeros, p, Nd, tab);
         }
         for (uint64_t e = main_end + lane; e < slen; e += 64) {
             const double p = prob_of(src[start + e]);
             w += weight_of(p);
-            stat_add(acc, zeros, p, Nd);
+            stat_add(acc, zeros, p, Nd, tab);
         }
         w = wave_sum_u64(w);
         if (lane == 0) {
@@ -428,6 +458,7 @@ __global__ __launch_bounds__(RB) void k_stats_weights(const S *__restrict__ src,
       }
       __syncthreads();   // sh is reused by the next bucket
     }
+    stat_finish(acc, Nd);
     block_sum<double, NSTAT>(acc, red);
     zeros = wave_sum(zeros);
     if (lane == 0) zred[wave] = zeros;

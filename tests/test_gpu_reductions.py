@@ -33,3 +33,32 @@ def test_cross_entropy_row_counts(k):
     # k logarithms of a few ulp each, compensated sums
     assert abs(ce - ce0) <= 1e-13 * abs(ce0) and abs(dh - dh0) <= 1e-12 and z == z0
     st.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 5, 9, 10, 11, 12, 13, 20, 21, 22])
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_moments_across_the_work_split(n, dtype):
+    # from less than one amplitude per thread to several loads per thread and
+    # all partial rows; probabilities near 1 and 1/2 among them (the bin
+    # edges of the table logarithm), exact zeros, and subnormals in complex128
+    psi, st = state_of(n, dtype, 50 + n)
+    st.close()
+    rng = np.random.default_rng(n)
+    idx = rng.choice(psi.size, min(psi.size, 24), replace=False)
+    special = [0.0, 1.0, np.sqrt(0.5), np.sqrt(1 - 2.0 ** -8), np.sqrt(1 + 2.0 ** -8), np.sqrt(0.69987), 1e-12]
+    if dtype == "c128":
+        special += [1e-155, 1e-161]
+    for i, v in zip(idx[1:], special * 3):
+        psi[i] = v
+    st = sv.State(n, dtype, tensor=torch.from_numpy(psi).to("cuda"))
+    got, want = st.moments(), oracle.stats(oracle.probs(psi))
+    both, _ = st.moments_and_sample(0, 1)
+    st.close()
+    for m in (got, both):
+        assert m["zero_count"] == want["zero_count"]
+        # logarithms of at most 2 ulp and compensated sums; the entropy may
+        # cancel against ln S
+        for key in ("norm", "entropy"):
+            assert abs(m[key] - want[key]) <= 1e-13 * max(1, abs(np.log(want["norm"])), abs(want[key])), key
+        assert m["unif_ce"] == want["unif_ce"] or abs(m["unif_ce"] - want["unif_ce"]) <= 1e-13 * abs(want["unif_ce"])
+        np.testing.assert_allclose(m["moments"], want["moments"], rtol=1e-13)
