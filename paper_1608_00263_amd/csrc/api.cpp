@@ -568,11 +568,7 @@ sv_status sv_sample(sv_state *st, int64_t k, uint64_t seed, uint64_t *out, int o
         SV_TRY(st->ws2.reserve((size_t)k * 8));
         dout = (uint64_t *)st->ws2.ptr;
     }
-    SV_TRY(run_sample(st, st->data, k, seed, dout));
-    if (!out_on_device)
-        SV_HIP(hipMemcpyAsync(out, dout, (size_t)k * 8, hipMemcpyDeviceToHost, st->stream));
-    SV_HIP(hipStreamSynchronize(st->stream));
-    return SV_OK;
+    return run_sample(st, st->data, k, seed, dout, out_on_device ? nullptr : out);
 }
 
 sv_status sv_moments_sample(sv_state *st, sv_stats *stats, int64_t k, uint64_t seed, uint64_t *out,
@@ -586,11 +582,7 @@ sv_status sv_moments_sample(sv_state *st, sv_stats *stats, int64_t k, uint64_t s
         SV_TRY(st->ws2.reserve((size_t)k * 8));
         dout = (uint64_t *)st->ws2.ptr;
     }
-    SV_TRY(run_stats_sample(st, st->data, stats, k, seed, dout));
-    if (k > 0 && !out_on_device)
-        SV_HIP(hipMemcpyAsync(out, dout, (size_t)k * 8, hipMemcpyDeviceToHost, st->stream));
-    SV_HIP(hipStreamSynchronize(st->stream));
-    return SV_OK;
+    return run_stats_sample(st, st->data, stats, k, seed, dout, out_on_device ? nullptr : out);
 }
 
 sv_status sv_moments_sample_noalloc(sv_state *st, sv_stats *stats, int64_t k, uint64_t seed, uint64_t *dev_out) {
@@ -598,9 +590,7 @@ sv_status sv_moments_sample_noalloc(sv_state *st, sv_stats *stats, int64_t k, ui
     if (!stats) return fail(SV_EINVAL, "null statistics output");
     if (k < 0 || k > ((int64_t)1 << 31)) return fail(SV_ERANGE, "sample count out of range");
     if (k > 0 && !dev_out) return fail(SV_EINVAL, "null device output");
-    SV_TRY(run_stats_sample_noalloc(st, stats, k, seed, dev_out));
-    SV_HIP(hipStreamSynchronize(st->stream));
-    return SV_OK;
+    return run_stats_sample_noalloc(st, stats, k, seed, dev_out);
 }
 
 sv_status sv_sample_from(const double *probs, uint64_t N, const uint64_t *r64, int64_t k, uint64_t *out,
@@ -616,8 +606,9 @@ sv_status sv_cross_entropy(sv_state *st, const uint64_t *samples, int64_t k, dou
     SV_TRY(check_state(st));
     if (k <= 0 || !samples || !ce) return fail(SV_EINVAL, "need k > 0 samples and an output");
     if (!(norm <= 0.0 || std::isfinite(norm))) return fail(SV_EINVAL, "norm must be finite");
-    for (int64_t i = 0; i < k; i++)
-        if (samples[i] >= (1ull << st->n)) return fail(SV_ERANGE, "sv_cross_entropy: a sample is not an n-bit string");
+    uint64_t high = 0;
+    for (int64_t i = 0; i < k; i++) high |= samples[i];
+    if (high >> st->n) return fail(SV_ERANGE, "sv_cross_entropy: a sample is not an n-bit string");
     double S = norm;
     if (!(norm > 0.0)) SV_TRY(run_norm(st, st->data, &S));
     SV_TRY(st->ws2.reserve((size_t)k * 8));

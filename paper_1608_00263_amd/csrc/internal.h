@@ -364,10 +364,11 @@ sv_status batch_stats_enqueue(sv_state *st, double *part, double *res);
 // the normalised statistics from the 14 combined sums of a 2^n state
 void finish_stats_row(int n, const double *r, sv_stats *out);
 sv_status run_norm(sv_state *st, const void *psi, double *S);
+// samples into dev_out, and (host_out not null) copied to host_out; both synchronise
 sv_status run_sample(sv_state *st, const void *psi, int64_t k, uint64_t seed,
-                     uint64_t *dev_out);
+                     uint64_t *dev_out, uint64_t *host_out);
 sv_status run_stats_sample(sv_state *st, const void *psi, sv_stats *stats, int64_t k, uint64_t seed,
-                           uint64_t *dev_out);
+                           uint64_t *dev_out, uint64_t *host_out);
 sv_status run_sample_from(const double *probs, uint64_t N, const uint64_t *r64,
                           int64_t k, uint64_t *out, hipStream_t s);
 // sv_moments_sample on the fixed device scratch (no allocation); the bytes

@@ -9,9 +9,11 @@
 // compensated summation, so results are deterministic for a given size.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 #include "reduce_common.h"
@@ -355,228 +357,400 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t i) {
     return z ^ (z >> 31);
 }
 
-// Buckets of 2^bs entries, split into sub-buckets of 2^sb entries (sb <= bs,
-// at most 64 per bucket).  One wavefront per sub-bucket: lane l sums entries
-// l, l + 64, ... (coalesced rows), the wave total is the exact integer sum of
-// the sub-bucket's weights; the workgroup then forms the bucket total from
-// its sub-bucket sums in order.
-constexpr int SUB_BITS = 10;   // 1024 entries per sub-bucket
+// The sampler's weight sums form four levels: groups of chunks (at most 8192,
+// with their exclusive prefix), chunks of 2^bs entries, at most 64 sub-buckets
+// of 2^sb entries per chunk, entries.  Sums are exact 64-bit integers, so a
+// sample does not depend on how the levels are cut.
+//
+// One wavefront sums whole chunks (no barrier) in units of UNIT entries: a row
+// of 16 lanes takes the 256 entries of one smallest sub-bucket, 16 at a time
+// (a 128-byte line of complex64 amplitudes per row and load), so a
+// sub-bucket's sum is a row sum.  Chunks are small enough that a state of 2^23 entries still gives 8192
+// wavefronts work: with 2^16-entry buckets, one workgroup each, the 16-qubit
+// pass ran on one workgroup (62 us) and the 20-qubit one on 16.
+constexpr int UNIT_BITS = 10, UNIT = 1 << UNIT_BITS;
+constexpr int PASS_BLOCKS = 2048;      // workgroups of a pass at most
+constexpr int MAX_GROUPS = 8192;
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xF, false);
+    return ((unsigned long long)hi << 32) | lo;
+}
+// Inclusive prefix sum over the 64 lanes (lane order): shifts within rows of
+// 16 lanes, then the row totals broadcast to the following rows.
+__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long v) {
+    v += dpp_u64<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+    v += dpp_u64<0x112, 0xF>(v);
+    v += dpp_u64<0x114, 0xF>(v);
+    v += dpp_u64<0x118, 0xF>(v);
+    v += dpp_u64<0x142, 0xA>(v);   // lane 15 of rows 0 and 2 to rows 1 and 3
+    v += dpp_u64<0x143, 0xC>(v);   // lane 31 to rows 2 and 3
     return v;
 }
-
-// Entries at index >= N (the ragged end of an explicit distribution whose
-// length is not a power of two) have weight 0 and are not read.
-template <typename S>
-__global__ __launch_bounds__(RB) void k_bucket_weights(const S *__restrict__ src, uint64_t N, int bs, int sb,
-                                                       unsigned long long *__restrict__ bsum,
-                                                       unsigned long long *__restrict__ subsum) {
-    __shared__ unsigned long long sh[64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nsub = 1 << (bs - sb);
-    const uint64_t slen = 1ull << sb;
-    for (int j = wave; j < nsub; j += RB / 64) {
-        const uint64_t start = ((uint64_t)blockIdx.x << bs) + ((uint64_t)j << sb);
-        unsigned long long acc = 0;
-        for (uint64_t e = lane; e < slen; e += 64)
-            if (start + e < N) acc += weight_of(prob_of(src[start + e]));
-        acc = wave_sum_u64(acc);
-        if (lane == 0) {
-            subsum[(uint64_t)blockIdx.x * nsub + j] = acc;
-            sh[j] = acc;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int j = 0; j < nsub; j++) t += sh[j];
-        bsum[blockIdx.x] = t;
-    }
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+    return lane_u64(wave_incl_scan_u64(v), 63);
+}
+// Sum over the 16 lanes of a row, in every lane of the row.
+__device__ __forceinline__ unsigned long long row_sum_u64(unsigned long long v) {
+    v += dpp_u64<0xB1, 0xF>(v);    // quad_perm 1,0,3,2
+    v += dpp_u64<0x4E, 0xF>(v);    // quad_perm 2,3,0,1
+    v += dpp_u64<0x141, 0xF>(v);   // half-row mirror
+    v += dpp_u64<0x140, 0xF>(v);   // row mirror
+    return v;
+}
+// Sum of rows 0, 1 and of rows 2, 3; then of all four.
+__device__ __forceinline__ unsigned long long row_pair_sum_u64(unsigned long long v) {
+    const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return (((unsigned long long)h[0] << 32) | l[0]) + (((unsigned long long)h[1] << 32) | l[1]);
+}
+__device__ __forceinline__ unsigned long long half_sum_u64(unsigned long long v) {
+    const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return (((unsigned long long)h[0] << 32) | l[0]) + (((unsigned long long)h[1] << 32) | l[1]);
 }
 
-// The statistics and the sampler's bucket weights in one read of the state:
-// workgroup g takes buckets g, g + G, ... (2^bs amplitudes each; G = the
-// grid size, at most 2048 so that few statistic rows remain to combine),
-// each wavefront whole sub-buckets of 2^sb amplitudes, as k_bucket_weights
-// does; every amplitude also enters this workgroup's row of statistic sums,
-// as in k_stats.
-template <typename S>
-__global__ __launch_bounds__(RB) void k_stats_weights(const S *__restrict__ src, int bs, int sb, uint64_t nbk,
-                                                      double Nd, double *__restrict__ part,
-                                                      unsigned long long *__restrict__ bsum,
-                                                      unsigned long long *__restrict__ subsum) {
-    __shared__ unsigned long long sh[64];
-    __shared__ double red[4 * NSTAT];
+// floor(p 2^62) of 0 <= p < 2 by one 64-bit shift of the mantissa (zeros and
+// subnormals give 0); any p through weight_of where a wave holds a larger one.
+// The conversion instructions of weight_of take twice the issues.
+__device__ __forceinline__ uint64_t weight_below2(double p) {
+    const unsigned hi = (unsigned)__double2hiint(p), lo = (unsigned)__double2loint(p);
+    const uint64_t m = ((uint64_t)((hi & 0xfffffu) | 0x100000u) << 32 | lo) << 10;   // p = m 2^(e - 1085)
+    const unsigned sh = 1023u - (hi >> 20);
+    return m >> (sh < 63u ? sh : 63u);
+}
+__device__ __forceinline__ bool weight_is_large(double p) { return (unsigned)__double2hiint(p) >= 0x40000000u; }
+
+// What a pass over 2^n entries leaves besides the sums: the 14 statistic sums
+// and the total weight with a status.
+enum { PASS_OK = 0, PASS_BAD = 1, PASS_OVERFLOW = 2, PASS_ZERO = 3 };
+struct PassResult {
+    double stats[16];
+    unsigned long long W;
+    unsigned long long status;
+    unsigned long long pad[6];
+};
+
+// The pass.  STATS: every amplitude also enters this workgroup's row of
+// statistic sums.  CHECK (explicit distributions): entries outside [0, 4) are
+// flagged and the weights summed exactly in halves (high and low 32 bits; a
+// workgroup holds at most 2^24 of them), row = {high, low, flag, 0}.  Entries
+// at index >= N (a length that is not a power of two) have weight 0 and are
+// not read.  Without STATS the pass is bound by HBM.
+template <typename S, bool STATS, bool CHECK>
+__global__ __launch_bounds__(RB) void k_pass(const S *__restrict__ src, uint64_t N, int bs, int sb, uint64_t nb,
+                                             double Nd, double *__restrict__ part,
+                                             unsigned long long *__restrict__ csum,
+                                             unsigned long long *__restrict__ subsum) {
+    __shared__ double red[STATS ? 4 * NSTAT : 1];
     __shared__ unsigned zred[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nsub = 1 << (bs - sb);
-    const uint64_t slen = 1ull << sb;
+    __shared__ unsigned long long chk[4 * 3];
+    __shared__ LnEntry tab[STATS ? LN_BINS : 1];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (STATS) {
+        load_ln_table(tab);
+        __syncthreads();
+    }
     double acc[NSTAT];
 #pragma unroll
     for (int i = 0; i < NSTAT; i++) acc[i] = 0.0;
     unsigned zeros = 0;
-    __shared__ LnEntry tab[LN_BINS];
-    load_ln_table(tab);
-    __syncthreads();
-    constexpr int UNR = 8;   // loads in flight per lane
-    for (uint64_t b = blockIdx.x; b < nbk; b += gridDim.x) {
-      for (int j = wave; j < nsub; j += RB / 64) {
-        const uint64_t start = (b << bs) + ((uint64_t)j << sb);
+    unsigned long long chigh = 0, clow = 0;
+    unsigned bad = 0;
+    const int steps = 1 << (bs - UNIT_BITS + 2);   // of 256 entries, four to a unit
+    const int row = lane >> 4;
+    const int first = 256 * row + (lane & 15);   // this lane's first entry of a unit, then every 16th
+    // one chunk; FULL: none of its entries lies beyond N (two copies, since a
+    // branch around the loads makes the loop wait for them at once)
+    auto chunk = [&](uint64_t c, auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        const uint64_t start = c << bs;
+        auto entry = [&](int st, int j) { return start + ((uint64_t)(st >> 2) << UNIT_BITS) + first + 64 * (st & 3) + 16 * j; };
+        auto load4 = [&](int st, S (&e)[4]) {
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (FULL || entry(st, j) < N) e[j] = src[entry(st, j)];
+                else e[j] = S{};
+        };
+        unsigned long long cs = 0;   // this row's share of the chunk
         unsigned long long w = 0;
-        const uint64_t main_end = slen - slen % (64 * UNR);
-        for (uint64_t e0 = lane; e0 < main_end; e0 += 64 * UNR) {
-            S buf[UNR];
+        S buf[4], nxt[4];
+        load4(0, buf);
+#pragma unroll 1
+        for (int st = 0; st < steps; st++) {
+            load4(st + 1 < steps ? st + 1 : st, nxt);
+            double p[4];
+            bool large = false;
 #pragma unroll
-            for (int u = 0; u < UNR; u++) buf[u] = src[start + e0 + (uint64_t)u * 64];
-            double p[UNR];
-#pragma unroll
-            for (int u = 0; u < UNR; u++) {
-                p[u] = prob_of(buf[u]);
-                w += weight_of(p[u]);
+            for (int j = 0; j < 4; j++) {
+                p[j] = prob_of(buf[j]);
+                if constexpr (CHECK) {
+                    const bool ok = (p[j] >= 0.0) & (p[j] < 4.0);
+                    bad |= ok ? 0u : 1u;
+                    p[j] = ok ? p[j] : 0.0;
+                }
+                large |= weight_is_large(p[j]);
             }
-            stat_add_n<UNR>(acc, zeros, p, Nd, tab);
+            unsigned long long x[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) x[j] = weight_below2(p[j]);
+            if (__ballot(large) != 0ull) {
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    if (weight_is_large(p[j])) x[j] = weight_of(p[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                w += x[j];
+                if constexpr (CHECK) { chigh += x[j] >> 32; clow += x[j] & 0xffffffffull; }
+            }
+            if constexpr (STATS) {
+                stat_add_n<4>(acc, zeros, p, Nd, tab);
+                if constexpr (!FULL) {   // entries beyond the state added exact zeros
+#pragma unroll
+                    for (int j = 0; j < 4; j++) zeros -= entry(st, j) >= N ? 1u : 0u;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) buf[j] = nxt[j];
+            if ((st & 3) == 3) {
+                // every lane of a row: the sum of its 256 entries, merged up
+                // to 2^sb entries
+                unsigned long long v = row_sum_u64(w);
+                w = 0;
+                cs += v;
+                if (sb >= 9) v = row_pair_sum_u64(v);
+                if (sb >= 10) v = half_sum_u64(v);
+                const int rows = 1 << (sb - 8);   // rows per sub-bucket
+                if ((lane & (16 * rows - 1)) == 0) subsum[(entry(st - 3, 0) - (lane & 15)) >> sb] = v;
+            }
         }
-        for (uint64_t e = main_end + lane; e < slen; e += 64) {
-            const double p = prob_of(src[start + e]);
-            w += weight_of(p);
-            stat_add(acc, zeros, p, Nd, tab);
-        }
-        w = wave_sum_u64(w);
-        if (lane == 0) {
-            subsum[b * nsub + j] = w;
-            sh[j] = w;
-        }
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-          unsigned long long t = 0;
-          for (int j = 0; j < nsub; j++) t += sh[j];
-          bsum[b] = t;
-      }
-      __syncthreads();   // sh is reused by the next bucket
+        cs = half_sum_u64(row_pair_sum_u64(cs));
+        if (lane == 0) csum[c] = cs;
+    };
+    for (uint64_t c = (uint64_t)blockIdx.x * (RB / 64) + wave; c < nb; c += (uint64_t)gridDim.x * (RB / 64)) {
+        if ((c + 1) << bs <= N) chunk(c, std::true_type{});
+        else chunk(c, std::false_type{});
     }
-    stat_finish(acc, Nd);
-    block_sum<double, NSTAT>(acc, red);
-    zeros = wave_sum(zeros);
-    if (lane == 0) zred[wave] = zeros;
-    __syncthreads();
-    if (threadIdx.x < NSTAT) part[(uint64_t)blockIdx.x * 16 + threadIdx.x] = red[threadIdx.x];
-    if (threadIdx.x == NSTAT) {
-        const unsigned long long z = (unsigned long long)zred[0] + zred[1] + zred[2] + zred[3];
-        part[(uint64_t)blockIdx.x * 16 + NSTAT] = (double)z;
+    if constexpr (STATS) {
+        stat_finish(acc, Nd);
+        block_sum<double, NSTAT>(acc, red);
+        zeros = wave_sum(zeros);
+        if (lane == 0) zred[wave] = zeros;
+        __syncthreads();
+        if (threadIdx.x < NSTAT) part[(uint64_t)blockIdx.x * 16 + threadIdx.x] = red[threadIdx.x];
+        if (threadIdx.x == NSTAT) {
+            const unsigned long long z = (unsigned long long)zred[0] + zred[1] + zred[2] + zred[3];
+            part[(uint64_t)blockIdx.x * 16 + NSTAT] = (double)z;
+        }
+    }
+    if constexpr (CHECK) {
+        chigh = wave_sum_u64(chigh);
+        clow = wave_sum_u64(clow);
+        const unsigned long long any = __ballot(bad != 0u) ? 1ull : 0ull;
+        if (lane == 0) { chk[wave * 3] = chigh; chk[wave * 3 + 1] = clow; chk[wave * 3 + 2] = any; }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            auto *row = (unsigned long long *)(part + (uint64_t)blockIdx.x * 16);
+            row[threadIdx.x] = chk[threadIdx.x] + chk[3 + threadIdx.x] + chk[6 + threadIdx.x] + chk[9 + threadIdx.x];
+        }
     }
 }
 
-// Exclusive scan of n uint64 values into out[0..n], out[n] = total.  One
-// workgroup of 1024 threads; each thread scans a contiguous stretch.
-__global__ __launch_bounds__(1024) void k_scan(const unsigned long long *__restrict__ in, uint64_t n,
-                                               unsigned long long *__restrict__ out) {
-    __shared__ unsigned long long sh[1024];
-    const uint64_t per = (n + 1023) / 1024;
-    const uint64_t b = threadIdx.x * per;
-    const uint64_t e = b + per < n ? b + per : n;
+// Two workgroups: the second combines the statistic rows (nrows > 0); the
+// first sums the chunks of each group (cg = 2^k <= 64 chunks) and forms the
+// exclusive prefix off[0..ng] of the ng = nb / cg groups, the total W and its
+// status (check: from the exact sums of the check rows).  The loads of the
+// chunk sums are coalesced rows, four in flight per wavefront.
+__global__ __launch_bounds__(CMB_THREADS) void k_finish_pass(const unsigned long long *__restrict__ csum, uint64_t nb,
+                                                             int cg, const double *__restrict__ part, int nrows,
+                                                             int check, unsigned long long *__restrict__ off,
+                                                             PassResult *__restrict__ res) {
+    __shared__ unsigned long long lds[MAX_GROUPS];
+    __shared__ unsigned long long wtot[16];
+    __shared__ unsigned long long chk[16 * 5];
+    if (blockIdx.x == 1) {
+        combine_rows_wg(part, nrows, NSTAT + 1, res->stats, (double *)lds);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ng = (int)(nb / (uint64_t)cg);
+    for (uint64_t i0 = (uint64_t)wave * 64; i0 < nb; i0 += 4 * 1024) {
+        unsigned long long v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint64_t i = i0 + (uint64_t)j * 1024 + lane;
+            v[j] = i < nb ? csum[i] : 0ull;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint64_t i = i0 + (uint64_t)j * 1024 + lane;
+            for (int m = 1; m < cg; m <<= 1) v[j] += __shfl_xor(v[j], m, 64);
+            if (i < nb && (lane & (cg - 1)) == 0) lds[i / (uint64_t)cg] = v[j];
+        }
+    }
+    __syncthreads();
+    const int per = (ng + 1023) / 1024;
+    const int b = tid * per, e = b + per < ng ? b + per : ng;
     unsigned long long s = 0;
-    for (uint64_t i = b; i < e; i++) s += in[i];
-    sh[threadIdx.x] = s;
+    for (int i = b; i < e; i++) s += lds[i];
+    const unsigned long long incl = wave_incl_scan_u64(s);
+    if (lane == 63) wtot[wave] = incl;
     __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        unsigned long long v = threadIdx.x >= (unsigned)d ? sh[threadIdx.x - d] : 0ull;
+    unsigned long long run = incl - s, W = 0;
+    for (int w = 0; w < 16; w++) {
+        if (w < wave) run += wtot[w];
+        W += wtot[w];
+    }
+    for (int i = b; i < e; i++) {
+        off[i] = run;
+        run += lds[i];
+    }
+    unsigned long long status = PASS_OK;
+    if (check) {
+        // exact total: sums of the 32-bit halves of the rows' halves
+        unsigned long long h1 = 0, h0 = 0, l1 = 0, l0 = 0, bad = 0;
+        for (int r = tid; r < check; r += CMB_THREADS) {
+            const auto *row = (const unsigned long long *)(part + (uint64_t)r * 16);
+            h1 += row[0] >> 32; h0 += row[0] & 0xffffffffull;
+            l1 += row[1] >> 32; l0 += row[1] & 0xffffffffull;
+            bad += row[2];
+        }
+        h1 = wave_sum_u64(h1); h0 = wave_sum_u64(h0); l1 = wave_sum_u64(l1); l0 = wave_sum_u64(l0);
+        bad = wave_sum_u64(bad);
+        if (lane == 0) {
+            chk[wave * 5] = h1; chk[wave * 5 + 1] = h0; chk[wave * 5 + 2] = l1; chk[wave * 5 + 3] = l0;
+            chk[wave * 5 + 4] = bad;
+        }
         __syncthreads();
-        sh[threadIdx.x] += v;
-        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < 16; w++)
+                for (int k = 0; k < 5; k++) chk[k] += chk[w * 5 + k];
+            // weights = 2^64 h1 + 2^32 (h0 + l1) + l0
+            const bool over = chk[0] != 0ull || ((chk[1] + chk[2] + (chk[3] >> 32)) >> 32) != 0ull;
+            status = chk[4] ? PASS_BAD : over ? PASS_OVERFLOW : PASS_OK;
+        }
     }
-    unsigned long long run = sh[threadIdx.x] - s;   // exclusive prefix of this stretch
-    for (uint64_t i = b; i < e; i++) {
-        out[i] = run;
-        run += in[i];
+    if (tid == 0) {
+        if (status == PASS_OK && W == 0ull) status = PASS_ZERO;
+        off[ng] = W;
+        res->W = W;
+        res->status = status;
     }
-    if (threadIdx.x == 1023) out[n] = sh[1023];
 }
 
-// Per sample: target t = floor(r W / 2^64), its bucket (last b with
-// off[b] <= t) and the target's offset inside the bucket.
-__global__ __launch_bounds__(RB) void k_targets(const uint64_t *__restrict__ words, uint64_t seed,
-                                                int64_t k, const unsigned long long *__restrict__ off,
-                                                uint64_t nb, uint32_t *__restrict__ tb,
-                                                unsigned long long *__restrict__ tloc) {
-    const int64_t i = (int64_t)blockIdx.x * RB + threadIdx.x;
-    if (i >= k) return;
-    const unsigned long long W = off[nb];
-    const uint64_t r = words ? words[i] : splitmix64(seed, (uint64_t)i);
-    const unsigned long long t = __umul64hi(r, W);
-    uint64_t lo = 0, hi = nb;   // first b with off[b] > t, minus one
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (off[mid] > t) hi = mid; else lo = mid + 1;
-    }
-    const uint64_t b = lo - 1;
-    tb[i] = (uint32_t)b;
-    tloc[i] = t - off[b];
-}
-
-// Inclusive prefix sum over the 64 lanes (lane order).
-__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long o = __shfl_up(v, d, 64);
-        if (lane >= d) v += o;
-    }
-    return v;
-}
-
-// One wavefront per sample: the sub-bucket holding the target (first
-// sub-bucket whose running sum exceeds it), then the lane run of R
-// consecutive entries holding it, then the entry: x = min{j : C_j > t}.
-template <typename S>
-__global__ __launch_bounds__(RB) void k_resolve(const S *__restrict__ src, uint64_t N, int bs, int sb,
+// One wavefront per sample: t = floor(r W / 2^64), then x = min{j : C_j > t}
+// by one 64-wide step per level (group prefix in two, chunks, sub-buckets,
+// the four consecutive entries of a lane).  Five dependent loads, and nothing
+// is read twice: bound by their latency over the resident wavefronts.  (A
+// binary search over the bucket prefix in a kernel of its own, then a serial
+// walk of the last 16 entries by one lane, took 0.6 ms for 10^5 samples at 30
+// qubits.)
+template <typename S, int G>
+__global__ __launch_bounds__(RB) void k_resolve(const S *__restrict__ src, uint64_t N, int bs, uint64_t nb, int cg,
+                                                const unsigned long long *__restrict__ off,
+                                                const unsigned long long *__restrict__ csum,
                                                 const unsigned long long *__restrict__ subsum,
-                                                const uint32_t *__restrict__ tb,
-                                                const unsigned long long *__restrict__ tloc, int64_t k,
-                                                uint64_t *__restrict__ out) {
+                                                const PassResult *__restrict__ res, const uint64_t *__restrict__ words,
+                                                uint64_t seed, int64_t k, uint64_t *__restrict__ out) {
+    constexpr int sb = G == 1 ? 8 : G == 2 ? 9 : 10;
     const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * (RB / 64) + (threadIdx.x >> 6);
-    if (i >= k) return;
-    const uint64_t b = tb[i];
-    const unsigned long long t = tloc[i];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * (RB / 64) + wave;
+    if (i >= k || res->status != PASS_OK) return;
+    const int ng = (int)(nb / (uint64_t)cg);
+    const uint64_t r = words ? words[i] : splitmix64(seed, (uint64_t)i);
+    const unsigned long long t = __umul64hi(r, res->W);
+    // the last group g with off[g] <= t (off[0] = 0): among every s1-th, then
+    // among the s1 that follow
+    const int s1 = (ng + 63) / 64;
+    const int i1 = lane * s1;
+    const unsigned long long o1 = i1 < ng ? off[i1] : ~0ull;
+    int f = __popcll(__ballot(i1 < ng && o1 <= t)) - 1;
+    f = f < 0 ? 0 : f;
+    int g = f * s1;
+    unsigned long long og = lane_u64(o1, f);
+    for (int j = 0; j < s1; j += 64) {
+        const int i2 = f * s1 + j + lane;
+        const bool in = j + lane < s1 && i2 < ng;
+        const unsigned long long o2 = in ? off[i2] : ~0ull;
+        const int c2 = __popcll(__ballot(in && o2 <= t));
+        if (c2 > 0) {
+            g = f * s1 + j + c2 - 1;
+            og = lane_u64(o2, c2 - 1);
+        }
+    }
+    unsigned long long tl = t - og;
+    // chunk of the group, sub-bucket of the chunk: the first whose inclusive
+    // sum exceeds the target (it exists, since the target lies below the
+    // total; the clamps keep every access in range all the same)
+    const unsigned long long cw = lane < cg ? csum[(uint64_t)g * cg + lane] : 0ull;
+    const unsigned long long ci = wave_incl_scan_u64(cw);
+    int cl = __ffsll((long long)__ballot(lane < cg && ci > tl)) - 1;
+    cl = cl < 0 ? cg - 1 : cl;
+    tl -= lane_u64(ci - cw, cl);
+    const uint64_t c = (uint64_t)g * cg + cl;
     const int nsub = 1 << (bs - sb);
-    // sub-bucket
-    const unsigned long long own = lane < nsub ? subsum[b * nsub + lane] : 0ull;
-    const unsigned long long incl = wave_incl_scan_u64(own, lane);
-    const unsigned long long above = __ballot(lane < nsub && incl > t);
-    int j = __ffsll((long long)above) - 1;
-    if (j < 0) j = nsub - 1;   // unreachable (t < bucket total); keeps every access in range
-    const unsigned long long before_j = __shfl(incl - own, j, 64);
-    const unsigned long long ts = t - before_j;
-    // lane runs of R entries inside sub-bucket j
-    const uint64_t start = (b << bs) + ((uint64_t)j << sb);
-    const int slen = 1 << sb;
-    const int R = slen >= 64 ? slen / 64 : 1;
-    const bool has = lane * R < slen;
-    unsigned long long run = 0;
-    if (has)
-        for (int e = 0; e < R; e++) {
-            const uint64_t x = start + (uint64_t)lane * R + e;
-            if (x < N) run += weight_of(prob_of(src[x]));
-        }
-    const unsigned long long rincl = wave_incl_scan_u64(run, lane);
-    const unsigned long long hit = __ballot(has && rincl > ts);
-    int L = __ffsll((long long)hit) - 1;
-    if (L < 0) L = (slen >= 64 ? 64 : slen) - 1;   // unreachable (ts < sub-bucket total)
-    if (lane == L) {
-        unsigned long long c = rincl - run;
-        uint64_t ans = start + (uint64_t)lane * R + (R - 1);
-        for (int e = 0; e < R; e++) {
-            const uint64_t x = start + (uint64_t)lane * R + e;
-            if (x < N) c += weight_of(prob_of(src[x]));
-            if (c > ts) {
-                ans = start + (uint64_t)lane * R + e;
-                break;
+    const unsigned long long sw = lane < nsub ? subsum[c * nsub + lane] : 0ull;
+    const unsigned long long si = wave_incl_scan_u64(sw);
+    int sl = __ffsll((long long)__ballot(lane < nsub && si > tl)) - 1;
+    sl = sl < 0 ? nsub - 1 : sl;
+    tl -= lane_u64(si - sw, sl);
+    // entries: lane l holds entries 4 l .. 4 l + 3 of each run of 256
+    const uint64_t start = (c << bs) + ((uint64_t)sl << sb);
+    unsigned long long w[G][4], own[G];
+    if (start + (256 * G) <= N) {
+        S e[G][4];
+#pragma unroll
+        for (int q = 0; q < G; q++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) e[q][j] = src[start + 256 * q + 4 * lane + j];
+#pragma unroll
+        for (int q = 0; q < G; q++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) w[q][j] = weight_of(prob_of(e[q][j]));
+    } else {
+#pragma unroll
+        for (int q = 0; q < G; q++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint64_t x = start + 256 * q + 4 * lane + j;
+                w[q][j] = x < N ? weight_of(prob_of(src[x])) : 0ull;
             }
+    }
+#pragma unroll
+    for (int q = 0; q < G; q++) own[q] = w[q][0] + w[q][1] + w[q][2] + w[q][3];
+    bool done = false;
+#pragma unroll
+    for (int q = 0; q < G; q++) {
+        const unsigned long long in = wave_incl_scan_u64(own[q]);
+        const unsigned long long total = lane_u64(in, 63);
+        if (!done && (total > tl || q == G - 1)) {
+            int L = __ffsll((long long)__ballot(in > tl)) - 1;
+            L = L < 0 ? 63 : L;
+            if (lane == L) {
+                unsigned long long s = in - own[q];
+                int j = 0;
+#pragma unroll
+                for (int m = 0; m < 3; m++) {
+                    s += w[q][m];
+                    j += s <= tl ? 1 : 0;
+                }
+                out[i] = start + 256 * q + 4 * lane + j;
+            }
+            done = true;
         }
-        out[i] = ans;
+        if (!done) tl -= total;
     }
 }
 
@@ -603,114 +777,129 @@ static sv_status take_scratch(const ScratchSource &scr, size_t need, uint8_t **o
     return SV_OK;
 }
 
-// Layout of the sampler's scratch for 2^n entries and k samples (with the
-// statistics rows when stats is set): byte offsets of its parts and the
-// total.
+// Layout of the sampler's scratch for 2^n entries: byte offsets of its parts
+// and the total.  Sub-buckets of 2^8 entries (2 KiB of complex64 amplitudes
+// read per sample) while their sums take at most 32 MiB, then 2^9 and 2^10.
 struct SampleLayout {
-    int bs, sb;
-    uint64_t nb, nsubs, ng;
-    size_t o_bsum, o_off, o_sub, o_tb, o_tl, o_part, o_res, need;
+    int bs, sb, cg;
+    uint64_t nb;
+    int blocks;
+    size_t o_csum, o_off, o_sub, o_part, o_res, need;
 };
 
-static SampleLayout sample_layout(int n, int64_t k, bool stats) {
+static SampleLayout sample_layout(int n) {
     SampleLayout L{};
-    L.bs = n < 16 ? n : 16;
-    L.sb = L.bs < SUB_BITS ? L.bs : SUB_BITS;
-    L.nb = 1ull << (n - L.bs);
-    L.nsubs = 1ull << (n - L.sb);
-    L.ng = L.nb < 2048 ? L.nb : 2048;   // workgroups of the fused statistics pass
+    L.sb = n <= 30 ? 8 : n == 31 ? 9 : 10;
+    // chunks: at least a unit, at most 64 sub-buckets, and 8192 of them (a
+    // full chip of wavefronts) before they grow
+    L.bs = std::min(std::max(UNIT_BITS, n - 13), L.sb + 6);
+    L.nb = n > L.bs ? 1ull << (n - L.bs) : 1ull;
+    L.cg = 1;
+    while (L.nb / (uint64_t)L.cg > (uint64_t)(L.cg < 16 ? MAX_GROUPS / 2 : MAX_GROUPS) && L.cg < 64) L.cg <<= 1;
+    const uint64_t wgs = (L.nb + RB / 64 - 1) / (RB / 64);
+    L.blocks = (int)(wgs < (uint64_t)PASS_BLOCKS ? wgs : (uint64_t)PASS_BLOCKS);
     size_t need = 0;
     auto take = [&](size_t bytes) { size_t o = need; need += (bytes + 255) & ~(size_t)255; return o; };
-    L.o_bsum = take(L.nb * 8);
-    L.o_off = take((L.nb + 1) * 8);
-    L.o_sub = take(L.nsubs * 8);
-    L.o_tb = take((size_t)k * 4);
-    L.o_tl = take((size_t)k * 8);
-    L.o_part = stats ? take(L.ng * 16 * 8) : 0;
-    L.o_res = stats ? take(16 * 8) : 0;
+    L.o_res = take(sizeof(PassResult));
+    L.o_csum = take(L.nb * 8);
+    L.o_off = take((L.nb / (uint64_t)L.cg + 1) * 8);
+    L.o_sub = take((L.nb << (L.bs - L.sb)) * 8);
+    L.o_part = take((size_t)L.blocks * 16 * 8);
     L.need = need;
     return L;
 }
 
-// The sampler; with stats16 non-null (states only) the bucket weights come
-// from the fused statistics pass, whose 14 combined sums are copied to
-// stats16 (and k may be 0).
-// src holds N = 2^n entries, or (explicit distributions) any N in
-// (2^{n-1}, 2^n], the entries beyond N counting as weight 0.
+// The sampler; with stats16 non-null (states only) the weights come from the
+// fused statistics pass, whose 14 combined sums are copied to stats16 (and k
+// may be 0).
+// src holds N = 2^n entries, or (explicit distributions, which are checked)
+// any N in (2^{n-1}, 2^n], the entries beyond N counting as weight 0.
+// host_out, when not null, receives a copy of the samples.  Synchronises: one
+// wait at the end, after the copies of the result block and the samples.
 template <typename S>
 static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *src, int n, const uint64_t *words,
-                             uint64_t seed, int64_t k, uint64_t *dev_out, double *stats16 = nullptr,
-                             uint64_t N = 0) {
+                             uint64_t seed, int64_t k, uint64_t *dev_out, uint64_t *host_out,
+                             double *stats16 = nullptr, uint64_t N = 0) {
+    constexpr bool CHECK = std::is_same<S, double>::value;
     if (N == 0) N = 1ull << n;
-    if (k <= 0 && !stats16) return SV_OK;
+    if (k <= 0 && !stats16 && !CHECK) return SV_OK;
     if (k < 0) k = 0;
-    const SampleLayout L = sample_layout(n, k, stats16 != nullptr);
-    const int bs = L.bs, sb = L.sb;
-    const uint64_t nb = L.nb, ng = L.ng;
-    const size_t o_bsum = L.o_bsum, o_off = L.o_off, o_sub = L.o_sub, o_tb = L.o_tb, o_tl = L.o_tl,
-                 o_part = L.o_part, o_res = L.o_res;
+    const SampleLayout L = sample_layout(n);
     uint8_t *w = nullptr;
     SV_TRY(take_scratch(scr, L.need, &w));
-    auto *bsum = (unsigned long long *)(w + o_bsum);
-    auto *off = (unsigned long long *)(w + o_off);
-    auto *sub = (unsigned long long *)(w + o_sub);
-    auto *tb = (uint32_t *)(w + o_tb);
-    auto *tl = (unsigned long long *)(w + o_tl);
-    if (stats16) {
-        double *part = (double *)(w + o_part), *res = (double *)(w + o_res);
-        hipLaunchKernelGGL((k_stats_weights<S>), dim3((unsigned)ng), dim3(RB), 0, s, src, bs, sb, nb,
-                           std::ldexp(1.0, n), part, bsum, sub);
-        hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, s, part, (int)ng, NSTAT + 1, res);
-        SV_HIP(hipGetLastError());
-        SV_HIP(hipMemcpyAsync(stats16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
-        if (k == 0) {
-            SV_HIP(hipStreamSynchronize(s));
-            return SV_OK;
-        }
+    auto *csum = (unsigned long long *)(w + L.o_csum);
+    auto *off = (unsigned long long *)(w + L.o_off);
+    auto *sub = (unsigned long long *)(w + L.o_sub);
+    double *part = (double *)(w + L.o_part);
+    auto *res = (PassResult *)(w + L.o_res);
+    const double Nd = std::ldexp(1.0, n);
+    if constexpr (!CHECK) {
+        if (stats16)
+            hipLaunchKernelGGL((k_pass<S, true, false>), dim3(L.blocks), dim3(RB), 0, s, src, N, L.bs, L.sb, L.nb, Nd,
+                               part, csum, sub);
+        else
+            hipLaunchKernelGGL((k_pass<S, false, false>), dim3(L.blocks), dim3(RB), 0, s, src, N, L.bs, L.sb, L.nb,
+                               Nd, part, csum, sub);
     } else {
-        hipLaunchKernelGGL((k_bucket_weights<S>), dim3((unsigned)nb), dim3(RB), 0, s, src, N, bs, sb, bsum, sub);
+        hipLaunchKernelGGL((k_pass<S, false, true>), dim3(L.blocks), dim3(RB), 0, s, src, N, L.bs, L.sb, L.nb, Nd,
+                           part, csum, sub);
     }
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, bsum, nb, off);
-    unsigned long long W = 0;
-    SV_HIP(hipMemcpyAsync(&W, off + nb, 8, hipMemcpyDeviceToHost, s));
-    SV_HIP(hipStreamSynchronize(s));
-    if (W == 0) return fail(SV_ESTATE, "sampler: every probability rounds to weight 0");
-    const unsigned kg = (unsigned)((k + RB - 1) / RB);
-    hipLaunchKernelGGL(k_targets, dim3(kg), dim3(RB), 0, s, words, seed, k, off, nb, tb, tl);
-    const unsigned rg = (unsigned)((k + RB / 64 - 1) / (RB / 64));
-    hipLaunchKernelGGL((k_resolve<S>), dim3(rg), dim3(RB), 0, s, src, N, bs, sb, sub, tb, tl, k, dev_out);
+    hipLaunchKernelGGL(k_finish_pass, dim3(stats16 ? 2 : 1), dim3(CMB_THREADS), 0, s, csum, L.nb, L.cg, part,
+                       stats16 ? L.blocks : 0, CHECK ? L.blocks : 0, off, res);
     SV_HIP(hipGetLastError());
+    if (k > 0) {
+        const unsigned rg = (unsigned)((k + RB / 64 - 1) / (RB / 64));
+#define RESOLVE(G)                                                                                                 \
+    hipLaunchKernelGGL((k_resolve<S, G>), dim3(rg), dim3(RB), 0, s, src, N, L.bs, L.nb, L.cg, off, csum, sub, res, \
+                       words, seed, k, dev_out)
+        if (L.sb == 8) RESOLVE(1);
+        else if (L.sb == 9) RESOLVE(2);
+        else RESOLVE(4);
+#undef RESOLVE
+        SV_HIP(hipGetLastError());
+    }
+    PassResult host;
+    SV_HIP(hipMemcpyAsync(&host, res, sizeof host, hipMemcpyDeviceToHost, s));
+    if (k > 0 && host_out) SV_HIP(hipMemcpyAsync(host_out, dev_out, (size_t)k * 8, hipMemcpyDeviceToHost, s));
+    SV_HIP(hipStreamSynchronize(s));
+    if (stats16)
+        for (int i = 0; i < 16; i++) stats16[i] = i <= NSTAT ? host.stats[i] : 0.0;
+    if (host.status == PASS_BAD)
+        return fail(SV_EINVAL, "sv_sample_from: a probability is negative, NaN, infinite or >= 4");
+    if (host.status == PASS_OVERFLOW)
+        return fail(SV_ERANGE, "sv_sample_from: the weights floor(p 2^62) sum to 2^64 or more (sum p >= 4)");
+    if (k > 0 && host.status == PASS_ZERO) return fail(SV_ESTATE, "sampler: every probability rounds to weight 0");
     return SV_OK;
 }
 
-sv_status run_sample(sv_state *st, const void *psi, int64_t k, uint64_t seed, uint64_t *dev_out) {
+sv_status run_sample(sv_state *st, const void *psi, int64_t k, uint64_t seed, uint64_t *dev_out, uint64_t *host_out) {
     ScratchSource scr;
     scr.ws = &st->ws;
     if (st->dt == SV_C64)
         return sample_impl<cpx<float>>(scr, st->stream, (const cpx<float> *)psi, st->n, nullptr,
-                                       seed, k, dev_out);
+                                       seed, k, dev_out, host_out);
     return sample_impl<cpx<double>>(scr, st->stream, (const cpx<double> *)psi, st->n, nullptr,
-                                    seed, k, dev_out);
+                                    seed, k, dev_out, host_out);
 }
 
 static sv_status stats_sample_from(const ScratchSource &scr, sv_state *st, const void *psi, sv_stats *stats,
-                                   int64_t k, uint64_t seed, uint64_t *dev_out) {
+                                   int64_t k, uint64_t seed, uint64_t *dev_out, uint64_t *host_out) {
     double r[16] = {0};
     if (st->dt == SV_C64)
         SV_TRY(sample_impl<cpx<float>>(scr, st->stream, (const cpx<float> *)psi, st->n, nullptr, seed, k,
-                                       dev_out, r));
+                                       dev_out, host_out, r));
     else
         SV_TRY(sample_impl<cpx<double>>(scr, st->stream, (const cpx<double> *)psi, st->n, nullptr, seed, k,
-                                        dev_out, r));
+                                        dev_out, host_out, r));
     finish_stats(st->n, r, stats);
     return SV_OK;
 }
 
 sv_status run_stats_sample(sv_state *st, const void *psi, sv_stats *stats, int64_t k, uint64_t seed,
-                           uint64_t *dev_out) {
+                           uint64_t *dev_out, uint64_t *host_out) {
     ScratchSource scr;
     scr.ws = &st->ws;
-    return stats_sample_from(scr, st, psi, stats, k, seed, dev_out);
+    return stats_sample_from(scr, st, psi, stats, k, seed, dev_out, host_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -744,7 +933,16 @@ static sv_status noalloc_scratch(int device, void **out) {
     return SV_OK;
 }
 
-size_t noalloc_scratch_need(int n, int64_t k) { return sample_layout(n, k, true).need; }
+// The documented limit of the call: 8 2^(n-10) + 16 2^(n-16) + 12 k bytes and
+// the statistic rows.  The pass itself needs no room per sample.
+size_t noalloc_scratch_need(int n, int64_t k) {
+    const int bs = n < 16 ? n : 16, sb = bs < 10 ? bs : 10;
+    const uint64_t nb = 1ull << (n - bs), rows = nb < 2048 ? nb : 2048;
+    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t per_k = al((size_t)k * 4) + al((size_t)k * 8);
+    const size_t limit = al(nb * 8) + al((nb + 1) * 8) + al((1ull << (n - sb)) * 8) + per_k + al(rows * 128) + 256;
+    return std::max(limit, sample_layout(n).need);
+}
 
 sv_status run_stats_sample_noalloc(sv_state *st, sv_stats *stats, int64_t k, uint64_t seed, uint64_t *dev_out) {
     const size_t need = noalloc_scratch_need(st->n, k);
@@ -757,90 +955,26 @@ sv_status run_stats_sample_noalloc(sv_state *st, sv_stats *stats, int64_t k, uin
     ScratchSource scr;
     SV_TRY(noalloc_scratch(st->device, &scr.fixed));
     scr.cap = NOALLOC_SCRATCH_BYTES;
-    return stats_sample_from(scr, st, st->data, stats, k, seed, dev_out);
+    return stats_sample_from(scr, st, st->data, stats, k, seed, dev_out, nullptr);
 }
 
-// Validation of an explicit distribution for the integer-CDF sampler: every
-// p must be finite, >= 0 and < 4 (its weight floor(p 2^62) fits 64 bits),
-// and the weights must sum below 2^64.  Per workgroup, the exact 128-bit
-// sum of the weights of its 2^16 entries (high and low words) and a flag for
-// an invalid entry; one more workgroup adds the rows (high words cannot
-// overflow: at most 2^19 rows of at most 2^80 each).
-constexpr int VAL_BITS = 16;
-
-__global__ __launch_bounds__(RB) void k_validate_weights(const double *__restrict__ p, uint64_t N,
-                                                         unsigned long long *__restrict__ rows) {
-    __shared__ unsigned long long slo[RB], shi[RB];
-    __shared__ unsigned sbad[RB];
-    const uint64_t start = (uint64_t)blockIdx.x << VAL_BITS;
-    unsigned long long lo = 0, hi = 0;
-    unsigned bad = 0;
-    for (uint64_t e = threadIdx.x; e < (1ull << VAL_BITS); e += RB) {
-        const uint64_t x = start + e;
-        if (x >= N) break;
-        const double v = p[x];
-        if (!(v >= 0.0) || !(v < 4.0)) { bad = 1; continue; }   // NaN, negative, >= 4, inf
-        const unsigned long long w = weight_of(v);
-        lo += w;
-        hi += lo < w ? 1ull : 0ull;
-    }
-    slo[threadIdx.x] = lo;
-    shi[threadIdx.x] = hi;
-    sbad[threadIdx.x] = bad;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long L = 0, H = 0;
-        unsigned B = 0;
-        for (int t = 0; t < RB; t++) {
-            L += slo[t];
-            H += shi[t] + (L < slo[t] ? 1ull : 0ull);
-            B |= sbad[t];
-        }
-        rows[3 * (uint64_t)blockIdx.x] = L;
-        rows[3 * (uint64_t)blockIdx.x + 1] = H;
-        rows[3 * (uint64_t)blockIdx.x + 2] = B;
-    }
-}
-
-__global__ __launch_bounds__(64) void k_validate_total(const unsigned long long *__restrict__ rows, uint64_t nrows,
-                                                       unsigned long long *__restrict__ out) {
-    if (threadIdx.x != 0) return;
-    unsigned long long L = 0, H = 0, B = 0;
-    for (uint64_t r = 0; r < nrows; r++) {
-        const unsigned long long l = rows[3 * r];
-        L += l;
-        H += rows[3 * r + 1] + (L < l ? 1ull : 0ull);
-        B |= rows[3 * r + 2];
-    }
-    out[0] = L;
-    out[1] = H;
-    out[2] = B;
-}
-
+// An explicit distribution: every p must be finite, >= 0 and < 4 (its weight
+// floor(p 2^62) fits 64 bits), and the weights must sum below 2^64; the pass
+// that sums the weights checks both (a separate validation read 46 workgroups
+// of a 3-million-entry distribution in 103 us).
 sv_status run_sample_from(const double *probs, uint64_t N, const uint64_t *r64, int64_t k,
                           uint64_t *out, hipStream_t s) {
     int n = 0;
     while ((1ull << n) < N) n++;
     // library-owned scratch for this standalone call; kept until the process
-    // ends (never freed from a static destructor, after the runtime is gone)
-    static ScratchSource *scr = new ScratchSource{new Workspace(), nullptr, 0};
-    static Workspace *vws = new Workspace();
-    const uint64_t nrows = (N + (1ull << VAL_BITS) - 1) >> VAL_BITS;
-    SV_TRY(vws->reserve((size_t)(nrows + 1) * 3 * 8));
-    auto *rows = (unsigned long long *)vws->ptr;
-    hipLaunchKernelGGL(k_validate_weights, dim3((unsigned)nrows), dim3(RB), 0, s, probs, N, rows);
-    hipLaunchKernelGGL(k_validate_total, dim3(1), dim3(64), 0, s, rows, nrows, rows + 3 * nrows);
-    SV_HIP(hipGetLastError());
-    unsigned long long tot[3] = {0, 0, 0};
-    SV_HIP(hipMemcpyAsync(tot, rows + 3 * nrows, sizeof tot, hipMemcpyDeviceToHost, s));
-    SV_HIP(hipStreamSynchronize(s));
-    if (tot[2]) return fail(SV_EINVAL, "sv_sample_from: a probability is negative, NaN, infinite or >= 4");
-    if (tot[1]) return fail(SV_ERANGE, "sv_sample_from: the weights floor(p 2^62) sum to 2^64 or more (sum p >= 4)");
-    if (k == 0) return SV_OK;
-    sv_status rc = sample_impl<double>(*scr, s, probs, n, r64, 0, k, out, nullptr, N);
-    if (rc != SV_OK) return rc;
-    SV_HIP(hipStreamSynchronize(s));
-    return SV_OK;
+    // ends (never freed from a static destructor, after the runtime is gone),
+    // one call at a time
+    static Workspace *ws = new Workspace();
+    static std::mutex *mu = new std::mutex();
+    std::lock_guard<std::mutex> lock(*mu);
+    ScratchSource scr;
+    scr.ws = ws;
+    return sample_impl<double>(scr, s, probs, n, r64, 0, k, out, nullptr, nullptr, N);
 }
 
 // ---------------------------------------------------------------------------
@@ -868,7 +1002,9 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
                             double S, double *sum_log, int64_t *zeros) {
     (void)S;
     if (k <= 0) { *sum_log = 0; *zeros = 0; return SV_OK; }
-    const int64_t per = 4096;
+    // one sample per thread (latency-bound gathers) up to 2048 rows; with 4096
+    // samples per workgroup 10^5 samples ran on 25 workgroups
+    const int64_t per = std::max<int64_t>(RB, (k + 2047) / 2048);
     const int64_t nb = (k + per - 1) / per;
     SV_TRY(st->ws.reserve((size_t)(nb + 1) * 16 * sizeof(double)));
     double *part = (double *)st->ws.ptr;

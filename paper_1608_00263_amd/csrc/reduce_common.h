@@ -256,7 +256,8 @@ __device__ __forceinline__ void load_ln_table(LnEntry *tab) {
 
 // x must be a positive normal double (any other value gives an unspecified
 // number; the table index stays in range).
-__device__ __forceinline__ double ln_normal(double x, const LnEntry *tab) {
+// eoff is added to its binary exponent.
+__device__ __forceinline__ double ln_normal(double x, const LnEntry *tab, int eoff = 0) {
     const int hi = __double2hiint(x);
     const int t = hi - LN_OFF;
     const LnEntry en = tab[(t >> 12) & (LN_BINS - 1)];
@@ -267,7 +268,7 @@ __device__ __forceinline__ double ln_normal(double x, const LnEntry *tab) {
     q = fma3s(q, r, -1.0 / 4.0);
     q = fma3s(q, r, 1.0 / 3.0);
     q = fma3s(q, r, -0.5);
-    const double b = fma((double)(t >> 20), 6.93147180559945309417e-01, en.ln);
+    const double b = fma((double)((t >> 20) + eoff), 6.93147180559945309417e-01, en.ln);
     return b + fma(r2, q, r);
 }
 
@@ -275,13 +276,17 @@ __device__ __forceinline__ double ln_normal(double x, const LnEntry *tab) {
 __device__ __forceinline__ unsigned rare_key(double p) { return (unsigned)__double2hiint(p) - 0x00100000u; }
 constexpr unsigned RARE_KEY = 0x7fe00000u;   // key >= RARE_KEY: not a positive normal number
 
-// Logarithm of any probability for the sums of the statistics: 0 for p = 0 or
+// Logarithm of a rare value for the sums of the statistics: 0 for p = 0 or
 // NaN (counted in zeros).
+__device__ __forceinline__ double ln_rare(double p, unsigned &zeros, const LnEntry *tab) {
+    const double sub = ln_normal(p * 18014398509481984.0, tab, -54);   // subnormals, scaled by 2^54
+    const bool pos = p > 0.0;
+    zeros += pos ? 0u : 1u;
+    return pos ? (p > 1.0 ? p : sub) : 0.0;   // p > 1: infinite
+}
 __device__ __forceinline__ double ln_prob(double p, unsigned &zeros, const LnEntry *tab) {
     if (rare_key(p) < RARE_KEY) return ln_normal(p, tab);
-    if (p > 0.0) return ln_pos(p);
-    zeros += 1u;
-    return 0.0;
+    return ln_rare(p, zeros, tab);
 }
 
 // Adds one probability p to the one-pass statistics: acc = {S, sum p ln p,
@@ -325,7 +330,7 @@ __device__ __forceinline__ void stat_add_n(double (&acc)[NSTAT], unsigned &zeros
     if (__ballot(key >= RARE_KEY) != 0ull) {
 #pragma unroll
         for (int k = 0; k < K; k++)
-            if (rare_key(p[k]) >= RARE_KEY) l[k] = ln_prob(p[k], zeros, tab);
+            if (rare_key(p[k]) >= RARE_KEY) l[k] = ln_rare(p[k], zeros, tab);
     }
 #pragma unroll
     for (int k = 0; k < K; k++) stat_add_ln(acc, p[k], l[k], Nd);

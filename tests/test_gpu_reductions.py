@@ -62,3 +62,82 @@ def test_moments_across_the_work_split(n, dtype):
             assert abs(m[key] - want[key]) <= 1e-13 * max(1, abs(np.log(want["norm"])), abs(want[key])), key
         assert m["unif_ce"] == want["unif_ce"] or abs(m["unif_ce"] - want["unif_ce"]) <= 1e-13 * abs(want["unif_ce"])
         np.testing.assert_allclose(m["moments"], want["moments"], rtol=1e-13)
+
+
+@pytest.mark.parametrize("n", [1, 4, 8, 9, 10, 11, 13, 16, 22, 23, 24])
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_sample_across_the_weight_levels(n, dtype):
+    # from a partial unit to several units per chunk and several chunks per
+    # group, with runs of empty outcomes
+    psi, st = state_of(n, dtype, 60 + n)
+    st.close()
+    psi[: psi.size // 3] = 0
+    psi[psi.size // 2 : psi.size // 2 + psi.size // 8] = 0
+    st = sv.State(n, dtype, tensor=torch.from_numpy(psi).to("cuda"))
+    want = oracle.sample(oracle.probs(psi), 3000, n)
+    np.testing.assert_array_equal(st.sample(3000, n), want)
+    np.testing.assert_array_equal(st.moments_and_sample(3000, n)[1], want)
+    st.close()
+
+
+@pytest.mark.parametrize("N", [1, 3, 255, 257, 1023, 1025, 16383, 16385, (1 << 20) + 1, (1 << 24) - 5, (1 << 24) + 77])
+def test_sample_from_ragged_levels(N):
+    p = C.random_probabilities(N, 70 + N % 97, zeros=N // 5)
+    if N > 10:
+        p[-1] = 0.0
+    words = C.splitmix64_words(N, 2000)
+    got = sv.sample_from(torch.from_numpy(p).to("cuda"), torch.from_numpy(words.view(np.int64)).to("cuda"))
+    np.testing.assert_array_equal(got.cpu().numpy().view(np.uint64), oracle.sample_from_words(p, words))
+
+
+@pytest.mark.parametrize("where", [0, 1500, -1])
+@pytest.mark.parametrize("bad", [-1e-300, float("nan"), 4.0, float("inf")])
+def test_sample_from_one_bad_entry(where, bad):
+    p = C.random_probabilities(70001, 5)
+    p[where] = bad
+    w = torch.zeros(4, dtype=torch.int64, device="cuda")
+    with pytest.raises(sv.SVError) as e:
+        sv.sample_from(torch.from_numpy(p).to("cuda"), w)
+    assert e.value.status == sv.SV_EINVAL
+
+
+def test_sample_from_total_at_the_limit():
+    # weights that sum to 2^64 - 2^11 (accepted; the largest word selects the
+    # last outcome) and to 2^64 (refused), entries of 2 and more among them
+    top = np.nextafter(4.0, 0.0)
+    p = np.zeros(3000)
+    p[7], p[2999] = top - 1.0, 1.0
+    w = torch.tensor([0, -1], dtype=torch.int64, device="cuda")
+    got = sv.sample_from(torch.from_numpy(p).to("cuda"), w).cpu().numpy()
+    np.testing.assert_array_equal(got, [7, 2999])
+    for q in (4.0 - 1.0, 3.5):
+        p[7] = q
+        with pytest.raises(sv.SVError) as e:
+            sv.sample_from(torch.from_numpy(p).to("cuda"), w)
+        assert e.value.status == sv.SV_ERANGE
+
+
+@pytest.mark.parametrize("n", [31, 32, 33])
+def test_sample_wide_sub_buckets(n):
+    # sub-buckets of 2^9 and 2^10 entries: a sparse state whose integer CDF is
+    # formed on the host
+    rng = np.random.default_rng(n)
+    idx = np.unique(rng.integers(0, 1 << n, 4000))
+    idx = np.unique(np.concatenate([idx, [0, 255, 256, 511, 512, 1023, 1024, (1 << n) - 1]]))
+    amp = (rng.standard_normal(idx.size) + 1j * rng.standard_normal(idx.size)) / np.sqrt(2.5 * idx.size)
+    amp = amp.astype(np.complex64)
+    t = torch.zeros(1 << n, dtype=torch.complex64, device="cuda")
+    t[torch.from_numpy(idx).to("cuda")] = torch.from_numpy(amp).to("cuda")
+    st = sv.State(n, "c64", tensor=t)
+    k, seed = 5000, 9
+    xs = st.sample(k, seed)
+    m, ys = st.moments_and_sample(k, seed)
+    st.close()
+    p = amp.real.astype(np.float64) ** 2 + amp.imag.astype(np.float64) ** 2
+    cdf = np.cumsum([int(np.floor(np.ldexp(v, 62))) for v in p], dtype=object)
+    words = C.splitmix64_words(seed, k)
+    want = idx[np.searchsorted(cdf, [(int(r) * int(cdf[-1])) >> 64 for r in words], side="right")]
+    np.testing.assert_array_equal(xs, want.astype(np.uint64))
+    np.testing.assert_array_equal(ys, xs)
+    assert m["zero_count"] == (1 << n) - idx.size
+    np.testing.assert_allclose(m["norm"], p.sum(), rtol=1e-12)
