@@ -524,7 +524,7 @@ sv_status sv_pair_stats(sv_state *a, sv_state *b, int32_t nbins, double zmin, do
     const double dz = nbins > 0 ? (zmax - zmin) / nbins : 0.0;
     for (int j = 0; j <= nbins && nbins > 0; j++) thr[(size_t)j] = std::ldexp(std::exp(zmin + j * dz), -n);
     double r[16] = {0};
-    SV_TRY(run_pair_stats(a, b, nbins, thr.data(), r, hist));
+    SV_TRY(run_pair_stats(a, b, nbins, zmin, zmax, thr.data(), r, hist));
     const double N = std::ldexp(1.0, n);
     const double Sa = r[0], Sb = r[1];
     if (nbins > 0 && !(Sa < 4.0 && Sb < 4.0))

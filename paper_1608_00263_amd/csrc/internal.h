@@ -380,8 +380,8 @@ sv_status run_stats_sample_noalloc(sv_state *st, sv_stats *stats, int64_t k, uin
 // into sums16 (S_a, S_b, Re, Im <a|b>, sum p_a^2, sum p_b^2, sum p_a p_b,
 // sum p_b ln p_a, sum ln p_a, sum of p_b where p_a = 0, zero count), and
 // with nbins > 0 the 3 (nbins + 2) histogram words into host_hist
-sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, const double *host_thr, double *sums16,
-                         uint64_t *host_hist);
+sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, double zmin, double zmax, const double *host_thr,
+                         double *sums16, uint64_t *host_hist);
 // sv_apply_circuit with SV_FLAG_CHECKPOINTS: the forward sweeps of the
 // adjoint plan, keeping its checkpoints for a later sv_backward
 sv_status run_forward_checkpoints(sv_state *st, const sv_circuit *c, const sv_opts *opts);

@@ -218,79 +218,121 @@ __device__ __forceinline__ uint64_t weight_of(double p) {
     return (uint64_t)(p * 4611686018427387904.0);
 }
 
+// floor(p 2^62) of 0 <= p < 2 by one 64-bit shift of the mantissa (zeros and
+// subnormals give 0); any p through weight_of where a wave holds a larger one.
+// The conversion instructions of weight_of take twice the issues.
+__device__ __forceinline__ uint64_t weight_below2(double p) {
+    const unsigned hi = (unsigned)__double2hiint(p), lo = (unsigned)__double2loint(p);
+    const uint64_t m = ((uint64_t)((hi & 0xfffffu) | 0x100000u) << 32 | lo) << 10;   // p = m 2^(e - 1085)
+    const unsigned sh = 1023u - (hi >> 20);
+    return m >> (sh < 63u ? sh : 63u);
+}
+__device__ __forceinline__ bool weight_is_large(double p) { return (unsigned)__double2hiint(p) >= 0x40000000u; }
+
 // ---------------------------------------------------------------------------
 // pair statistics of an ideal output a and another output b
 // ---------------------------------------------------------------------------
 // Per workgroup, in FP64: S_a, S_b, Re and Im of sum conj(a) b, sum p_a^2,
 // sum p_b^2, sum p_a p_b, sum over p_a > 0 of p_b ln p_a and of ln p_a, sum
 // over p_a = 0 of p_b; and the number of p_a = 0.  With nbins > 0, the
-// histogram of z = ln(N p_a): the slot of x is found by comparing p_a with
+// histogram of z = ln(N p_a): the slot of x is decided by comparing p_a with
 // the thresholds thr[0..nbins] (bin j: thr[j] <= p_a < thr[j+1]; nbins:
-// below thr[0] or p_a = 0; nbins + 1: at or above thr[nbins]), and the slot
-// gets the count and the integer masses floor(p 2^62) of both outputs
-// (64-bit integer sums: exact, in any order) in LDS, added to hist at the
-// end.
+// below thr[0] or p_a = 0; nbins + 1: at or above thr[nbins]), starting from
+// the bin that ln p_a falls into, and the slot gets the count and the integer
+// masses floor(p 2^62) of both outputs (64-bit integer sums: exact, in any
+// order) in LDS; the workgroup writes them as one row of hcols words.
+// The slots of one wavefront's outcomes collide (most of a Porter-Thomas
+// output lies in a few bins), so each slot has `copies` LDS words, one per
+// lane modulo copies.  Small states are bound by latency: four outcomes per
+// thread at least (2^20 amplitudes run on 1024 workgroups; 4096 outcomes per
+// workgroup took 24 us).
 constexpr int NPAIR = 10;
-constexpr int MAX_PAIR_BINS = 1024;
+constexpr int PAIR_INLINE = 256;      // thresholds that travel as kernel arguments
+struct PairThr { double t[PAIR_INLINE]; };
 
-template <typename T>
+template <typename T, bool HIST>
 __global__ __launch_bounds__(RB) void k_pair_stats(const cpx<T> *__restrict__ a, const cpx<T> *__restrict__ b,
-                                                   uint64_t chunk, const double *__restrict__ thr, int nbins,
-                                                   double *__restrict__ part, unsigned long long *__restrict__ hist) {
+                                                   uint64_t chunk, const double *__restrict__ thr, PairThr inl,
+                                                   int nbins, int copies, double l0, double inv_dz,
+                                                   double *__restrict__ part, unsigned long long *__restrict__ hrows,
+                                                   int hcols) {
     __shared__ double red[4 * NPAIR];
     __shared__ unsigned zred[4];
-    __shared__ double sthr[MAX_PAIR_BINS + 1];
-    __shared__ unsigned long long sh[3 * (MAX_PAIR_BINS + 2)];
-    const int nslot = nbins + 2;
-    if (nbins > 0) {
-        for (int i = threadIdx.x; i <= nbins; i += RB) sthr[i] = thr[i];
-        for (int i = threadIdx.x; i < 3 * nslot; i += RB) sh[i] = 0ull;
+    __shared__ LnEntry tab[LN_BINS];
+    extern __shared__ unsigned long long dyn[];   // nbins + 1 thresholds, 3 nslot copies words
+    const int nslot = nbins + 2, nw = 3 * nslot * copies;
+    double *const sthr = (double *)dyn;
+    unsigned long long *const sh = dyn + nbins + 1;
+    constexpr int UNR = 4;
+    const uint64_t start = (uint64_t)blockIdx.x * chunk;
+    const uint64_t end = start + chunk;
+    cpx<T> av[UNR], bv[UNR];
+    // entries past the end of a small state's chunk read its last entry and
+    // are left out below
+    auto load4 = [&](uint64_t j0) {
+#pragma unroll
+        for (int u = 0; u < UNR; u++) {
+            const uint64_t j = j0 + (uint64_t)u * RB;
+            av[u] = a[j < end ? j : end - 1];
+            bv[u] = b[j < end ? j : end - 1];
+        }
+    };
+    uint64_t j0 = start + threadIdx.x;
+    load4(j0);
+    load_ln_table(tab);
+    if constexpr (HIST) {
+        for (int i = threadIdx.x; i <= nbins; i += RB) sthr[i] = thr ? thr[i] : inl.t[i];
+        for (int i = threadIdx.x; i < nw; i += RB) sh[i] = 0ull;
     }
     __syncthreads();
     double acc[NPAIR];
 #pragma unroll
     for (int i = 0; i < NPAIR; i++) acc[i] = 0.0;
     unsigned zeros = 0;
-    const uint64_t start = (uint64_t)blockIdx.x * chunk, end = start + chunk;
-    for (uint64_t j = start + threadIdx.x; j < end; j += RB) {
-        const cpx<T> av = a[j], bv = b[j];
-        const double ar = av.re, ai = av.im, br = bv.re, bi = bv.im;
-        const double pa = prob_of(av), pb = prob_of(bv);
-        acc[0] += pa;
-        acc[1] += pb;
-        acc[2] += fma(ar, br, ai * bi);
-        acc[3] += fma(ar, bi, -ai * br);
-        acc[4] = fma(pa, pa, acc[4]);
-        acc[5] = fma(pb, pb, acc[5]);
-        acc[6] = fma(pa, pb, acc[6]);
-        const bool pos = pa > 0.0;
-        const double l = pos ? ln_pos(pa) : 0.0;
-        acc[7] = fma(pb, l, acc[7]);
-        acc[8] += l;
-        acc[9] += pos ? 0.0 : pb;
-        zeros += pos ? 0u : 1u;
-        if (nbins > 0) {
-            int slot;
-            if (!(pa >= sthr[0])) {
-                slot = nbins;
-            } else if (pa >= sthr[nbins]) {
-                slot = nbins + 1;
-            } else {
-                int lo = 0, hi = nbins;   // last j with thr[j] <= p_a
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (sthr[mid] <= pa) lo = mid;
-                    else hi = mid;
+    const int cp = threadIdx.x & (copies - 1);
+    for (uint64_t base = start; base < end; base += RB * UNR, j0 += RB * UNR) {
+        cpx<T> ca[UNR], cb[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; u++) { ca[u] = av[u]; cb[u] = bv[u]; }
+        load4(base + RB * UNR < end ? j0 + RB * UNR : j0);
+#pragma unroll
+        for (int u = 0; u < UNR; u++) {
+            if (j0 + (uint64_t)u * RB >= end) continue;
+            const double ar = ca[u].re, ai = ca[u].im, br = cb[u].re, bi = cb[u].im;
+            const double pa = prob_of(ca[u]), pb = prob_of(cb[u]);
+            acc[0] += pa;
+            acc[1] += pb;
+            acc[2] += fma(ar, br, ai * bi);
+            acc[3] += fma(ar, bi, -ai * br);
+            acc[4] = fma(pa, pa, acc[4]);
+            acc[5] = fma(pb, pb, acc[5]);
+            acc[6] = fma(pa, pb, acc[6]);
+            const double l = ln_prob(pa, zeros, tab);
+            acc[7] = fma(pb, l, acc[7]);
+            acc[8] += l;
+            acc[9] += pa > 0.0 ? 0.0 : pb;
+            if constexpr (HIST) {
+                int slot;
+                if (!(pa >= sthr[0])) {
+                    slot = nbins;
+                } else if (pa >= sthr[nbins]) {
+                    slot = nbins + 1;
+                } else {   // thr[0] <= p_a < thr[nbins]: both walks end inside
+                    const double z = (l - l0) * inv_dz;
+                    slot = z > 0.0 ? (z < (double)nbins ? (int)z : nbins - 1) : 0;
+                    slot = slot < nbins ? slot : nbins - 1;
+                    while (pa < sthr[slot]) slot--;
+                    while (pa >= sthr[slot + 1]) slot++;
                 }
-                slot = lo;
+                // the host rejects the histogram when a norm reaches 4, so a
+                // weight that would not fit is never reported
+                unsigned long long wa = weight_below2(pa), wb = weight_below2(pb);
+                if (weight_is_large(pa)) wa = pa < 4.0 ? weight_of(pa) : 0ull;
+                if (weight_is_large(pb)) wb = pb < 4.0 ? weight_of(pb) : 0ull;
+                atomicAdd(&sh[slot * copies + cp], 1ull);
+                atomicAdd(&sh[(nslot + slot) * copies + cp], wa);
+                atomicAdd(&sh[(2 * nslot + slot) * copies + cp], wb);
             }
-            // the host rejects the histogram when a norm reaches 4, so a
-            // weight that would not fit is never reported
-            const unsigned long long wa = pa < 4.0 ? weight_of(pa) : 0ull;
-            const unsigned long long wb = pb < 4.0 ? weight_of(pb) : 0ull;
-            atomicAdd(&sh[slot], 1ull);
-            atomicAdd(&sh[nslot + slot], wa);
-            atomicAdd(&sh[2 * nslot + slot], wb);
         }
     }
     block_sum<double, NPAIR>(acc, red);
@@ -303,46 +345,87 @@ __global__ __launch_bounds__(RB) void k_pair_stats(const cpx<T> *__restrict__ a,
         const unsigned long long z = (unsigned long long)zred[0] + zred[1] + zred[2] + zred[3];
         part[(uint64_t)blockIdx.x * 16 + NPAIR] = (double)z;
     }
-    if (nbins > 0)
-        for (int i = threadIdx.x; i < 3 * nslot; i += RB)
-            if (sh[i]) atomicAdd(&hist[i], sh[i]);
+    if constexpr (HIST) {
+        for (int i = threadIdx.x; i < 3 * nslot; i += RB) {
+            unsigned long long s = 0;
+            for (int k = 0; k < copies; k++) s += sh[i * copies + k];
+            hrows[(uint64_t)blockIdx.x * hcols + i] = s;
+        }
+    }
 }
 
-__global__ void k_zero_u64(unsigned long long *p, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0ull;
+// The combined sums (workgroup 0) and the histogram (workgroups 1 up, 16
+// columns of the rows each) into one block: 16 doubles, then the words.
+__global__ __launch_bounds__(CMB_THREADS) void k_pair_finish(const double *__restrict__ part,
+                                                             const unsigned long long *__restrict__ hrows, int hcols,
+                                                             int nwords, int nblocks, double *__restrict__ out) {
+    __shared__ unsigned long long red[2 * 64 * 16];
+    if (blockIdx.x == 0) {
+        combine_rows_wg(part, nblocks, NPAIR + 1, out, (double *)red);
+        return;
+    }
+    const int q = threadIdx.x & 15, seg = threadIdx.x >> 4;
+    const int col = (blockIdx.x - 1) * 16 + q;   // below hcols, a multiple of 16
+    unsigned long long s = 0;
+    if (col < nwords) {
+#pragma unroll 8
+        for (int r = seg; r < nblocks; r += 64) s += hrows[(uint64_t)r * hcols + col];
+    }
+    red[threadIdx.x] = s;
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) {
+        __syncthreads();
+        if (seg < h) red[threadIdx.x] += red[threadIdx.x + h * 16];
+    }
+    if (seg == 0 && col < nwords) ((unsigned long long *)(out + 16))[col] = red[q];
 }
 
-sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, const double *host_thr, double *sums16,
-                         uint64_t *host_hist) {
+sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, double zmin, double zmax, const double *host_thr,
+                         double *sums16, uint64_t *host_hist) {
     int nb;
     uint64_t chunk;
     stats_grid(a->n, &nb, &chunk);
-    const int nslot = nbins + 2;
+    const int nwords = nbins > 0 ? 3 * (nbins + 2) : 0, hcols = (nwords + 15) & ~15;
+    // histogram rows of at most 16 MiB in all
+    while (nb > 256 && (int64_t)nb * hcols > ((int64_t)1 << 21)) { nb >>= 1; chunk <<= 1; }
+    int copies = 16;   // at most 16 KiB of histogram words per workgroup, or one copy
+    while (copies > 1 && nwords * copies > 2048) copies >>= 1;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t o_part = 0, o_res = al((size_t)nb * 16 * 8), o_thr = o_res + al(16 * 8),
-                 o_hist = o_thr + al((size_t)(nbins + 1) * 8), need = o_hist + al((size_t)3 * nslot * 8);
+    const size_t o_part = 0, o_res = al((size_t)nb * 16 * 8), o_thr = o_res + al(16 * 8 + (size_t)nwords * 8),
+                 o_rows = o_thr + al((size_t)(nbins + 1) * 8), need = o_rows + al((size_t)nb * hcols * 8);
     SV_TRY(a->ws.reserve(need));
     uint8_t *w = (uint8_t *)a->ws.ptr;
-    double *part = (double *)(w + o_part), *res = (double *)(w + o_res), *thr = (double *)(w + o_thr);
-    auto *hist = (unsigned long long *)(w + o_hist);
+    double *part = (double *)(w + o_part), *res = (double *)(w + o_res), *thr = nullptr;
+    auto *rows = (unsigned long long *)(w + o_rows);
     hipStream_t s = a->stream;
-    if (nbins > 0) {
-        hipLaunchKernelGGL(k_zero_u64, dim3(4), dim3(256), 0, s, hist, 3 * nslot);
+    PairThr inl{};
+    if (nbins >= PAIR_INLINE) {
+        thr = (double *)(w + o_thr);
         SV_HIP(hipMemcpyAsync(thr, host_thr, (size_t)(nbins + 1) * 8, hipMemcpyHostToDevice, s));
+    } else {
+        for (int i = 0; i <= nbins && nbins > 0; i++) inl.t[i] = host_thr[i];
     }
-    if (a->dt == SV_C64)
-        hipLaunchKernelGGL(k_pair_stats<float>, dim3(nb), dim3(RB), 0, s, (const cpx<float> *)a->data,
-                           (const cpx<float> *)b->data, chunk, thr, nbins, part, hist);
-    else
-        hipLaunchKernelGGL(k_pair_stats<double>, dim3(nb), dim3(RB), 0, s, (const cpx<double> *)a->data,
-                           (const cpx<double> *)b->data, chunk, thr, nbins, part, hist);
+    const double l0 = zmin - a->n * 0.69314718055994530942, inv_dz = nbins > 0 ? nbins / (zmax - zmin) : 0.0;
+    const size_t lds = nbins > 0 ? ((size_t)nbins + 1 + (size_t)nwords * copies) * 8 : 0;
+#define PAIR_LAUNCH(T, HIST)                                                                                        \
+    hipLaunchKernelGGL((k_pair_stats<T, HIST>), dim3(nb), dim3(RB), lds, s, (const cpx<T> *)a->data,                \
+                       (const cpx<T> *)b->data, chunk, thr, inl, nbins, copies, l0, inv_dz, part, rows, hcols)
+    if (a->dt == SV_C64) {
+        if (nbins > 0) PAIR_LAUNCH(float, true);
+        else PAIR_LAUNCH(float, false);
+    } else {
+        if (nbins > 0) PAIR_LAUNCH(double, true);
+        else PAIR_LAUNCH(double, false);
+    }
+#undef PAIR_LAUNCH
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, s, part, nb, NPAIR + 1, res);
+    hipLaunchKernelGGL(k_pair_finish, dim3(1 + hcols / 16), dim3(CMB_THREADS), 0, s, part, rows, hcols, nwords, nb, res);
     SV_HIP(hipGetLastError());
-    SV_HIP(hipMemcpyAsync(sums16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
-    if (nbins > 0)
-        SV_HIP(hipMemcpyAsync(host_hist, hist, (size_t)3 * nslot * 8, hipMemcpyDeviceToHost, s));
+    std::vector<uint64_t> host((size_t)16 + nwords);
+    SV_HIP(hipMemcpyAsync(host.data(), res, host.size() * 8, hipMemcpyDeviceToHost, s));
     SV_HIP(hipStreamSynchronize(s));
+    std::memcpy(sums16, host.data(), (NPAIR + 1) * sizeof(double));
+    if (nwords) std::memcpy(host_hist, host.data() + 16, (size_t)nwords * 8);
     return SV_OK;
 }
 
@@ -418,17 +501,6 @@ __device__ __forceinline__ unsigned long long half_sum_u64(unsigned long long v)
     const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
     return (((unsigned long long)h[0] << 32) | l[0]) + (((unsigned long long)h[1] << 32) | l[1]);
 }
-
-// floor(p 2^62) of 0 <= p < 2 by one 64-bit shift of the mantissa (zeros and
-// subnormals give 0); any p through weight_of where a wave holds a larger one.
-// The conversion instructions of weight_of take twice the issues.
-__device__ __forceinline__ uint64_t weight_below2(double p) {
-    const unsigned hi = (unsigned)__double2hiint(p), lo = (unsigned)__double2loint(p);
-    const uint64_t m = ((uint64_t)((hi & 0xfffffu) | 0x100000u) << 32 | lo) << 10;   // p = m 2^(e - 1085)
-    const unsigned sh = 1023u - (hi >> 20);
-    return m >> (sh < 63u ? sh : 63u);
-}
-__device__ __forceinline__ bool weight_is_large(double p) { return (unsigned)__double2hiint(p) >= 0x40000000u; }
 
 // What a pass over 2^n entries leaves besides the sums: the 14 statistic sums
 // and the total weight with a status.

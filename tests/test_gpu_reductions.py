@@ -141,3 +141,31 @@ def test_sample_wide_sub_buckets(n):
     np.testing.assert_array_equal(ys, xs)
     assert m["zero_count"] == (1 << n) - idx.size
     np.testing.assert_allclose(m["norm"], p.sum(), rtol=1e-12)
+
+
+@pytest.mark.parametrize("n,nbins,zmin,zmax", [(1, 3, -8.0, 4.0), (9, 1, -1.0, 1.0), (10, 24, -8.0, 4.0),
+                                               (11, 255, -8.0, 4.0), (12, 256, -3.0, 1.0), (13, 1024, -8.0, 4.0),
+                                               (20, 1024, -20.0, 3.0), (21, 24, 0.5, 0.5 + 1e-13), (22, 7, 6.0, 9.0)])
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_pair_histogram_slots(n, nbins, zmin, zmax, dtype):
+    # thresholds as arguments and from memory, one to sixteen copies per slot,
+    # rows limited by size; zeros, a bin narrower than the logarithm's error
+    # and outcomes exactly on thresholds
+    a, st = state_of(n, dtype, 80 + n)
+    st.close()
+    b, _ = state_of(n, dtype, 180 + n)
+    if n > 4:
+        a[3] = a[7] = 0
+        thr = np.ldexp(np.exp(zmin + np.arange(nbins + 1) * ((zmax - zmin) / nbins)), -n)
+        m = min(nbins + 1, a.size // 4)
+        a[8:8 + m] = np.sqrt(thr[:m])
+    sa, sb_ = (sv.State(n, dtype, tensor=torch.from_numpy(x).to("cuda")) for x in (a, b))
+    d, h = sv.pair_stats(sa, sb_, nbins, zmin, zmax)
+    d0, _ = sv.pair_stats(sa, sb_)
+    sa.close()
+    sb_.close()
+    want, hw = oracle.pair_stats(a, b, nbins, zmin, zmax)
+    np.testing.assert_array_equal(h, hw)
+    for k, v in want.items():
+        for got in (d[k], d0[k]):
+            assert (np.isnan(v) and np.isnan(got)) or got == v or abs(got - v) <= 1e-11 * max(1.0, abs(v)), k
