@@ -7,6 +7,7 @@
 #include <limits>
 #include <cstdio>
 #include <cstdlib>
+#include <mutex>
 #include <new>
 
 #include "internal.h"
@@ -85,6 +86,20 @@ static PlanRequest make_request(sv_state *st, const sv_opts *o) {
 // autotuner
 // ---------------------------------------------------------------------------
 static std::map<std::string, sv_opts> g_tuned;   // process-wide choices
+static std::mutex g_tuned_mu;
+
+static bool tuned_choice(const std::string &key, sv_opts *out) {
+    std::lock_guard<std::mutex> lock(g_tuned_mu);
+    auto it = g_tuned.find(key);
+    if (it == g_tuned.end()) return false;
+    *out = it->second;
+    return true;
+}
+
+static void keep_choice(const std::string &key, const sv_opts &o) {
+    std::lock_guard<std::mutex> lock(g_tuned_mu);
+    g_tuned[key] = o;
+}
 
 static std::vector<sv_opts> tune_candidates(const sv_state *st) {
     std::vector<sv_opts> c;
@@ -115,13 +130,18 @@ static std::vector<sv_opts> tune_candidates(const sv_state *st) {
     return c;
 }
 
+// A choice holds for every setting of the rotation offsets: they change the
+// coefficients of a plan, not its sweeps.  (Keyed by the offsets as well, a
+// training loop tuned at every step: 26 of the 30 ms of a 25-qubit step.)
 static std::string tune_key(const sv_state *st, const sv_circuit *c, bool from_zero) {
+    sv_circuit shape = *c;
+    shape.theta = nullptr;
     PlanRequest rq{};
     rq.n = st->n;
     rq.dtype = st->dt;
     rq.mode = SV_MODE_AUTO;
     rq.from_zero = from_zero;
-    return plan_key(c, rq);
+    return plan_key(&shape, rq);
 }
 
 static sv_status time_plan(sv_state *st, const Plan &plan, void *psi, float *ms) {
@@ -158,10 +178,9 @@ static double plan_floor_ms(const Plan &plan) {
 static sv_status resolve_auto(sv_state *st, const sv_circuit *c, bool from_zero, sv_opts *out, int *explore) {
     *explore = -1;
     const std::string key = tune_key(st, c, from_zero);
-    auto it = g_tuned.find(key);
-    if (it != g_tuned.end()) { *out = it->second; return SV_OK; }
+    if (tuned_choice(key, out)) return SV_OK;
     std::vector<sv_opts> cand = tune_candidates(st);
-    if (cand.size() == 1) { g_tuned[key] = cand[0]; *out = cand[0]; return SV_OK; }
+    if (cand.size() == 1) { keep_choice(key, cand[0]); *out = cand[0]; return SV_OK; }
     const size_t bytes = (size_t)state_bytes(st->n, st->dt);
     size_t freeb = 0, total = 0;
     SV_HIP(hipMemGetInfo(&freeb, &total));
@@ -190,7 +209,7 @@ static sv_status resolve_auto(sv_state *st, const sv_circuit *c, bool from_zero,
         (void)hipStreamSynchronize(st->stream);
         (void)hipFree(scratch);
         if (rc != SV_OK) return rc;
-        g_tuned[key] = cand[best];
+        keep_choice(key, cand[best]);
         *out = cand[best];
         return SV_OK;
     }
@@ -215,7 +234,7 @@ static sv_status resolve_auto(sv_state *st, const sv_circuit *c, bool from_zero,
     int best = 0;
     for (size_t i = 1; i < t.ms.size(); i++)
         if (t.ms[i] < t.ms[best]) best = (int)i;
-    g_tuned[key] = t.cand[best];
+    keep_choice(key, t.cand[best]);
     *out = t.cand[best];
     return SV_OK;
 }

@@ -21,6 +21,8 @@
 #include <cmath>
 #include <cstdio>
 #include <functional>
+#include <map>
+#include <mutex>
 #include <set>
 #include <sstream>
 
@@ -1188,9 +1190,9 @@ static void plan_per_gate(const sv_circuit *c, const std::vector<SGate> &g, cons
 // 250 against 16 in 58 ms at 110).  Complex128: 220.
 // flex: lane bits 4 and 5 may take any qubit (the sweep gathers vb + 2
 // qubits above 3) instead of qubits 4 and 5.
-static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
-                                         double budget = -1, bool flex = false) {
-    if (budget < 0) budget = dtype == SV_C64 ? 250.0 : 220.0;
+static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
+                                         double budget, bool flex) {
+    (void)dtype;
     const int nfixed = flex ? 4 : LANE_BITS;
     auto cost = [&](int i, const std::vector<char> &in_tile) -> double {
         const SGate &s = g[i];
@@ -1210,6 +1212,32 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
             return q;
         },
         cost, budget, nfixed);
+}
+
+// The grouping depends on the gates' kinds, forms and qubits only, not on
+// their angles, and takes most of a plan's time (the beam search: about 5 ms
+// for 600 gates).  A program that trains rotation offsets plans a new set of
+// angles every step, so the last groupings are kept, found by their whole
+// input.
+static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
+                                         double budget = -1, bool flex = false) {
+    if (budget < 0) budget = dtype == SV_C64 ? 250.0 : 220.0;
+    std::vector<int32_t> key = {n, vb, flex ? 1 : 0, (int32_t)(budget * 256.0)};
+    key.reserve(4 + 4 * g.size());
+    for (const SGate &s : g) key.insert(key.end(), {s.kind, s.form, s.q0, s.q1});
+    constexpr size_t KEPT = 64;
+    static std::mutex *mu = new std::mutex();
+    static auto *kept = new std::map<std::vector<int32_t>, std::vector<Sweep>>();   // kept for the process
+    {
+        std::lock_guard<std::mutex> lock(*mu);
+        auto it = kept->find(key);
+        if (it != kept->end()) return it->second;
+    }
+    std::vector<Sweep> sw = find_regtile_sweeps(g, n, vb, dtype, budget, flex);
+    std::lock_guard<std::mutex> lock(*mu);
+    if (kept->size() >= KEPT) kept->clear();
+    (*kept)[std::move(key)] = sw;
+    return sw;
 }
 
 std::string plan_key(const sv_circuit *c, const PlanRequest &rq) {

@@ -202,3 +202,26 @@ def test_cycle_plan_rejects_unordered_cycles():
     assert e.value.status == sv.SV_EINVAL
     with pytest.raises(ValueError):
         oracle.cycle_stats(bad)
+
+
+def test_kept_groupings_follow_the_structure():
+    # the grouping of a circuit is reused for other rotation offsets, but not
+    # where an offset changes what a gate is (an X^1/2 turned into the
+    # identity is diagonal), and the replayed plan matches the FP64 reference
+    # each time
+    circ = C.make_circuit(3, 4, 12, seed=21, parametrise=True)
+    sx = [int(p) for k, p in zip(circ.gates["kind"], circ.gates["param"]) if k == C.SX and p >= 0]
+    thetas = [circ.theta, circ.theta + 0.3, np.zeros_like(circ.theta)]
+    turned = circ.theta.copy()
+    turned[sx[0]] = -np.pi / 2
+    thetas.append(turned)
+    flipped = circ.theta.copy()
+    flipped[sx[-1]] = np.pi / 2      # c = 0: no tangent form
+    thetas.append(flipped)
+    for _ in range(2):
+        for th in thetas:
+            c = circ.with_theta(th)
+            for dtype, tile in (("c64", 6), ("c128", 4)):
+                got = sv.host_emulate(c, oracle.zero_state(c.n), dtype, "regtile", 0, tile)
+                # complex64 plans carry FP32 coefficients (the bound of the replays above)
+                assert np.linalg.norm(got - oracle.apply_circuit(c)) < (1e-5 if dtype == "c64" else 1e-11)
