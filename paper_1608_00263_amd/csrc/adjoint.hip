@@ -336,21 +336,9 @@ __global__ __launch_bounds__(BLOCK, (sizeof(T) == 4 && VB <= 5) ? 3 : 1) void k_
                 lane_gate_dispatch<T, NR, false>(mu, u, arg, lane, form);
             }
         } else if (kind == RT_SIGNS) {
-            uint64_t par = 0;
-            const int nt = ops[o].nterms;
-            for (int t = arg; t < arg + nt; t++) {
-                const uint64_t out = terms[t].outside;
-                if ((base & out) != out) continue;
-                const uint32_t lm = terms[t].lanemask;
-                par ^= ((uint32_t)lane & lm) == lm ? terms[t].regset : 0ull;
-            }
-#pragma unroll
-            for (int r = 0; r < NR; r++) {
-                if ((par >> r) & 1) {
-                    phi[r].re = -phi[r].re; phi[r].im = -phi[r].im;
-                    mu[r].re = -mu[r].re; mu[r].im = -mu[r].im;
-                }
-            }
+            const uint64_t par = sign_parity(terms, arg, ops[o].nterms, base, lane);
+            flip_signs<T, NR>(phi, (uint32_t)par, (uint32_t)(par >> 32));
+            flip_signs<T, NR>(mu, (uint32_t)par, (uint32_t)(par >> 32));
         } else if (kind == RT_PHASE && slot < 0) {
             // a group of phase terms sharing one register set (no gradient):
             // the per-lane product of the matching phases, applied once

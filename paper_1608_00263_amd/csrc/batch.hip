@@ -140,9 +140,12 @@ __device__ __forceinline__ double combine_rows(const BInst &I, int q) {
     return sum + c;
 }
 
-// Round schedule: items [item0, item0 + gridDim.x), one per workgroup.
+// Round schedule: items [item0, item0 + gridDim.x), one per workgroup.  The
+// launch bound keeps the 6-qubit tiles at 3 wavefronts per SIMD (168
+// registers; at 169 and 2 wavefronts an ensemble of 16 took 8.9 ms instead of
+// 8.0) and narrower ones at 4.
 template <int VB>
-__global__ __launch_bounds__(BLOCK) void k_batch_round(const BRound *__restrict__ rounds,
+__global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_round(const BRound *__restrict__ rounds,
                                                        const uint32_t *__restrict__ item_round, uint64_t item0,
                                                        const BInst *__restrict__ insts) {
     __shared__ double red[4 * NSTAT];
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_batch_combine(const BInst *__re
 
 // Persistent schedule.
 template <int VB>
-__global__ __launch_bounds__(BLOCK) void k_batch_persistent(const BRound *__restrict__ rounds,
+__global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_persistent(const BRound *__restrict__ rounds,
                                                             const uint32_t *__restrict__ item_round,
                                                             uint64_t total, const BInst *__restrict__ insts,
                                                             unsigned long long *head, unsigned *err,

@@ -290,8 +290,12 @@ __device__ __forceinline__ void lane_gate_f(cplx<T> (&a)[NR], const Mat2<T> &u, 
     cplx<T> cs, cp;
     T sg = (T)1, rc = (T)0, rs = (T)0;
     if constexpr (FORM == F_GEN) {
-        cs = hi ? u.m[3] : u.m[0];
-        cp = hi ? u.m[2] : u.m[1];
+        // choices between copies: a choice between elements of u is one of
+        // addresses, which put u in memory (32 bytes of LDS per thread,
+        // written at every op)
+        const cplx<T> m0 = u.m[0], m1 = u.m[1], m2 = u.m[2], m3 = u.m[3];
+        cs = hi ? m3 : m0;
+        cp = hi ? m2 : m1;
     } else if constexpr (FORM == F_RX) {
         rc = u.m[0].re;
         rs = -u.m[1].im;            // self c - i s p (both halves)
@@ -299,8 +303,9 @@ __device__ __forceinline__ void lane_gate_f(cplx<T> (&a)[NR], const Mat2<T> &u, 
         rc = u.m[0].re;
         rs = hi ? u.m[2].re : -u.m[2].re;   // lo: c self - s p, hi: c self + s p
     } else if constexpr (FORM == F_REAL) {
-        rc = hi ? u.m[3].re : u.m[0].re;
-        rs = hi ? u.m[2].re : u.m[1].re;    // cs self + cp p
+        const T m0 = u.m[0].re, m1 = u.m[1].re, m2 = u.m[2].re, m3 = u.m[3].re;
+        rc = hi ? m3 : m0;
+        rs = hi ? m2 : m1;                  // cs self + cp p
     } else if constexpr (FORM == F_TRX) {
         rs = -u.m[1].im;            // self - i t p (both halves)
     } else if constexpr (FORM == F_TRY) {
@@ -432,6 +437,52 @@ __device__ __forceinline__ Mat2<T> load_mat(PD u) {
 }
 
 
+// Per-lane parity of a run of sign terms: bit r set where register r of this
+// lane is negated.  Terms without lane bits are wave-uniform and stay on the
+// scalar unit; the next record is read while the current one is used.
+__device__ __forceinline__ uint64_t sign_parity(const cptr<DiagTerm> terms, int first, int nt, uint64_t base, int lane) {
+    uint64_t par = 0, spar = 0;
+    uint64_t out = terms[first].outside, rs = terms[first].regset;
+    uint32_t lm = terms[first].lanemask;
+    for (int t = 0; t < nt; t++) {
+        const int tn = first + (t + 1 < nt ? t + 1 : t);
+        const uint64_t out_n = terms[tn].outside, rs_n = terms[tn].regset;
+        const uint32_t lm_n = terms[tn].lanemask;
+        const uint64_t on = (base & out) == out ? rs : 0ull;
+        if (lm == 0) spar ^= on;
+        else par ^= ((uint32_t)lane & lm) == lm ? on : 0ull;
+        out = out_n;
+        rs = rs_n;
+        lm = lm_n;
+    }
+    return par ^ spar;
+}
+
+// Negates the amplitude where bit r of the parity words is set: the bit is
+// shifted to the sign position and merged into each component by one
+// three-input bit operation (x ^ (t & sign)): 3 issues per complex64
+// amplitude where a compare and two selects took 5.
+template <int R>
+__device__ __forceinline__ uint32_t sign_word(uint32_t lo, uint32_t hi) {
+    return R < 32 ? lo << (31 - (R & 31)) : hi << (31 - (R & 31));
+}
+__device__ __forceinline__ void flip_sign(cplx<float> &x, uint32_t t) {
+    x.re = __uint_as_float(__float_as_uint(x.re) ^ (t & 0x80000000u));
+    x.im = __uint_as_float(__float_as_uint(x.im) ^ (t & 0x80000000u));
+}
+__device__ __forceinline__ void flip_sign(cplx<double> &x, uint32_t t) {
+    const int s = (int)(t & 0x80000000u);
+    x.re = __hiloint2double(__double2hiint(x.re) ^ s, __double2loint(x.re));
+    x.im = __hiloint2double(__double2hiint(x.im) ^ s, __double2loint(x.im));
+}
+template <typename T, int NR, int R = 0>
+__device__ __forceinline__ void flip_signs(cplx<T> (&a)[NR], uint32_t lo, uint32_t hi) {
+    if constexpr (R < NR) {
+        flip_sign(a[R], sign_word<R>(lo, hi));
+        flip_signs<T, NR, R + 1>(a, lo, hi);
+    }
+}
+
 // One register-tile op: kind, argument, term count, form and its 2x2 matrix.
 template <typename T, int NR>
 __device__ __forceinline__ void regtile_op(cplx<T> (&a)[NR], int kind, int arg, int nt, int form, const Mat2<T> &u,
@@ -441,18 +492,8 @@ __device__ __forceinline__ void regtile_op(cplx<T> (&a)[NR], int kind, int arg, 
     } else if (kind == RT_LANE) {
         lane_gate_dispatch<T, NR>(a, u, arg, lane, form);
     } else if (kind == RT_SIGNS) {
-        uint64_t par = 0;
-        for (int t = arg; t < arg + nt; t++) {
-            const uint64_t out = terms[t].outside;
-            if ((base & out) != out) continue;
-            const uint32_t lm = terms[t].lanemask;
-            const uint64_t rs = terms[t].regset;
-            par ^= ((uint32_t)lane & lm) == lm ? rs : 0ull;
-        }
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            if ((par >> r) & 1) { a[r].re = -a[r].re; a[r].im = -a[r].im; }
-        }
+        const uint64_t par = sign_parity(terms, arg, nt, base, lane);
+        flip_signs<T, NR>(a, (uint32_t)par, (uint32_t)(par >> 32));
     } else if (kind == RT_PHASE) {
         // a group of phase terms sharing one register set: the product
         // of the phases whose lane and outside bits match, per lane,
