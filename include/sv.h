@@ -89,8 +89,10 @@ typedef struct {
  *  SV_MODE_TILED    the fused blocks grouped into LDS tile sweeps of
  *                   2^tile_qubits amplitudes (several blocks per sweep);
  *  SV_MODE_REGTILE  gates applied one by one inside register tiles (qubits
- *                   0..5 across the 64 lanes of a wavefront, a few gathered
- *                   qubits in registers), diagonal gates folded;
+ *                   0..3 and two gathered ones across the 64 lanes of a
+ *                   wavefront, a few gathered qubits in registers, two more
+ *                   across the four wavefronts of a workgroup where that saves
+ *                   a sweep), diagonal gates folded;
  *  SV_MODE_AUTO     time candidate plans once per circuit shape and keep
  *                   the fastest (autotuner; results cached per process). */
 enum {
@@ -127,12 +129,13 @@ typedef struct {
     int32_t k_max;        /* fused block width 1..5 (0 = default 4)           */
     int32_t tile_qubits;  /* TILED: 8..13 (0 = default 12 / 11); REGTILE:
                              register qubits 1..6 complex64, 1..5 complex128
-                             (0 = default 6 / 5)                              */
+                             (0 = default: 3 for small states up to 6 / 5)    */
     int32_t flags;        /* SV_FLAG_* bits                                   */
     int32_t sweep_budget; /* REGTILE: vector instructions per amplitude
                              register one sweep may spend on gates before a
-                             new sweep starts (0 = default, 250 complex64,
-                             220 complex128; 20..2000)                       */
+                             new sweep starts (0 = default, 250 complex64
+                             (300 for tiles of four wavefronts), 220
+                             complex128; 20..2000)                           */
     int32_t checkpoint_c; /* SV_FLAG_CHECKPOINTS: the checkpoint interval of
                              the sv_backward that will follow (0 = none)     */
 } sv_opts;
@@ -212,8 +215,8 @@ sv_status sv_plan_info(sv_state *st, const sv_circuit *c, const sv_opts *opts,
                        int64_t *sweeps, double *bytes);
 
 /* Autotuner behind SV_MODE_AUTO: times candidate plans for c on this device
- * -- register tiles with 4, 5 or 6 register qubits (complex64) and 3 or 4
- * (complex128), fused blocks with k = 2 and 3, LDS tiles -- and keeps the
+ * -- register tiles with three numbers of register qubits around the one that
+ * suits the size, fused blocks with k = 2 and 3, LDS tiles -- and keeps the
  * fastest for the circuit (cached per process).  The timing runs on a
  * scratch state of the same size when the device has room for one (the
  * handle's contents are untouched); otherwise successive sv_apply_circuit

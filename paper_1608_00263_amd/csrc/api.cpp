@@ -105,19 +105,15 @@ static std::vector<sv_opts> tune_candidates(const sv_state *st) {
     std::vector<sv_opts> c;
     auto add = [&](int mode, int k, int t, int budget = 0) { c.push_back(sv_opts{mode, k, t, 0, budget, 0}); };
     if (st->n >= 10) {
-        // register tiles of each width at the default sweep budget, and the
-        // widest also at a smaller budget: lighter sweeps, sometimes one more
-        // of them (which is faster depends on the circuit: measured on the
-        // 30-qubit depth-40 circuit 42.3 against 43.4 ms in complex64, 95.2
-        // against 97.8 ms in complex128, on the 35-qubit one 1.68 against
-        // 1.61 s)
-        if (st->dt == SV_C64) {
-            add(SV_MODE_REGTILE, 0, 4); add(SV_MODE_REGTILE, 0, 5); add(SV_MODE_REGTILE, 0, 6);
-            add(SV_MODE_REGTILE, 0, 6, 160);
-        } else {
-            add(SV_MODE_REGTILE, 0, 3); add(SV_MODE_REGTILE, 0, 4); add(SV_MODE_REGTILE, 0, 5);
-            add(SV_MODE_REGTILE, 0, 5, 140);
-        }
+        // register tiles of three widths around the one that suits the size,
+        // at the default sweep budget, and for large states the widest also at
+        // a smaller budget: lighter sweeps, sometimes one more of them (which
+        // is faster depends on the circuit: at 30 qubits complex64 three
+        // circuits took 35.2, 37.2, 37.5 ms at 160 and 36.1, 35.8, 35.6 at the
+        // default)
+        const int wmax = st->n > 20 ? (st->dt == SV_C64 ? 6 : 5) : (st->dt == SV_C64 ? 5 : 4);
+        for (int w = wmax - 2; w <= wmax; w++) add(SV_MODE_REGTILE, 0, w);
+        if (st->n > 20) add(SV_MODE_REGTILE, 0, wmax, st->dt == SV_C64 ? 160 : 140);
         add(SV_MODE_FUSED, 2, 0);
         add(SV_MODE_FUSED, 3, 0);
         // complex64 LDS tiles of dense 8x8 blocks are bound by the FP32 VALU

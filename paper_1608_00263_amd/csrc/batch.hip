@@ -437,6 +437,7 @@ extern "C" sv_status sv_apply_batch(sv_state **sts, const sv_circuit *cs, int64_
             rq.tile = vb;
             rq.from_zero = true;
             rq.force_zero = true;
+            rq.narrow = true;
             SV_TRY(get_plan(sts[i], &cs[i], rq, &plans[i]));
             for (const Op &op : plans[i]->ops)
                 if (op.type != OP_REGTILE || op.vbits != vb) {

@@ -526,19 +526,30 @@ __device__ __forceinline__ void regtile_op(cplx<T> (&a)[NR], int kind, int arg, 
 // processed by the calling wavefront (lane = its lane id).  ck, when not
 // null, receives a second copy of the stored tile (a checkpoint of the
 // state after the sweep, written from the registers).
-template <typename T, int VB>
+// WIDE: the tile spans the four wavefronts of the workgroup (two more
+// gathered qubits, on the wave bits); every wavefront of the workgroup calls
+// with the same tile, and lds holds XCHG_WORDS<VB> words.
+template <typename T, int VB, bool WIDE = false>
 __device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog,
-                                              uint64_t tile, int lane, cplx<T> *__restrict__ ck = nullptr) {
+                                              uint64_t tile, int lane, cplx<T> *__restrict__ ck = nullptr,
+                                              int wave = 0, T *lds = nullptr) {
     constexpr int NR = 1 << VB;
     const cptr<RTHeader> h = (cptr<RTHeader>)prog;
     uint64_t bq[VB];
 #pragma unroll
     for (int i = 0; i < VB; i++) bq[i] = 1ull << h->rq[i];
     // tile base: the tile index with zeros inserted at the tile's qubits
-    // above 3 (lane qubits and register qubits), in ascending order
-    uint64_t base = tile << 4;
+    // above 3 (lane, wave and register qubits), in ascending order
+    uint64_t tbase = tile << 4;
 #pragma unroll
-    for (int i = 0; i < VB + 2; i++) base = insert_zero(base, h->tq[i]);
+    for (int i = 0; i < VB + (WIDE ? 4 : 2); i++) tbase = insert_zero(tbase, h->tq[i]);
+    // the wave bits' part of this wavefront's addresses
+    uint64_t wb0 = 0, wb1 = 0, base = tbase;
+    if constexpr (WIDE) {
+        wb0 = 1ull << h->wq[0];
+        wb1 = 1ull << h->wq[1];
+        base |= (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
+    }
     // lane bits 0..3 are qubits 0..3; lane bits 4 and 5 are qubits lq[0],
     // lq[1].  With lq = (4, 5) a row is 64 contiguous amplitudes: uniform row
     // pointer (scalar registers) + lane index, one address register per lane.
@@ -560,6 +571,74 @@ __device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const u
         // the Hadamard layer on |0..0>: every amplitude is 2^{-n/2}
         double vd = ldexp(1.0, -(gen_n / 2));
         if (gen_n & 1) vd *= 0.70710678118654752440;
+// Pointer into LDS.
+template <typename P> using lptr = volatile __attribute__((address_space(3))) P *;
+
+// Wide tiles: the exchange of the two wave bits with the top two register
+// slots.  Wavefront w sends its registers with top bits v to wavefront v and
+// receives into the same registers those of v with top bits w, for the three
+// v != w; one component at a time through 3/4 of the tile's words (48 KB for
+// 128 KB tiles, so that three workgroups fit a CU), lane-contiguous.  The
+// accesses are volatile: paired ones (two registers per instruction) tie
+// amplitude registers into aligned groups, which costs copies and spills.
+template <int VB> constexpr int XCHG_WORDS = 4 * 3 * (1 << (VB - 2)) * 64;
+
+template <typename T, int VB, int W, bool IM>
+__device__ __forceinline__ void xchg_put(const cplx<T> (&a)[1 << VB], lptr<T> lds, int lane) {
+    constexpr int NL = 1 << (VB - 2);
+#pragma unroll
+    for (int x = 1; x < 4; x++)
+#pragma unroll
+        for (int i = 0; i < NL; i++)
+            lds[((W * 3 + x - 1) * NL + i) * 64 + lane] = IM ? a[(W ^ x) * NL + i].im : a[(W ^ x) * NL + i].re;
+}
+template <typename T, int VB, int W, bool IM>
+__device__ __forceinline__ void xchg_get(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane) {
+    constexpr int NL = 1 << (VB - 2);
+#pragma unroll
+    for (int x = 1; x < 4; x++)
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            const T v = lds[(((W ^ x) * 3 + x - 1) * NL + i) * 64 + lane];
+            if (IM) a[(W ^ x) * NL + i].im = v;
+            else a[(W ^ x) * NL + i].re = v;
+        }
+}
+template <typename T, int VB, int W>
+__device__ __forceinline__ void xchg_wave(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane) {
+    __syncthreads();   // the words are free (an earlier exchange has been read)
+    xchg_put<T, VB, W, false>(a, lds, lane);
+    __syncthreads();
+    xchg_get<T, VB, W, false>(a, lds, lane);
+    __syncthreads();
+    xchg_put<T, VB, W, true>(a, lds, lane);
+    __syncthreads();
+    xchg_get<T, VB, W, true>(a, lds, lane);
+}
+template <typename T, int VB>
+__device__ __forceinline__ void wave_exchange(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane, int wave) {
+    switch (wave) {
+    case 0: xchg_wave<T, VB, 0>(a, lds, lane); break;
+    case 1: xchg_wave<T, VB, 1>(a, lds, lane); break;
+    case 2: xchg_wave<T, VB, 2>(a, lds, lane); break;
+    default: xchg_wave<T, VB, 3>(a, lds, lane); break;
+    }
+}
+
+// The exchange and the arrangement after it: the slots' address bits bq, the
+// wave bits' wb0 and wb1, and the base of this wavefront.
+template <typename T, int VB>
+__device__ __forceinline__ void xchg_step(cplx<T> (&a)[1 << VB], T *lds, int lane, int wave, uint64_t (&bq)[VB],
+                                          uint64_t &wb0, uint64_t &wb1, uint64_t &base, uint64_t tbase) {
+    wave_exchange<T, VB>(a, (lptr<T>)lds, lane, wave);
+    const uint64_t t0 = bq[VB - 2], t1 = bq[VB - 1];
+    bq[VB - 2] = wb0;
+    bq[VB - 1] = wb1;
+    wb0 = t0;
+    wb1 = t1;
+    base = tbase | (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
+}
+
         vd *= scale;
         scale = 1.0;
         if (h->gph_off > 0) {
@@ -630,16 +709,21 @@ __device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const u
             Mat2<T> u;
 #pragma unroll
             for (int k = 0; k < 4; k++) { u.m[k].re = uf[2 * k]; u.m[k].im = uf[2 * k + 1]; }
-            regtile_op<T, NR>(a, kind, arg, nt, form, u, terms, base, lane);
+            regtile_op<T, NR>(a, kind, arg, nt, form, u, terms, base, lane);   // (does nothing for an exchange)
+            if constexpr (WIDE)
+                if (kind == RT_XCHG) xchg_step<T, VB>(a, lds, lane, wave, bq, wb0, wb1, base, tbase);
             kind = kind_n; arg = arg_n; nt = nt_n; form = form_n;
 #pragma unroll
             for (int k = 0; k < 8; k++) uf[k] = un[k];
         }
     } else {
         const cptr<RTOp> ops = (cptr<RTOp>)(prog + h->op_off);
-        for (int o = 0; o < nops; o++)
-            regtile_op<T, NR>(a, ops[o].kind, ops[o].a, ops[o].nterms, ops[o].form, load_mat<T>(ops[o].u), terms, base,
-                              lane);
+        for (int o = 0; o < nops; o++) {
+            const int kind = ops[o].kind;
+            regtile_op<T, NR>(a, kind, ops[o].a, ops[o].nterms, ops[o].form, load_mat<T>(ops[o].u), terms, base, lane);
+            if constexpr (WIDE)
+                if (kind == RT_XCHG) xchg_step<T, VB>(a, lds, lane, wave, bq, wb0, wb1, base, tbase);
+        }
     }
     if (scale != 1.0) {
         const T f = (T)scale;

@@ -26,50 +26,77 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
     const RTOp *ops = (const RTOp *)(prog + h->op_off);
     const DiagTerm *terms = (const DiagTerm *)(prog + h->term_off);
     const int vb = op.vbits, nr = 1 << vb;
-    const uint64_t ntiles = (1ull << n) >> (LANE_BITS + vb);
-    std::vector<uint64_t> roff(nr, 0);
-    for (int r = 1; r < nr; r++) roff[r] = roff[r & (r - 1)] | (1ull << h->rq[__builtin_ctz(r)]);
+    // wide tiles: four wavefronts, two more qubits on the wave bits
+    const int nw = h->wide ? 4 : 1, ntq = vb + (h->wide ? 4 : 2);
+    const uint64_t ntiles = (1ull << n) >> (4 + ntq);
     // lane l: bits 0..3 are qubits 0..3, bits 4 and 5 qubits lq[0], lq[1]
     std::vector<uint64_t> loff(64);
     for (int l = 0; l < 64; l++)
         loff[l] = (uint64_t)(l & 15) | ((uint64_t)((l >> 4) & 1) << h->lq[0]) | ((uint64_t)((l >> 5) & 1) << h->lq[1]);
-    std::vector<cx> a(64 * nr);
+    std::vector<cx> all((size_t)nw * 64 * nr);
     const bool f32 = plan.dtype == SV_C64;
     auto rnd = [&](cx v) { return f32 ? cx((float)v.real(), (float)v.imag()) : v; };
     for (uint64_t tile = 0; tile < ntiles; tile++) {
-        uint64_t base = tile << 4;
-        for (int i = 0; i < vb + 2; i++) base = ins0(base, h->tq[i]);
-        // generated state: 2^{-n/2} times the folded diagonal phases (the
-        // product of c and the ratios of the qubits whose bit is set)
-        cx gtile = 1.0;
-        const RTGenPhases *gp = nullptr;
-        if (h->gen_n > 0 && h->gph_off > 0) {
-            gp = (const RTGenPhases *)((const uint8_t *)h + h->gph_off);
-            const RTGenOut *go = (const RTGenOut *)((const uint8_t *)gp + sizeof(RTGenPhases));
-            gtile = cx(gp->c[0], gp->c[1]);
-            for (int k = 0; k < h->gph_nout; k++)
-                if (base & go[k].mask) gtile *= cx(go[k].r[0], go[k].r[1]);
-        }
-        for (int l = 0; l < 64; l++)
-            for (int r = 0; r < nr; r++) {
-                if (h->gen_n > 0) {
-                    double v = std::ldexp(1.0, -(h->gen_n / 2));
-                    if (h->gen_n & 1) v /= std::sqrt(2.0);
-                    cx x = v;
-                    if (gp) {
-                        x *= gtile;
-                        for (int b = 0; b < 6; b++)
-                            if ((l >> b) & 1) x *= cx(gp->lane[b][0], gp->lane[b][1]);
-                        for (int sb = 0; sb < vb; sb++)
-                            if ((r >> sb) & 1) x *= cx(gp->reg[sb][0], gp->reg[sb][1]);
-                    }
-                    a[l * nr + r] = rnd(x);
-                } else {
-                    a[l * nr + r] = psi[base + roff[r] + loff[l]];
-                }
+        uint64_t tbase = tile << 4;
+        for (int i = 0; i < ntq; i++) tbase = ins0(tbase, h->tq[i]);
+        int rq[8], wq[2] = {h->wq[0], h->wq[1]};
+        for (int i = 0; i < vb; i++) rq[i] = h->rq[i];
+        std::vector<uint64_t> roff(nr, 0);
+        uint64_t wbase[4];
+        auto arrange = [&]() {
+            for (int r = 1; r < nr; r++) roff[r] = roff[r & (r - 1)] | (1ull << rq[__builtin_ctz(r)]);
+            for (int w = 0; w < nw; w++)
+                wbase[w] = tbase | (w & 1 ? 1ull << wq[0] : 0ull) | (w & 2 ? 1ull << wq[1] : 0ull);
+        };
+        arrange();
+        for (int w = 0; w < nw; w++) {
+            const uint64_t base = wbase[w];
+            cx *a = &all[(size_t)w * 64 * nr];
+            // generated state: 2^{-n/2} times the folded diagonal phases (the
+            // product of c and the ratios of the qubits whose bit is set)
+            cx gtile = 1.0;
+            const RTGenPhases *gp = nullptr;
+            if (h->gen_n > 0 && h->gph_off > 0) {
+                gp = (const RTGenPhases *)((const uint8_t *)h + h->gph_off);
+                const RTGenOut *go = (const RTGenOut *)((const uint8_t *)gp + sizeof(RTGenPhases));
+                gtile = cx(gp->c[0], gp->c[1]);
+                for (int k = 0; k < h->gph_nout; k++)
+                    if (base & go[k].mask) gtile *= cx(go[k].r[0], go[k].r[1]);
             }
+            for (int l = 0; l < 64; l++)
+                for (int r = 0; r < nr; r++) {
+                    if (h->gen_n > 0) {
+                        double v = std::ldexp(1.0, -(h->gen_n / 2));
+                        if (h->gen_n & 1) v /= std::sqrt(2.0);
+                        cx x = v;
+                        if (gp) {
+                            x *= gtile;
+                            for (int b = 0; b < 6; b++)
+                                if ((l >> b) & 1) x *= cx(gp->lane[b][0], gp->lane[b][1]);
+                            for (int sb = 0; sb < vb; sb++)
+                                if ((r >> sb) & 1) x *= cx(gp->reg[sb][0], gp->reg[sb][1]);
+                        }
+                        a[l * nr + r] = rnd(x);
+                    } else {
+                        a[l * nr + r] = psi[base + roff[r] + loff[l]];
+                    }
+                }
+        }
         for (int o = 0; o < h->nops; o++) {
             const RTOp &p = ops[o];
+            if (p.kind == RT_XCHG) {
+                const int nl = nr / 4;
+                for (int w = 0; w < 4; w++)
+                    for (int v = w + 1; v < 4; v++)
+                        for (int l = 0; l < 64; l++)
+                            for (int i = 0; i < nl; i++)
+                                std::swap(all[((size_t)w * 64 + l) * nr + v * nl + i],
+                                          all[((size_t)v * 64 + l) * nr + w * nl + i]);
+                std::swap(rq[vb - 2], wq[0]);
+                std::swap(rq[vb - 1], wq[1]);
+                arrange();
+                continue;
+            }
             cx u[4];
             for (int i = 0; i < 4; i++) u[i] = rnd(to_cx(p.u, i));
             // the add-only forms are sqrt2 times the gate
@@ -83,50 +110,56 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
             case F_PHASE: u[0] = 1; u[1] = 0; u[2] = 0; break;
             default: break;
             }
-            if (p.kind == RT_REG) {
-                for (int l = 0; l < 64; l++)
-                    for (int r = 0; r < nr; r++) {
-                        if (r & (1 << p.a)) continue;
-                        cx &x = a[l * nr + r], &y = a[l * nr + (r | (1 << p.a))];
-                        cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
-                        x = nx;
-                        y = ny;
-                    }
-            } else if (p.kind == RT_LANE) {
-                for (int l = 0; l < 64; l++) {
-                    if (l & (1 << p.a)) continue;
-                    int l1 = l | (1 << p.a);
-                    for (int r = 0; r < nr; r++) {
-                        cx &x = a[l * nr + r], &y = a[l1 * nr + r];
-                        cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
-                        x = nx;
-                        y = ny;
-                    }
-                }
-            } else if (p.kind == RT_SIGNS || p.kind == RT_PHASE) {
-                int t0 = p.a, t1 = p.a + p.nterms;
-                for (int l = 0; l < 64; l++) {
-                    uint64_t par = 0;
-                    for (int t = t0; t < t1; t++) {
-                        const DiagTerm &d = terms[t];
-                        if ((base & d.outside) != d.outside) continue;
-                        if (((uint32_t)l & d.lanemask) != d.lanemask) continue;
-                        if (p.kind == RT_SIGNS) {
-                            par ^= d.regset;
-                        } else {
-                            cx v = rnd(cx(d.val[0], d.val[1]));
-                            for (int r = 0; r < nr; r++)
-                                if ((d.regset >> r) & 1) a[l * nr + r] *= v;
+            for (int w = 0; w < nw; w++) {
+                const uint64_t base = wbase[w];
+                cx *a = &all[(size_t)w * 64 * nr];
+                if (p.kind == RT_REG) {
+                    for (int l = 0; l < 64; l++)
+                        for (int r = 0; r < nr; r++) {
+                            if (r & (1 << p.a)) continue;
+                            cx &x = a[l * nr + r], &y = a[l * nr + (r | (1 << p.a))];
+                            cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
+                            x = nx;
+                            y = ny;
+                        }
+                } else if (p.kind == RT_LANE) {
+                    for (int l = 0; l < 64; l++) {
+                        if (l & (1 << p.a)) continue;
+                        int l1 = l | (1 << p.a);
+                        for (int r = 0; r < nr; r++) {
+                            cx &x = a[l * nr + r], &y = a[l1 * nr + r];
+                            cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
+                            x = nx;
+                            y = ny;
                         }
                     }
-                    for (int r = 0; r < nr; r++)
-                        if ((par >> r) & 1) a[l * nr + r] = -a[l * nr + r];
+                } else if (p.kind == RT_SIGNS || p.kind == RT_PHASE) {
+                    int t0 = p.a, t1 = p.a + p.nterms;
+                    for (int l = 0; l < 64; l++) {
+                        uint64_t par = 0;
+                        for (int t = t0; t < t1; t++) {
+                            const DiagTerm &d = terms[t];
+                            if ((base & d.outside) != d.outside) continue;
+                            if (((uint32_t)l & d.lanemask) != d.lanemask) continue;
+                            if (p.kind == RT_SIGNS) {
+                                par ^= d.regset;
+                            } else {
+                                cx v = rnd(cx(d.val[0], d.val[1]));
+                                for (int r = 0; r < nr; r++)
+                                    if ((d.regset >> r) & 1) a[l * nr + r] *= v;
+                            }
+                        }
+                    }
                 }
             }
+                        for (int r = 0; r < nr; r++)
+                            if ((par >> r) & 1) a[l * nr + r] = -a[l * nr + r];
         }
         const double sc = std::ldexp(1.0, h->sexp) * (h->shalf ? 1.0 / std::sqrt(2.0) : 1.0) * h->fscale;
-        for (int l = 0; l < 64; l++)
-            for (int r = 0; r < nr; r++) psi[base + roff[r] + loff[l]] = a[l * nr + r] * sc;
+        for (int w = 0; w < nw; w++)
+            for (int l = 0; l < 64; l++)
+                for (int r = 0; r < nr; r++)
+                    psi[wbase[w] + roff[r] + loff[l]] = all[((size_t)w * 64 + l) * nr + r] * sc;
     }
 }
 
@@ -359,7 +392,7 @@ extern "C" sv_status sv_host_plan_describe(const sv_circuit *c, sv_dtype dt, con
         if (op.type == OP_REGTILE) {
             const RTHeader *h = (const RTHeader *)(plan.prog.data() + op.prog_off);
             const RTOp *ops = (const RTOp *)((const uint8_t *)h + h->op_off);
-            int nreg = 0, nlane = 0, nsign = 0, nterm = 0, nphase = 0;
+            int nreg = 0, nlane = 0, nsign = 0, nterm = 0, nphase = 0, nxchg = 0;
             int nform[12] = {0}, nbit[6] = {0};
             for (int o = 0; o < h->nops; o++) {
                 if (ops[o].kind == RT_REG || ops[o].kind == RT_LANE) nform[std::min(11, std::max(0, (int)ops[o].form))]++;
@@ -371,6 +404,7 @@ extern "C" sv_status sv_host_plan_describe(const sv_circuit *c, sv_dtype dt, con
             std::string rq;
             for (int j = 0; j < h->vbits; j++) rq += (j ? "," : "") + std::to_string(h->rq[j]);
             rq += "] lanes=[" + std::to_string(h->lq[0]) + "," + std::to_string(h->lq[1]);
+                else if (ops[o].kind == RT_XCHG) nxchg++;
             rq += "] lanebits=[";
             for (int b = 0; b < 6; b++) rq += (b ? "," : "") + std::to_string(nbit[b]);
             std::string fs;
@@ -383,6 +417,9 @@ extern "C" sv_status sv_host_plan_describe(const sv_circuit *c, sv_dtype dt, con
         } else if (op.type == OP_LDSTILE) {
             const LTHeader *h = (const LTHeader *)(plan.prog.data() + op.prog_off);
             const LTOp *ops = (const LTOp *)((const uint8_t *)h + h->op_off);
+            if (h->wide)
+                rq += "] waves=[" + std::to_string(h->wq[0]) + "," + std::to_string(h->wq[1]) +
+                      "] exchanges=[" + std::to_string(nxchg);
             std::string ks;
             int nd = 0;
             for (int o = 0; o < h->nops; o++) {

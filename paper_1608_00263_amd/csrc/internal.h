@@ -67,6 +67,8 @@ enum RTKind : int32_t {
     RT_LANE = 2,    // dense 2x2 on lane bit a (cross-lane shuffles)
     RT_SIGNS = 3,   // nterms sign flips (CZ) starting at term index a
     RT_PHASE = 4,   // one general diagonal phase term (index a)
+    RT_XCHG = 5,    // wide tiles: the top two register slots and the wave bits
+                    // exchange their qubits
 };
 
 // Arithmetic forms of a single-qubit gate inside a register tile.  The
@@ -133,10 +135,10 @@ struct RTOpF {              // 64 bytes
     int32_t pad[4];
 };
 
-struct RTHeader {           // 128 bytes
+struct RTHeader {           // 160 bytes
     int32_t nops;
     int32_t vbits;
-    int32_t rq[8];          // register qubits, ascending
+    int32_t rq[8];          // register qubits, by slot
     int32_t nterms;
     int32_t op_off;         // byte offset of the RTOp array from the header
     int32_t term_off;       // byte offset of the DiagTerm array
@@ -148,13 +150,15 @@ struct RTHeader {           // 128 bytes
                             // product of the cosines of the F_TRX/F_TRY ops)
     int32_t lq[2];          // qubits on lane bits 4 and 5 (lane bits 0..3 are
                             // qubits 0..3); 4 and 5 give contiguous rows
-    int32_t tq[8];          // the tile's qubits above 3 (lane qubits and
-                            // register qubits), ascending: vbits + 2 entries
+    int32_t tq[10];         // the tile's qubits above 3 (lane, wave and register
+                            // qubits), ascending: vbits + 2 entries, + 2 if wide
     int32_t fop_off;        // byte offset of the RTOpF array from the header
     int32_t gph_off;        // gen_n > 0 and gph_off > 0: byte offset of the
                             // RTGenPhases of the generated state, then
     int32_t gph_nout;       // gph_nout RTGenOut records
-    int32_t pad2;
+    int32_t wide;           // 1: a tile spans the four wavefronts of a workgroup
+    int32_t wq[2];          // wide: qubits on wave bits 0 and 1 at the load
+    int32_t pad2[4];
 };
 
 // Single-qubit diagonal gates that act on the uniform state before any dense
@@ -235,6 +239,7 @@ struct Op {
     int32_t mfma = 0;       // LDSTILE program uses matrix-core blocks
     // LDSTILE: q1 = the widest block, q0 = 1 when every block of 4 or 5
     // qubits runs on the matrix cores (selects the kernel variant)
+    int32_t wide = 0;       // REGTILE: tiles of four wavefronts
     // adjoint plans: q1 of a forward REGTILE op = the checkpoint its store
     // also writes, of an ADJ_REGTILE op = the checkpoint it reads phi from
     // (-1: none)
@@ -283,6 +288,7 @@ struct PlanRequest {
 };
 
 // Validate the circuit and produce the specialised gate list in order.
+    bool narrow;         // REGTILE: tiles of one wavefront only (ensembles)
 sv_status specialise(const sv_circuit *c, int n, std::vector<SGate> *out);
 // Fold single-qubit diagonal gates into neighbouring dense gates on the
 // same qubit (exact algebra, FP64).  With param_safe, parametrised gates

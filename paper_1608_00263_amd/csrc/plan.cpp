@@ -285,9 +285,15 @@ static size_t push_bytes(std::vector<uint8_t> *buf, const void *p, size_t bytes)
 // ---------------------------------------------------------------------------
 // register tiles
 // ---------------------------------------------------------------------------
+static uint64_t bit64(int q) { return (uint64_t)1 << q; }
+
 struct Sweep {
     std::vector<int> tile;     // gathered qubits (>= LANE_BITS), ascending
     std::vector<int> items;    // indices into the gate / block list, in order
+    // wide register tiles: the qubits on lane bits 4 and 5, on the wave bits
+    // and in the register slots at the load, and the items in the order they
+    // run, -1 for an exchange of the wave bits with the top two slots
+    std::vector<int> lq, wq, rq, order;
 };
 
 // Grouping of an ordered list of items into sweeps.  An item is either
@@ -303,64 +309,66 @@ struct Sweep {
 // among the next W pending items, for a few look-ahead windows W; and a beam
 // search (beam > 1) that keeps the `beam` partial groupings with the most
 // items taken after each sweep, each extended by all of those candidates.
+// Qubit sets are 64-bit masks.  The cost of an item depends on whether its
+// first qubit is in the tile.
+using CostFn = std::function<double(int, bool)>;
 static std::vector<Sweep> group_sweeps_once(bool lookahead, int nfixed, int nitems, int n, int cap,
                                             const std::function<bool(int)> &diag,
-                                            const std::function<std::vector<int>(int)> &qubits,
-                                            const std::function<double(int, const std::vector<char> &)> &cost,
+                                            const std::function<std::vector<int>(int)> &qubits, const CostFn &cost,
                                             double budget, int beam = 1) {
     std::vector<Sweep> out;
     std::vector<char> done0(nitems, 0);
     const std::vector<char> *cur = &done0;   // the items already taken
     int left = nitems;
     std::vector<std::vector<int>> qs_of(nitems);
+    std::vector<uint64_t> mask(nitems, 0), first_bit(nitems, 0);
     std::vector<char> is_diag(nitems);
+    std::vector<double> cost_in(nitems, 0.0), cost_out(nitems, 0.0);
     for (int i = 0; i < nitems; i++) {
         qs_of[i] = qubits(i);
+        for (int q : qs_of[i]) mask[i] |= bit64(q);
+        if (!qs_of[i].empty()) first_bit[i] = bit64(qs_of[i][0]);
         is_diag[i] = diag(i) ? 1 : 0;
+        if (cost) {
+            cost_in[i] = cost(i, true);
+            cost_out[i] = cost(i, false);
+        }
     }
-    std::vector<char> block_all(n), block_dense(n), in_tile(n);
+    const bool costed = (bool)cost;
+    const uint64_t everything = bit64(n) - 1;
+    int first_left = 0;   // no item before it is left
     // one sweep from the current state; fixed != null: the gathered set is
     // given, else it grows greedily
     auto simulate = [&](const std::vector<char> *fixed, Sweep *sw) {
-        std::fill(block_all.begin(), block_all.end(), 0);
-        std::fill(block_dense.begin(), block_dense.end(), 0);
-        std::fill(in_tile.begin(), in_tile.end(), 0);
-        for (int q = 0; q < std::min(n, nfixed); q++) in_tile[q] = 1;
+        uint64_t block_all = 0, block_dense = 0, in_tile = bit64(std::min(n, nfixed)) - 1;
         int ngather = 0;
         if (fixed)
             for (int q = nfixed; q < n; q++)
-                if ((*fixed)[q]) { in_tile[q] = 1; sw->tile.push_back(q); ngather++; }
+                if ((*fixed)[q]) { in_tile |= bit64(q); sw->tile.push_back(q); ngather++; }
         double spent = 0;
-        for (int i = 0; i < nitems; i++) {
+        for (int i = first_left; i < nitems && block_all != everything; i++) {
             if ((*cur)[i]) continue;
-            const std::vector<int> &qs = qs_of[i];
+            const uint64_t qm = mask[i];
             const bool d = is_diag[i];
-            bool ok = true;
-            for (int q : qs)
-                if (block_all[q] || (!d && block_dense[q])) ok = false;
-            int need = 0;
+            bool ok = !(qm & block_all) && (d || !(qm & block_dense));
             if (ok && !d) {
-                for (int q : qs)
-                    if (!in_tile[q]) need++;
+                const int need = __builtin_popcountll(qm & ~in_tile);
                 if (need && (fixed || ngather + need > cap)) ok = false;
             }
             // arithmetic budget of a sweep (the first item always fits)
-            if (ok && cost && !sw->items.empty()) {
-                std::vector<char> t2(in_tile);
-                for (int q : qs) t2[q] = 1;
-                double c = cost(i, d ? in_tile : t2);
-                if (spent + c > budget) ok = false;
-            }
+            if (ok && costed && !sw->items.empty() &&
+                spent + (!d || (first_bit[i] & in_tile) ? cost_in[i] : cost_out[i]) > budget)
+                ok = false;
             if (ok) {
-                if (cost) spent += cost(i, in_tile);
+                if (costed) spent += first_bit[i] & in_tile ? cost_in[i] : cost_out[i];
                 if (!d)
-                    for (int q : qs)
-                        if (!in_tile[q]) { in_tile[q] = 1; sw->tile.push_back(q); ngather++; }
+                    for (int q : qs_of[i])
+                        if (!(in_tile & bit64(q))) { in_tile |= bit64(q); sw->tile.push_back(q); ngather++; }
                 sw->items.push_back(i);
             } else if (d) {
-                for (int q : qs) block_dense[q] = 1;
+                block_dense |= qm;
             } else {
-                for (int q : qs) block_all[q] = 1;
+                block_all |= qm;
             }
         }
         std::sort(sw->tile.begin(), sw->tile.end());
@@ -369,7 +377,10 @@ static std::vector<Sweep> group_sweeps_once(bool lookahead, int nfixed, int nite
     // look-ahead, one per window W
     auto candidates = [&](const std::vector<int> &windows) {
         std::vector<Sweep> cs(1);
+        first_left = 0;
+        while (first_left < nitems && (*cur)[first_left]) first_left++;
         simulate(nullptr, &cs[0]);
+        std::vector<uint64_t> tried;
         for (int W : windows) {
             std::vector<int> count(n, 0), first(n, nitems);
             int seen = 0;
@@ -391,7 +402,10 @@ static std::vector<Sweep> group_sweeps_once(bool lookahead, int nfixed, int nite
             });
             if ((int)cand.size() > cap) cand.resize(cap);
             std::vector<char> fixed(n, 0);
-            for (int q : cand) fixed[q] = 1;
+            uint64_t set = 0;
+            for (int q : cand) { fixed[q] = 1; set |= bit64(q); }
+            if (std::find(tried.begin(), tried.end(), set) != tried.end()) continue;   // the same sweep again
+            tried.push_back(set);
             Sweep sw;
             simulate(&fixed, &sw);
             cs.push_back(sw);
@@ -455,8 +469,7 @@ static std::vector<Sweep> group_sweeps_once(bool lookahead, int nfixed, int nite
 // nfixed: qubits 0..nfixed-1 are always in the sweep's set (the lanes).
 static std::vector<Sweep> group_sweeps(int nitems, int n, int cap, const std::function<bool(int)> &diag,
                                        const std::function<std::vector<int>(int)> &qubits,
-                                       const std::function<double(int, const std::vector<char> &)> &cost =
-                                           nullptr,
+                                       const CostFn &cost = nullptr,
                                        double budget = 0, int nfixed = LANE_BITS) {
     std::vector<Sweep> a = group_sweeps_once(false, nfixed, nitems, n, cap, diag, qubits, cost, budget);
     std::vector<Sweep> b = group_sweeps_once(true, nfixed, nitems, n, cap, diag, qubits, cost, budget);
@@ -466,8 +479,6 @@ static std::vector<Sweep> group_sweeps(int nitems, int n, int cap, const std::fu
     if (!c.empty() && c.size() < best.size()) best = c;
     return best;
 }
-
-static uint64_t bit64(int q) { return (uint64_t)1 << q; }
 
 struct RTProgram {
     RTHeader h{};
@@ -551,6 +562,95 @@ static std::vector<int> batch_diagonals(const std::vector<SGate> &g, const std::
     return out;
 }
 
+// Layout and schedule of a wide sweep.  Of the tile's vbits + 4 gathered
+// qubits two go to lane bits 4 and 5 (qubits 4 and 5 if gathered, else those
+// with the fewest dense gates: a lane gate costs twice a register gate), two
+// to the wave bits and the rest to registers.  A dense gate needs its qubit on
+// a lane bit or in a register; an exchange swaps the wave bits' qubits with
+// those of the top two slots.  All choices of the two pairs are tried and the
+// one with the fewest exchanges is kept (an exchange moves 3/4 of the tile
+// through LDS: about 6% of a sweep's memory time); within a stretch between
+// exchanges every item that can run does, in diagonal and dense batches.
+static void wide_layout(const std::vector<SGate> &g, int vbits, int n, Sweep *sw) {
+    std::vector<int> G(sw->tile.begin(), sw->tile.end());
+    auto has = [](const std::vector<int> &v, int q) { return std::find(v.begin(), v.end(), q) != v.end(); };
+    for (int q = 4; q < n && (int)G.size() < vbits + 4; q++)
+        if (!has(G, q)) G.push_back(q);
+    std::vector<int> dense(64, 0);
+    for (int i : sw->items)
+        if (g[i].kind == SG_DENSE) dense[g[i].q0]++;
+    std::sort(G.begin(), G.end(), [&](int a, int b) { return dense[a] != dense[b] ? dense[a] < dense[b] : a < b; });
+    std::vector<int> lq;
+    if (has(G, 4) && has(G, 5)) lq = {4, 5};
+    for (int q : G)
+        if (lq.size() < 2 && !has(lq, q)) lq.push_back(q);
+    std::sort(lq.begin(), lq.end());
+    std::vector<int> R;   // vbits + 2 qubits, fewest dense gates first
+    for (int q : G)
+        if (!has(lq, q)) R.push_back(q);
+    const int m = (int)sw->items.size();
+    std::vector<char> done(m);
+    // exchanges needed with the pairs (w0, w1) on the wave bits and (a0, a1)
+    // in the top slots at the load; with out, the items of each stretch too
+    auto run = [&](int w0, int w1, int a0, int a1, int limit, std::vector<std::vector<int>> *out) {
+        std::fill(done.begin(), done.end(), 0);
+        int left = m, count = 0;
+        for (;;) {
+            uint64_t all = 0, densely = 0, away = bit64(count % 2 ? a0 : w0) | bit64(count % 2 ? a1 : w1);
+            if (out) out->emplace_back();
+            for (int k = 0; k < m; k++) {
+                if (done[k]) continue;
+                const SGate &s = g[sw->items[k]];
+                const uint64_t qs = bit64(s.q0) | (s.kind == SG_CZ ? bit64(s.q1) : 0);
+                const bool d = s.kind != SG_DENSE;
+                if (!(qs & all) && (d || !(qs & (densely | away)))) {
+                    done[k] = 1;
+                    left--;
+                    if (out) out->back().push_back(sw->items[k]);
+                } else if (d) {
+                    densely |= qs;
+                } else {
+                    all |= qs;
+                }
+            }
+            if (!left || count >= limit) return count;
+            count++;
+        }
+    };
+    int best = 1 << 20, bp[4] = {0, 1, 2, 3};
+    const int r = (int)R.size();
+    int used = 0;   // qubits that need a register at some time
+    for (int q : R) used += dense[q] > 0;
+    const int least = used > vbits ? 1 : 0;
+    for (int i = 0; i < r && best > least; i++)
+        for (int j = i + 1; j < r && best > least; j++)
+            for (int k = 0; k < r && best > least; k++)
+                for (int l = k + 1; l < r && best > least; l++) {
+                    if (k == i || k == j || l == i || l == j) continue;
+                    const int c = run(R[i], R[j], R[k], R[l], best, nullptr);
+                    if (c < best) {
+                        best = c;
+                        bp[0] = i; bp[1] = j; bp[2] = k; bp[3] = l;
+                    }
+                }
+    std::vector<std::vector<int>> parts;
+    run(R[bp[0]], R[bp[1]], R[bp[2]], R[bp[3]], 1 << 20, &parts);
+    sw->lq = lq;
+    sw->wq = {R[bp[0]], R[bp[1]]};
+    sw->rq.clear();
+    for (int i = 0; i < r; i++)
+        if (i != bp[0] && i != bp[1] && i != bp[2] && i != bp[3]) sw->rq.push_back(R[i]);
+    std::sort(sw->rq.begin(), sw->rq.end());
+    sw->rq.push_back(R[bp[2]]);
+    sw->rq.push_back(R[bp[3]]);
+    sw->order.clear();
+    for (size_t p = 0; p < parts.size(); p++) {
+        if (p) sw->order.push_back(-1);
+        const std::vector<int> o = batch_diagonals(g, parts[p]);
+        sw->order.insert(sw->order.end(), o.begin(), o.end());
+    }
+}
+
 // gen: the sweep starts from the uniform state (generated in its registers);
 // single-qubit diagonals without a gradient slot that act before any dense
 // gate on their qubit are then folded into the generated values.
@@ -559,41 +659,47 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
     RTProgram P;
     RTHeader &h = P.h;
     h.vbits = vbits;
-    // Lane bits 0..3 are qubits 0..3.  Lane bits 4 and 5 take qubits 4 and 5
-    // when the sweep has them (contiguous 512-byte rows), else the gathered
-    // qubits with the fewest dense gates in the sweep (cross-lane gates cost
-    // more than register gates).  The other gathered qubits go to registers;
-    // unused slots are filled with further qubits so that every tile covers
-    // 2^(6+vbits) distinct amplitudes.
-    std::vector<int> G(sw.tile.begin(), sw.tile.end());
-    for (int q = 4; q < std::min(n, LANE_BITS); q++)
-        if (std::find(G.begin(), G.end(), q) == G.end() && (int)G.size() < vbits + 2) G.push_back(q);
-    std::vector<int> dense(64, 0);
-    for (int idx : sw.items)
-        if (g[idx].kind == SG_DENSE) dense[g[idx].q0]++;
+    const bool wide = !sw.rq.empty();
     std::vector<int> lq, rq;
-    for (int q : {4, 5})
-        if (std::find(G.begin(), G.end(), q) != G.end()) lq.push_back(q);
-    std::vector<int> rest;
-    for (int q : G)
-        if (std::find(lq.begin(), lq.end(), q) == lq.end()) rest.push_back(q);
-    std::sort(rest.begin(), rest.end(), [&](int a, int b) { return dense[a] != dense[b] ? dense[a] < dense[b] : a < b; });
-    // keep the gathered set's register share within vbits
-    size_t take_lanes = rest.size() > (size_t)vbits ? rest.size() - (size_t)vbits : 0;
-    for (size_t i = 0; i < rest.size(); i++) {
-        if (lq.size() < 2 && (i < take_lanes || (int)(rest.size() - i) > vbits)) lq.push_back(rest[i]);
-        else rq.push_back(rest[i]);
+    if (wide) {
+        lq = sw.lq;
+        rq = sw.rq;
+    } else {
+        // Lane bits 0..3 are qubits 0..3.  Lane bits 4 and 5 take qubits 4 and 5
+        // when the sweep has them (contiguous 512-byte rows), else the gathered
+        // qubits with the fewest dense gates in the sweep (cross-lane gates cost
+        // more than register gates).  The other gathered qubits go to registers;
+        // unused slots are filled with further qubits so that every tile covers
+        // 2^(6+vbits) distinct amplitudes.
+        std::vector<int> G(sw.tile.begin(), sw.tile.end());
+        for (int q = 4; q < std::min(n, LANE_BITS); q++)
+            if (std::find(G.begin(), G.end(), q) == G.end() && (int)G.size() < vbits + 2) G.push_back(q);
+        std::vector<int> dense(64, 0);
+        for (int idx : sw.items)
+            if (g[idx].kind == SG_DENSE) dense[g[idx].q0]++;
+        for (int q : {4, 5})
+            if (std::find(G.begin(), G.end(), q) != G.end()) lq.push_back(q);
+        std::vector<int> rest;
+        for (int q : G)
+            if (std::find(lq.begin(), lq.end(), q) == lq.end()) rest.push_back(q);
+        std::sort(rest.begin(), rest.end(), [&](int a, int b) { return dense[a] != dense[b] ? dense[a] < dense[b] : a < b; });
+        // keep the gathered set's register share within vbits
+        size_t take_lanes = rest.size() > (size_t)vbits ? rest.size() - (size_t)vbits : 0;
+        for (size_t i = 0; i < rest.size(); i++) {
+            if (lq.size() < 2 && (i < take_lanes || (int)(rest.size() - i) > vbits)) lq.push_back(rest[i]);
+            else rq.push_back(rest[i]);
+        }
+        auto used = [&](int q) {
+            return q < 4 || std::find(lq.begin(), lq.end(), q) != lq.end() ||
+                   std::find(rq.begin(), rq.end(), q) != rq.end();
+        };
+        for (int q = 4; lq.size() < 2 && q < n; q++)
+            if (!used(q)) lq.push_back(q);
+        for (int q = 4; (int)rq.size() < vbits && q < n; q++)
+            if (!used(q)) rq.push_back(q);
+        std::sort(lq.begin(), lq.end());
+        std::sort(rq.begin(), rq.end());
     }
-    auto used = [&](int q) {
-        return q < 4 || std::find(lq.begin(), lq.end(), q) != lq.end() ||
-               std::find(rq.begin(), rq.end(), q) != rq.end();
-    };
-    for (int q = 4; lq.size() < 2 && q < n; q++)
-        if (!used(q)) lq.push_back(q);
-    for (int q = 4; (int)rq.size() < vbits && q < n; q++)
-        if (!used(q)) rq.push_back(q);
-    std::sort(lq.begin(), lq.end());
-    std::sort(rq.begin(), rq.end());
     std::vector<int> slot(64, -1), lane_of(64, -1);
     for (int q = 0; q < 4; q++) lane_of[q] = q;
     lane_of[lq[0]] = 4;
@@ -603,11 +709,14 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
     std::vector<int> tq(rq);
     tq.push_back(lq[0]);
     tq.push_back(lq[1]);
-    std::sort(tq.begin(), tq.end());
-    for (int i = 0; i < 8; i++) {
-        h.rq[i] = i < (int)rq.size() ? rq[i] : -1;
-        h.tq[i] = i < (int)tq.size() ? tq[i] : -1;
+    h.wide = wide ? 1 : 0;
+    for (int i = 0; i < 2; i++) {
+        h.wq[i] = wide ? sw.wq[i] : -1;
+        if (wide) tq.push_back(sw.wq[i]);
     }
+    std::sort(tq.begin(), tq.end());
+    for (int i = 0; i < 8; i++) h.rq[i] = i < (int)rq.size() ? rq[i] : -1;
+    for (int i = 0; i < 10; i++) h.tq[i] = i < (int)tq.size() ? tq[i] : -1;
     for (size_t i = 0; i < rq.size(); i++) slot[rq[i]] = (int)i;
     std::vector<RTOp> &ops = P.ops;
     std::vector<DiagTerm> &terms = P.terms;
@@ -625,7 +734,8 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
         return t;
     };
     int nc = 0;
-    const std::vector<int> order = batch_diagonals(g, sw.items);
+    std::vector<int> wnow = wide ? sw.wq : std::vector<int>();   // qubits on the wave bits
+    const std::vector<int> order = wide ? sw.order : batch_diagonals(g, sw.items);
     std::vector<char> fold(order.size(), 0);
     if (gen) {
         // diagonals commute with each other and with CZ, so one before the
@@ -638,6 +748,7 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
         std::vector<std::pair<int, cd>> outr;
         auto mul = [](cd a, cd b) { return cd{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; };
         for (size_t k = 0; k < order.size(); k++) {
+            if (order[k] < 0) continue;
             const SGate &s = g[order[k]];
             if (s.kind == SG_DENSE) { dense_seen[s.q0] = 1; continue; }
             if (s.kind != SG_DIAG1 || s.slot >= 0 || dense_seen[s.q0]) continue;
@@ -698,6 +809,20 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
             double c = 1.0;
             if (s.kind == SG_DENSE && tangent_form(&o, &c)) h.fscale *= c;
             ops.push_back(o);
+        if (idx < 0) {   // exchange: the wave bits' qubits move into the top slots
+            RTOp o{};
+            o.kind = RT_XCHG;
+            o.slot = -1;
+            o.gscale = 1.0;
+            ops.push_back(o);
+            P.opc.push_back(1.0);
+            for (int i = 0; i < 2; i++) {
+                slot[rq[vbits - 2 + i]] = -1;
+                slot[wnow[i]] = vbits - 2 + i;
+                std::swap(rq[vbits - 2 + i], wnow[i]);
+            }
+            continue;
+        }
             P.opc.push_back(c);
         } else if (s.kind == SG_CZ) {
             DiagTerm t = term_for(bit64(s.q0) | bit64(s.q1));
@@ -905,6 +1030,7 @@ struct Block {
 static std::vector<Block> fuse_blocks(const std::vector<SGate> &g, int n, int kmax) {
     std::vector<Block> blocks;
     std::vector<int> last(n, -1);
+    op.wide = P.h.wide;
     for (int i = 0; i < (int)g.size(); i++) {
         const SGate &s = g[i];
         std::vector<int> qs = {s.q0};
@@ -1191,21 +1317,21 @@ static void plan_per_gate(const sv_circuit *c, const std::vector<SGate> &g, cons
 // flex: lane bits 4 and 5 may take any qubit (the sweep gathers vb + 2
 // qubits above 3) instead of qubits 4 and 5.
 static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
-                                         double budget, bool flex) {
+                                         double budget, bool flex, bool wide) {
     (void)dtype;
     const int nfixed = flex ? 4 : LANE_BITS;
-    auto cost = [&](int i, const std::vector<char> &in_tile) -> double {
+    auto cost = [&](int i, bool in_tile) -> double {
         const SGate &s = g[i];
         if (s.kind == SG_CZ) return 1.0;
         const bool lane = s.q0 < nfixed;
-        const bool reg = !lane && in_tile[s.q0];
+        const bool reg = !lane && in_tile;
         if (s.kind == SG_DIAG1) return reg ? 2.0 : 4.0;
         if (form_scaled(s.form) || s.form == F_RX || s.form == F_RY) return lane ? 5.0 : 2.0;
         if (s.form == F_GEN) return lane ? 11.0 : 8.0;
         return lane ? 7.0 : 4.0;   // real forms
     };
-    return group_sweeps(
-        (int)g.size(), n, vb + (LANE_BITS - nfixed), [&](int i) { return g[i].kind != SG_DENSE; },
+    std::vector<Sweep> sweeps = group_sweeps(
+        (int)g.size(), n, vb + (LANE_BITS - nfixed) + (wide ? 2 : 0), [&](int i) { return g[i].kind != SG_DENSE; },
         [&](int i) {
             std::vector<int> q = {g[i].q0};
             if (g[i].kind == SG_CZ) q.push_back(g[i].q1);
@@ -1220,9 +1346,11 @@ static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n
 // angles every step, so the last groupings are kept, found by their whole
 // input.
 static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
-                                         double budget = -1, bool flex = false) {
-    if (budget < 0) budget = dtype == SV_C64 ? 250.0 : 220.0;
-    std::vector<int32_t> key = {n, vb, flex ? 1 : 0, (int32_t)(budget * 256.0)};
+                                         double budget = -1, bool flex = false, bool wide = false) {
+    // the wide default: 30 qubits complex64, three circuits, 35.6-36.1 ms at 300
+    // against 35.5-38.9 at 250 and 35.2-37.5 at 160; complex128 flat from 200
+    if (budget < 0) budget = dtype == SV_C64 ? (wide ? 300.0 : 250.0) : 220.0;
+    std::vector<int32_t> key = {n, vb, (flex ? 1 : 0) | (wide ? 2 : 0), (int32_t)(budget * 256.0)};
     key.reserve(4 + 4 * g.size());
     for (const SGate &s : g) key.insert(key.end(), {s.kind, s.form, s.q0, s.q1});
     constexpr size_t KEPT = 64;
@@ -1233,11 +1361,14 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
         auto it = kept->find(key);
         if (it != kept->end()) return it->second;
     }
-    std::vector<Sweep> sw = find_regtile_sweeps(g, n, vb, dtype, budget, flex);
+    std::vector<Sweep> sw = find_regtile_sweeps(g, n, vb, dtype, budget, flex, wide);
     std::lock_guard<std::mutex> lock(*mu);
     if (kept->size() >= KEPT) kept->clear();
     (*kept)[std::move(key)] = sw;
     return sw;
+    if (wide)
+        for (Sweep &sw : sweeps) wide_layout(g, vb, n, &sw);
+    return sweeps;
 }
 
 std::string plan_key(const sv_circuit *c, const PlanRequest &rq) {
@@ -1266,6 +1397,19 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
     SV_TRY(specialise(c, rq.n, &g));
     plan->n = rq.n;
     plan->dtype = rq.dtype;
+// Register qubits of a tile when the caller names none.  Large states take
+// the widest tile that keeps 3 wavefronts per SIMD; small ones are bound by
+// the time one wavefront needs for its operations (their code comes from
+// beyond the instruction cache), so narrower tiles on more wavefronts finish
+// sooner although they need more sweeps.  Depth-30 circuits, us by width 3, 4,
+// 5 (and 6): complex64 16 qubits 53, 60, 74, 104; 20 qubits 88, 88, 103, 139;
+// 22 qubits 181, 141, 139, 166; 25 qubits 1419, 884, 731, 716; complex128 16
+// qubits 62, 71, 91; 20 qubits 105, 111, 132; 22 qubits 231, 185, 194; 25
+// qubits 1679, 1525, 1433.
+static int default_width(int n, int dtype) {
+    return dtype == SV_C64 ? std::max(3, std::min(6, (n - 12) / 2)) : std::max(3, std::min(5, (n - 14) / 2));
+}
+
     int mode = rq.mode;
     // tile kernels need the 64 lanes of a wavefront plus gathered qubits
     if ((mode == SV_MODE_REGTILE || mode == SV_MODE_FUSED || mode == SV_MODE_TILED) && rq.n < 10)
@@ -1288,10 +1432,20 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         plan_per_gate(c, g, r2, plan);
     } else if (mode == SV_MODE_REGTILE) {
         fold_diagonals(&g, rq.n, false, true);
-        int vb = rq.tile > 0 ? rq.tile : (rq.dtype == SV_C64 ? 6 : 5);
+        int vb = rq.tile > 0 ? rq.tile : default_width(rq.n, rq.dtype);
         vb = std::max(1, std::min(vb, rq.dtype == SV_C64 ? 6 : 5));
         vb = std::min(vb, rq.n - LANE_BITS);
-        auto sweeps = regtile_sweeps(g, rq.n, vb, rq.dtype, rq.budget > 0 ? (double)rq.budget : -1.0, true);
+        const double budget = rq.budget > 0 ? (double)rq.budget : -1.0;
+        auto sweeps = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true);
+        // Tiles of four wavefronts where their two more gathered qubits save a
+        // sweep: 30 qubits complex64 10 sweeps in 35.0 ms against 13 in 40.4,
+        // 28 qubits complex128 10 in 17.0 ms against 14 in 22.2.  With equal
+        // counts the exchanges only cost (12 qubits complex128, 3 register
+        // qubits: 44.7 against 40.9 us).
+        if (!rq.narrow && vb >= 2 && rq.n >= vb + LANE_BITS + 2) {
+            auto w = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true, true);
+            if (!w.empty() && w.size() < sweeps.size()) sweeps.swap(w);
+        }
         std::vector<std::pair<size_t, int>> scales;
         // the uniform initialisation is generated inside the first sweep's
         // registers instead of being written and read back (with the

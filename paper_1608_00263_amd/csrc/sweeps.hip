@@ -127,6 +127,23 @@ __global__ __launch_bounds__(BLOCK, (sizeof(T) << VB) <= 256 ? 3 : 1) void k_reg
     regtile_apply<T, VB>(psi, prog, tile, lane, ck);
 }
 
+// A register tile over the four wavefronts of a workgroup: 2^(VB + 8)
+// amplitudes, two more gathered qubits than one wavefront's tile, so fewer
+// sweeps (30 qubits complex64 10 instead of 13, 28 qubits complex128 10
+// instead of 14).  The four wavefronts meet only at an exchange (one per sweep
+// of the random circuits, 48 KB of LDS for 128 KB tiles: three workgroups per
+// CU, as the registers allow).  The complex64 sweeps are then bound by VALU
+// issue (35 ms for the 30-qubit circuit at any of 9 or 10 sweeps), the
+// complex128 ones by HBM (1.7 ms for 2 x 4 GiB, 5.1 TB/s).
+template <typename T, int VB>
+__global__ __launch_bounds__(BLOCK, (sizeof(T) << VB) <= 256 ? 3 : 1) void k_widetile(cplx<T> *__restrict__ psi,
+                                                   const uint8_t *__restrict__ prog) {
+    __shared__ T lds[XCHG_WORDS<VB>];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    regtile_apply<T, VB, true>(psi, prog, blockIdx.x, lane, nullptr, wave, lds);
+}
+
 // ---------------------------------------------------------------------------
 // LDS tiles
 // ---------------------------------------------------------------------------
@@ -503,6 +520,24 @@ static sv_status launch_typed(sv_state *st, const Plan &plan, const Op &op, cplx
         break;
     case OP_REGTILE: {
         const uint8_t *prog = (const uint8_t *)plan.dprog + op.prog_off;
+        if (op.wide) {
+            if (ck) return fail(SV_EINVAL, "a checkpoint store needs tiles of one wavefront");
+            const unsigned wgrid = (unsigned)(N >> (LANE_BITS + 2 + op.vbits));
+#define WT_CASE(VB) \
+    case VB: hipLaunchKernelGGL((k_widetile<T, VB>), dim3(wgrid), dim3(BLOCK), 0, s, psi, prog); break;
+            switch (op.vbits) {
+                WT_CASE(2) WT_CASE(3) WT_CASE(4) WT_CASE(5)
+            case 6:
+                if constexpr (sizeof(T) == 4) {
+                    hipLaunchKernelGGL((k_widetile<T, 6>), dim3(wgrid), dim3(BLOCK), 0, s, psi, prog);
+                    break;
+                }
+                return fail(SV_EINVAL, "wide register tile too large for complex128");
+            default: return fail(SV_EINVAL, "wide register tile width out of range");
+            }
+#undef WT_CASE
+            break;
+        }
         const uint64_t ntiles = N >> (LANE_BITS + op.vbits);
         const unsigned grid = (unsigned)((ntiles + 3) / 4);
 #define RT_CASE(VB) \

@@ -225,3 +225,37 @@ def test_kept_groupings_follow_the_structure():
                 got = sv.host_emulate(c, oracle.zero_state(c.n), dtype, "regtile", 0, tile)
                 # complex64 plans carry FP32 coefficients (the bound of the replays above)
                 assert np.linalg.norm(got - oracle.apply_circuit(c)) < (1e-5 if dtype == "c64" else 1e-11)
+
+
+WIDE_CASES = [(10, 2, "c64"), (11, 3, "c64"), (12, 4, "c64"), (13, 5, "c64"), (14, 6, "c64"), (15, 6, "c64"),
+              (16, 3, "c64"), (10, 2, "c128"), (11, 3, "c128"), (13, 5, "c128"), (14, 4, "c128"), (15, 5, "c128")]
+
+
+def wide_circuits(n):
+    """Gates of every kind on random qubits (several exchanges a sweep) and a
+    lattice chain from |0..0>."""
+    return C.random_unitary_circuit(n, 160, seed=300 + n), C.make_circuit(1, n, 30, seed=n)
+
+
+@pytest.mark.parametrize("n,tile,dtype", WIDE_CASES)
+def test_wide_tiles_replay(n, tile, dtype):
+    # tiles of four wavefronts from one tile per state up: layout, exchanges,
+    # masks of the wave bits, generated first sweep
+    rnd, chain = wide_circuits(n)
+    psi0 = C.random_state(n, 9, dtype=np.complex128)
+    tol = 1e-5 if dtype == "c64" else 1e-12
+    for budget in (0, 60, 2000):
+        got = sv.host_emulate(rnd, psi0, dtype, "regtile", 0, tile, from_zero=False, budget=budget)
+        assert np.linalg.norm(got - oracle.apply_circuit(rnd, psi0.copy())) < tol, budget
+        got = sv.host_emulate(chain, oracle.zero_state(n), dtype, "regtile", 0, tile, budget=budget)
+        assert np.linalg.norm(got - oracle.apply_circuit(chain)) < tol, budget
+
+
+def test_wide_tiles_are_planned():
+    # the lattice circuits take them at the sizes that have more sweeps
+    # without, with at least one exchange
+    for dtype in ("c64", "c128"):
+        text = sv.host_plan_describe(C.make_circuit(4, 5, 30, seed=5), dtype, "regtile")
+        assert "waves=[" in text and "exchanges=[1" in text
+        narrow = sv.host_plan_describe(C.make_circuit(2, 5, 30, seed=5), dtype, "regtile", 0, 5)
+        assert "waves=[" not in narrow
