@@ -522,55 +522,6 @@ __device__ __forceinline__ void regtile_op(cplx<T> (&a)[NR], int kind, int arg, 
     }
 }
 
-// One register tile of a sweep: tile index `tile` of the program at prog,
-// processed by the calling wavefront (lane = its lane id).  ck, when not
-// null, receives a second copy of the stored tile (a checkpoint of the
-// state after the sweep, written from the registers).
-// WIDE: the tile spans the four wavefronts of the workgroup (two more
-// gathered qubits, on the wave bits); every wavefront of the workgroup calls
-// with the same tile, and lds holds XCHG_WORDS<VB> words.
-template <typename T, int VB, bool WIDE = false>
-__device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog,
-                                              uint64_t tile, int lane, cplx<T> *__restrict__ ck = nullptr,
-                                              int wave = 0, T *lds = nullptr) {
-    constexpr int NR = 1 << VB;
-    const cptr<RTHeader> h = (cptr<RTHeader>)prog;
-    uint64_t bq[VB];
-#pragma unroll
-    for (int i = 0; i < VB; i++) bq[i] = 1ull << h->rq[i];
-    // tile base: the tile index with zeros inserted at the tile's qubits
-    // above 3 (lane, wave and register qubits), in ascending order
-    uint64_t tbase = tile << 4;
-#pragma unroll
-    for (int i = 0; i < VB + (WIDE ? 4 : 2); i++) tbase = insert_zero(tbase, h->tq[i]);
-    // the wave bits' part of this wavefront's addresses
-    uint64_t wb0 = 0, wb1 = 0, base = tbase;
-    if constexpr (WIDE) {
-        wb0 = 1ull << h->wq[0];
-        wb1 = 1ull << h->wq[1];
-        base |= (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
-    }
-    // lane bits 0..3 are qubits 0..3; lane bits 4 and 5 are qubits lq[0],
-    // lq[1].  With lq = (4, 5) a row is 64 contiguous amplitudes: uniform row
-    // pointer (scalar registers) + lane index, one address register per lane.
-    const int l4 = h->lq[0], l5 = h->lq[1];
-    const bool rows = (l4 == 4) & (l5 == 5);
-    const uint64_t loff = (uint64_t)(lane & 15) | ((uint64_t)((lane >> 4) & 1) << l4) |
-                          ((uint64_t)((lane >> 5) & 1) << l5);
-
-    cplx<T> a[NR];
-    const int gen_n = h->gen_n;
-    // the Clifford forms leave a power of sqrt2 (2^sexp exactly, then
-    // 1/sqrt2) and the tangent-form rotations their cosines: one factor,
-    // applied to the generated value when the sweep generates its input
-    // (the ops are linear), else once after the ops
-    double scale = ldexp(1.0, h->sexp);
-    if (h->shalf) scale *= 0.70710678118654752440;
-    scale *= h->fscale;
-    if (gen_n > 0) {
-        // the Hadamard layer on |0..0>: every amplitude is 2^{-n/2}
-        double vd = ldexp(1.0, -(gen_n / 2));
-        if (gen_n & 1) vd *= 0.70710678118654752440;
 // Pointer into LDS.
 template <typename P> using lptr = volatile __attribute__((address_space(3))) P *;
 
@@ -639,6 +590,55 @@ __device__ __forceinline__ void xchg_step(cplx<T> (&a)[1 << VB], T *lds, int lan
     base = tbase | (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
 }
 
+// One register tile of a sweep: tile index `tile` of the program at prog,
+// processed by the calling wavefront (lane = its lane id).  ck, when not
+// null, receives a second copy of the stored tile (a checkpoint of the
+// state after the sweep, written from the registers).
+// WIDE: the tile spans the four wavefronts of the workgroup (two more
+// gathered qubits, on the wave bits); every wavefront of the workgroup calls
+// with the same tile, and lds holds XCHG_WORDS<VB> words.
+template <typename T, int VB, bool WIDE = false>
+__device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog,
+                                              uint64_t tile, int lane, cplx<T> *__restrict__ ck = nullptr,
+                                              int wave = 0, T *lds = nullptr) {
+    constexpr int NR = 1 << VB;
+    const cptr<RTHeader> h = (cptr<RTHeader>)prog;
+    uint64_t bq[VB];
+#pragma unroll
+    for (int i = 0; i < VB; i++) bq[i] = 1ull << h->rq[i];
+    // tile base: the tile index with zeros inserted at the tile's qubits
+    // above 3 (lane, wave and register qubits), in ascending order
+    uint64_t tbase = tile << 4;
+#pragma unroll
+    for (int i = 0; i < VB + (WIDE ? 4 : 2); i++) tbase = insert_zero(tbase, h->tq[i]);
+    // the wave bits' part of this wavefront's addresses
+    uint64_t wb0 = 0, wb1 = 0, base = tbase;
+    if constexpr (WIDE) {
+        wb0 = 1ull << h->wq[0];
+        wb1 = 1ull << h->wq[1];
+        base |= (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
+    }
+    // lane bits 0..3 are qubits 0..3; lane bits 4 and 5 are qubits lq[0],
+    // lq[1].  With lq = (4, 5) a row is 64 contiguous amplitudes: uniform row
+    // pointer (scalar registers) + lane index, one address register per lane.
+    const int l4 = h->lq[0], l5 = h->lq[1];
+    const bool rows = (l4 == 4) & (l5 == 5);
+    const uint64_t loff = (uint64_t)(lane & 15) | ((uint64_t)((lane >> 4) & 1) << l4) |
+                          ((uint64_t)((lane >> 5) & 1) << l5);
+
+    cplx<T> a[NR];
+    const int gen_n = h->gen_n;
+    // the Clifford forms leave a power of sqrt2 (2^sexp exactly, then
+    // 1/sqrt2) and the tangent-form rotations their cosines: one factor,
+    // applied to the generated value when the sweep generates its input
+    // (the ops are linear), else once after the ops
+    double scale = ldexp(1.0, h->sexp);
+    if (h->shalf) scale *= 0.70710678118654752440;
+    scale *= h->fscale;
+    if (gen_n > 0) {
+        // the Hadamard layer on |0..0>: every amplitude is 2^{-n/2}
+        double vd = ldexp(1.0, -(gen_n / 2));
+        if (gen_n & 1) vd *= 0.70710678118654752440;
         vd *= scale;
         scale = 1.0;
         if (h->gph_off > 0) {

@@ -149,11 +149,11 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                                     if ((d.regset >> r) & 1) a[l * nr + r] *= v;
                             }
                         }
+                        for (int r = 0; r < nr; r++)
+                            if ((par >> r) & 1) a[l * nr + r] = -a[l * nr + r];
                     }
                 }
             }
-                        for (int r = 0; r < nr; r++)
-                            if ((par >> r) & 1) a[l * nr + r] = -a[l * nr + r];
         }
         const double sc = std::ldexp(1.0, h->sexp) * (h->shalf ? 1.0 / std::sqrt(2.0) : 1.0) * h->fscale;
         for (int w = 0; w < nw; w++)
@@ -399,12 +399,12 @@ extern "C" sv_status sv_host_plan_describe(const sv_circuit *c, sv_dtype dt, con
                 if (ops[o].kind == RT_REG) nreg++;
                 else if (ops[o].kind == RT_LANE) { nlane++; nbit[std::min(5, std::max(0, (int)ops[o].a))]++; }
                 else if (ops[o].kind == RT_SIGNS) { nsign++; nterm += ops[o].nterms; }
+                else if (ops[o].kind == RT_XCHG) nxchg++;
                 else nphase++;
             }
             std::string rq;
             for (int j = 0; j < h->vbits; j++) rq += (j ? "," : "") + std::to_string(h->rq[j]);
             rq += "] lanes=[" + std::to_string(h->lq[0]) + "," + std::to_string(h->lq[1]);
-                else if (ops[o].kind == RT_XCHG) nxchg++;
             rq += "] lanebits=[";
             for (int b = 0; b < 6; b++) rq += (b ? "," : "") + std::to_string(nbit[b]);
             std::string fs;
@@ -412,14 +412,14 @@ extern "C" sv_status sv_host_plan_describe(const sv_circuit *c, sv_dtype dt, con
                                             "trx", "try"};
             for (int f = 0; f < 12; f++)
                 if (nform[f]) fs += std::string(fs.empty() ? "" : ",") + fname[f] + ":" + std::to_string(nform[f]);
+            if (h->wide)
+                rq += "] waves=[" + std::to_string(h->wq[0]) + "," + std::to_string(h->wq[1]) +
+                      "] exchanges=[" + std::to_string(nxchg);
             snprintf(line, sizeof line, "%zu regtile v=%d rq=[%s] reg=%d lane=%d signops=%d cz=%d phase=%d forms=[%s]\n",
                      i, h->vbits, rq.c_str(), nreg, nlane, nsign, nterm, nphase, fs.c_str());
         } else if (op.type == OP_LDSTILE) {
             const LTHeader *h = (const LTHeader *)(plan.prog.data() + op.prog_off);
             const LTOp *ops = (const LTOp *)((const uint8_t *)h + h->op_off);
-            if (h->wide)
-                rq += "] waves=[" + std::to_string(h->wq[0]) + "," + std::to_string(h->wq[1]) +
-                      "] exchanges=[" + std::to_string(nxchg);
             std::string ks;
             int nd = 0;
             for (int o = 0; o < h->nops; o++) {

@@ -236,10 +236,10 @@ struct Op {
     int32_t vbits = 0;      // REGTILE: register qubits; LDSTILE: tile bits
     size_t prog_off = 0;    // byte offset in the plan's program buffer
     double bytes = 0;       // algorithmic HBM bytes of this sweep
+    int32_t wide = 0;       // REGTILE: tiles of four wavefronts
     int32_t mfma = 0;       // LDSTILE program uses matrix-core blocks
     // LDSTILE: q1 = the widest block, q0 = 1 when every block of 4 or 5
     // qubits runs on the matrix cores (selects the kernel variant)
-    int32_t wide = 0;       // REGTILE: tiles of four wavefronts
     // adjoint plans: q1 of a forward REGTILE op = the checkpoint its store
     // also writes, of an ADJ_REGTILE op = the checkpoint it reads phi from
     // (-1: none)
@@ -285,10 +285,10 @@ struct PlanRequest {
                          // replaced by the uniform initialisation
     bool force_zero;     // the plan must itself start from |0..0>
     bool no_mfma;        // k >= 4 blocks on the VALU
+    bool narrow;         // REGTILE: tiles of one wavefront only (ensembles)
 };
 
 // Validate the circuit and produce the specialised gate list in order.
-    bool narrow;         // REGTILE: tiles of one wavefront only (ensembles)
 sv_status specialise(const sv_circuit *c, int n, std::vector<SGate> *out);
 // Fold single-qubit diagonal gates into neighbouring dense gates on the
 // same qubit (exact algebra, FP64).  With param_safe, parametrised gates

@@ -785,6 +785,20 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
     for (size_t k = 0; k < order.size(); k++) {
         if (fold[k]) continue;
         const int idx = order[k];
+        if (idx < 0) {   // exchange: the wave bits' qubits move into the top slots
+            RTOp o{};
+            o.kind = RT_XCHG;
+            o.slot = -1;
+            o.gscale = 1.0;
+            ops.push_back(o);
+            P.opc.push_back(1.0);
+            for (int i = 0; i < 2; i++) {
+                slot[rq[vbits - 2 + i]] = -1;
+                slot[wnow[i]] = vbits - 2 + i;
+                std::swap(rq[vbits - 2 + i], wnow[i]);
+            }
+            continue;
+        }
         const SGate &s = g[idx];
         const bool in_tile = lane_of[s.q0] >= 0 || slot[s.q0] >= 0;
         if (s.kind == SG_DENSE || (s.kind == SG_DIAG1 && in_tile)) {
@@ -809,20 +823,6 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
             double c = 1.0;
             if (s.kind == SG_DENSE && tangent_form(&o, &c)) h.fscale *= c;
             ops.push_back(o);
-        if (idx < 0) {   // exchange: the wave bits' qubits move into the top slots
-            RTOp o{};
-            o.kind = RT_XCHG;
-            o.slot = -1;
-            o.gscale = 1.0;
-            ops.push_back(o);
-            P.opc.push_back(1.0);
-            for (int i = 0; i < 2; i++) {
-                slot[rq[vbits - 2 + i]] = -1;
-                slot[wnow[i]] = vbits - 2 + i;
-                std::swap(rq[vbits - 2 + i], wnow[i]);
-            }
-            continue;
-        }
             P.opc.push_back(c);
         } else if (s.kind == SG_CZ) {
             DiagTerm t = term_for(bit64(s.q0) | bit64(s.q1));
@@ -1005,6 +1005,7 @@ static void push_regtile(const RTProgram &P, int n, int dtype, OpType type, std:
     Op op;
     op.type = type;
     op.vbits = P.h.vbits;
+    op.wide = P.h.wide;
     op.prog_off = hoff;
     op.bytes = (type == OP_ADJ_REGTILE ? 4 : 2) * state_bytes(n, dtype);
     seq->push_back(op);
@@ -1030,7 +1031,6 @@ struct Block {
 static std::vector<Block> fuse_blocks(const std::vector<SGate> &g, int n, int kmax) {
     std::vector<Block> blocks;
     std::vector<int> last(n, -1);
-    op.wide = P.h.wide;
     for (int i = 0; i < (int)g.size(); i++) {
         const SGate &s = g[i];
         std::vector<int> qs = {s.q0};
@@ -1338,6 +1338,9 @@ static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n
             return q;
         },
         cost, budget, nfixed);
+    if (wide)
+        for (Sweep &sw : sweeps) wide_layout(g, vb, n, &sw);
+    return sweeps;
 }
 
 // The grouping depends on the gates' kinds, forms and qubits only, not on
@@ -1366,9 +1369,19 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
     if (kept->size() >= KEPT) kept->clear();
     (*kept)[std::move(key)] = sw;
     return sw;
-    if (wide)
-        for (Sweep &sw : sweeps) wide_layout(g, vb, n, &sw);
-    return sweeps;
+}
+
+// Register qubits of a tile when the caller names none.  Large states take
+// the widest tile that keeps 3 wavefronts per SIMD; small ones are bound by
+// the time one wavefront needs for its operations (their code comes from
+// beyond the instruction cache), so narrower tiles on more wavefronts finish
+// sooner although they need more sweeps.  Depth-30 circuits, us by width 3, 4,
+// 5 (and 6): complex64 16 qubits 53, 60, 74, 104; 20 qubits 88, 88, 103, 139;
+// 22 qubits 181, 141, 139, 166; 25 qubits 1419, 884, 731, 716; complex128 16
+// qubits 62, 71, 91; 20 qubits 105, 111, 132; 22 qubits 231, 185, 194; 25
+// qubits 1679, 1525, 1433.
+static int default_width(int n, int dtype) {
+    return dtype == SV_C64 ? std::max(3, std::min(6, (n - 12) / 2)) : std::max(3, std::min(5, (n - 14) / 2));
 }
 
 std::string plan_key(const sv_circuit *c, const PlanRequest &rq) {
@@ -1397,19 +1410,6 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
     SV_TRY(specialise(c, rq.n, &g));
     plan->n = rq.n;
     plan->dtype = rq.dtype;
-// Register qubits of a tile when the caller names none.  Large states take
-// the widest tile that keeps 3 wavefronts per SIMD; small ones are bound by
-// the time one wavefront needs for its operations (their code comes from
-// beyond the instruction cache), so narrower tiles on more wavefronts finish
-// sooner although they need more sweeps.  Depth-30 circuits, us by width 3, 4,
-// 5 (and 6): complex64 16 qubits 53, 60, 74, 104; 20 qubits 88, 88, 103, 139;
-// 22 qubits 181, 141, 139, 166; 25 qubits 1419, 884, 731, 716; complex128 16
-// qubits 62, 71, 91; 20 qubits 105, 111, 132; 22 qubits 231, 185, 194; 25
-// qubits 1679, 1525, 1433.
-static int default_width(int n, int dtype) {
-    return dtype == SV_C64 ? std::max(3, std::min(6, (n - 12) / 2)) : std::max(3, std::min(5, (n - 14) / 2));
-}
-
     int mode = rq.mode;
     // tile kernels need the 64 lanes of a wavefront plus gathered qubits
     if ((mode == SV_MODE_REGTILE || mode == SV_MODE_FUSED || mode == SV_MODE_TILED) && rq.n < 10)
