@@ -18,7 +18,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsv.so")
 ROOT = os.path.dirname(HERE)
 
-SOURCES = ["api.cpp", "plan.cpp", "emulate.cpp", "sweeps.hip", "reduce.hip", "adjoint.hip", "batch.hip"]
+SOURCES = ["api.cpp", "plan.cpp", "emulate.cpp", "sweeps.hip", "reduce.hip", "cycles.hip",
+           "adjoint.hip", "batch.hip"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -53,7 +54,7 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build(jobs: int = 6) -> str:
+def build(jobs: int = 8) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -505,16 +505,27 @@ sv_status sv_cycle_moments(sv_state *st, const sv_circuit *c, const sv_opts *opt
     if (ncycles) *ncycles = nc;
     if (cap < nc) return fail(SV_ERANGE, "per-cycle statistics: cap is smaller than the number of cycles");
     int64_t nrows = 0;
-    for (const Op &op : plan->ops) nrows += op.type == OP_STATS;
-    SV_TRY(st->ws.reserve((size_t)(2048 + nrows) * 16 * sizeof(double)));
-    double *part = (double *)st->ws.ptr;
-    double *res = part + (size_t)2048 * 16;
+    for (const Op &op : plan->ops) nrows += op.type == OP_STATS || op.stat >= 0;
+    // partial rows of every point, combined by one launch at the end
+    const size_t stride = (size_t)STATS_BLOCKS * 16;
+    const size_t cnt = ((size_t)nrows * sizeof(int) + 255) & ~(size_t)255;
+    SV_TRY(st->ws.reserve(cnt + ((size_t)nrows * stride + (size_t)nrows * 16) * sizeof(double)));
+    int *dev_rows = (int *)st->ws.ptr;
+    double *part = (double *)((uint8_t *)st->ws.ptr + cnt);
+    double *res = part + (size_t)nrows * stride;
+    std::vector<int> counts((size_t)nrows, 0);
     st->ck_key.clear();
     for (const Op &op : plan->ops) {
-        if (op.type == OP_STATS) SV_TRY(batch_stats_enqueue(st, part, res + (size_t)16 * op.q0));
-        else SV_TRY(launch_op(st, *plan, op, st->data));
+        if (op.type == OP_STATS)
+            SV_TRY(stats_rows_enqueue(st, part + stride * (size_t)op.q0, &counts[(size_t)op.q0]));
+        else if (op.stat >= 0)
+            SV_TRY(launch_stat_sweep(st, *plan, op, part + stride * (size_t)op.stat, &counts[(size_t)op.stat]));
+        else
+            SV_TRY(launch_op(st, *plan, op, st->data));
     }
     st->known_zero = false;
+    SV_HIP(hipMemcpyAsync(dev_rows, counts.data(), counts.size() * sizeof(int), hipMemcpyHostToDevice, st->stream));
+    SV_TRY(combine_lists_enqueue(st, part, stride, dev_rows, nrows, res));
     std::vector<double> host((size_t)nrows * 16);
     SV_HIP(hipMemcpyAsync(host.data(), res, host.size() * sizeof(double), hipMemcpyDeviceToHost, st->stream));
     SV_HIP(hipStreamSynchronize(st->stream));

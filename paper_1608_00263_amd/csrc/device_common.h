@@ -590,6 +590,11 @@ __device__ __forceinline__ void xchg_step(cplx<T> (&a)[1 << VB], T *lds, int lan
     base = tbase | (wave & 1 ? wb0 : 0ull) | (wave & 2 ? wb1 : 0ull);
 }
 
+// What a sweep does with the stored tile while it is in registers.
+struct NoAfter {
+    template <typename T, int NR> __device__ __forceinline__ void operator()(const cplx<T> (&)[NR]) const {}
+};
+
 // One register tile of a sweep: tile index `tile` of the program at prog,
 // processed by the calling wavefront (lane = its lane id).  ck, when not
 // null, receives a second copy of the stored tile (a checkpoint of the
@@ -597,10 +602,10 @@ __device__ __forceinline__ void xchg_step(cplx<T> (&a)[1 << VB], T *lds, int lan
 // WIDE: the tile spans the four wavefronts of the workgroup (two more
 // gathered qubits, on the wave bits); every wavefront of the workgroup calls
 // with the same tile, and lds holds XCHG_WORDS<VB> words.
-template <typename T, int VB, bool WIDE = false>
+template <typename T, int VB, bool WIDE = false, typename After = NoAfter>
 __device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog,
                                               uint64_t tile, int lane, cplx<T> *__restrict__ ck = nullptr,
-                                              int wave = 0, T *lds = nullptr) {
+                                              int wave = 0, T *lds = nullptr, After after = After()) {
     constexpr int NR = 1 << VB;
     const cptr<RTHeader> h = (cptr<RTHeader>)prog;
     uint64_t bq[VB];
@@ -744,6 +749,7 @@ __device__ __forceinline__ void regtile_apply(cplx<T> *__restrict__ psi, const u
 #pragma unroll
         for (int r = 0; r < NR; r++) gstore<T>(uniform_ptr(ck + (base + reg_offset<VB>(bq, r))) + loff, a[r]);
     }
+    after(a);
 }
 
 

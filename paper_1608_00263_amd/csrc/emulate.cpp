@@ -361,7 +361,7 @@ extern "C" sv_status sv_host_cycle_emulate(const sv_circuit *c, sv_dtype dt, con
     Plan plan;
     SV_TRY(build_cycle_plan(c, rq, &plan));
     int64_t rows = 0;
-    for (const Op &op : plan.ops) rows += op.type == OP_STATS;
+    for (const Op &op : plan.ops) rows += op.type == OP_STATS || op.stat >= 0;
     if (nrows) *nrows = rows;
     if (ncycles) *ncycles = (int64_t)plan.cycle_row.size();
     if (cap_rows < rows || cap_cycles < (int64_t)plan.cycle_row.size())
@@ -375,6 +375,8 @@ extern "C" sv_status sv_host_cycle_emulate(const sv_circuit *c, sv_dtype dt, con
             continue;
         }
         emulate_op(plan, op, c->n, psi.data());
+        if (op.stat >= 0 && probs)
+            for (uint64_t i = 0; i < N; i++) probs[(uint64_t)op.stat * N + i] = std::norm(psi[i]);
     }
     if (cycle_row)
         for (size_t t = 0; t < plan.cycle_row.size(); t++) cycle_row[t] = plan.cycle_row[t];

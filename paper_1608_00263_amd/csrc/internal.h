@@ -236,6 +236,8 @@ struct Op {
     int32_t vbits = 0;      // REGTILE: register qubits; LDSTILE: tile bits
     size_t prog_off = 0;    // byte offset in the plan's program buffer
     double bytes = 0;       // algorithmic HBM bytes of this sweep
+    int32_t stat = -1;      // REGTILE of a per-cycle plan: the sweep also sums the
+                            // statistics of the stored state into this row
     int32_t wide = 0;       // REGTILE: tiles of four wavefronts
     int32_t mfma = 0;       // LDSTILE program uses matrix-core blocks
     // LDSTILE: q1 = the widest block, q0 = 1 when every block of 4 or 5
@@ -365,8 +367,18 @@ sv_status upload_plan(sv_state *st, Plan *plan);
 sv_status run_probs(sv_state *st, uint64_t begin, uint64_t count, int f64, void *out);
 sv_status run_stats(sv_state *st, const void *psi, sv_stats *out);
 // statistics pass of st's state into res[0..14) without synchronising; part
-// holds up to 2048 partial rows of 16 doubles
+// holds up to STATS_BLOCKS partial rows of 16 doubles
+constexpr uint64_t STATS_BLOCKS = 2048;
 sv_status batch_stats_enqueue(sv_state *st, double *part, double *res);
+// the partial rows only; their number into nrows
+sv_status stats_rows_enqueue(sv_state *st, double *part, int *nrows);
+// a register-tile sweep that also writes the partial rows of the statistics of
+// the state it stores (cycles.hip)
+sv_status launch_stat_sweep(sv_state *st, const Plan &plan, const Op &op, double *part, int *nrows);
+// combines count lists of partial rows (list i: part + i * stride rows of 16
+// doubles, rows[i] of them, device memory) into res + 16 i
+sv_status combine_lists_enqueue(sv_state *st, const double *part, size_t stride, const int *dev_rows, int64_t count,
+                                double *res);
 // the normalised statistics from the 14 combined sums of a 2^n state
 void finish_stats_row(int n, const double *r, sv_stats *out);
 sv_status run_norm(sv_state *st, const void *psi, double *S);

@@ -287,6 +287,9 @@ static size_t push_bytes(std::vector<uint8_t> *buf, const void *p, size_t bytes)
 // ---------------------------------------------------------------------------
 static uint64_t bit64(int q) { return (uint64_t)1 << q; }
 
+// Smallest state whose per-cycle sweeps form the statistics themselves.
+constexpr int STAT_SWEEP_MIN_QUBITS = 18;
+
 struct Sweep {
     std::vector<int> tile;     // gathered qubits (>= LANE_BITS), ascending
     std::vector<int> items;    // indices into the gate / block list, in order
@@ -1573,7 +1576,12 @@ sv_status build_cycle_plan(const sv_circuit *c, const PlanRequest &rq, Plan *pla
     // before t
     int nrows = 0;
     std::vector<int> row_at(D + 1, -1);
-    auto stats = [&](int first_cycle) {
+    auto stats = [&](int first_cycle, bool in_sweep = false) {
+        if (in_sweep) {   // the last sweep sums them while it holds the state
+            plan->ops.back().stat = nrows;
+            row_at[first_cycle] = nrows++;
+            return;
+        }
         Op op;
         op.type = OP_STATS;
         op.q0 = nrows;
@@ -1583,6 +1591,7 @@ sv_status build_cycle_plan(const sv_circuit *c, const PlanRequest &rq, Plan *pla
     };
     if (segs.empty() || segs[0].cycle > 0) stats(0);
     for (const Seg &sg : segs) {
+        bool in_sweep = false;
         if (mode == SV_MODE_REGTILE) {
             int vb = rq.tile > 0 ? rq.tile : (rq.dtype == SV_C64 ? 6 : 5);
             vb = std::max(1, std::min(vb, rq.dtype == SV_C64 ? 6 : 5));
@@ -1593,12 +1602,16 @@ sv_status build_cycle_plan(const sv_circuit *c, const PlanRequest &rq, Plan *pla
             // the sqrt2 powers of the add-only forms are settled within the
             // segment, so every statistics point sees the true norm
             assign_scales(plan, scales);
+            // complex128 only: the complex64 tile and the sums leave 2 wavefronts
+            // per SIMD (30 qubits: 279 ms a series against 192 with passes of
+            // their own); small states have too few tiles for the sums
+            in_sweep = !sweeps.empty() && rq.dtype == SV_C128 && rq.n >= STAT_SWEEP_MIN_QUBITS;
         } else {
             PlanRequest r2 = rq;
             r2.mode = mode;
             plan_per_gate(c, sg.items, r2, plan);
         }
-        stats(sg.cycle);
+        stats(sg.cycle, in_sweep);
     }
     plan->cycle_row.assign(D + 1, 0);
     int cur = 0;

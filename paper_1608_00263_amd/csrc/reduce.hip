@@ -110,7 +110,6 @@ __global__ __launch_bounds__(CMB_THREADS) void k_combine(const double *__restric
     combine_rows_wg(part, nblocks, nq, out, red);
 }
 
-constexpr uint64_t STATS_BLOCKS = 2048;
 static void stats_grid(int n, int *nblocks, uint64_t *chunk) {
     const uint64_t N = 1ull << n;
     // four amplitudes per thread at least; 2^21 amplitudes fill the chip's
@@ -169,18 +168,39 @@ sv_status run_stats(sv_state *st, const void *psi, sv_stats *out) {
 
 // Enqueue the statistics pass of st into res[0..14) without synchronising
 // (used inside captured graphs); part holds up to 2048 partial rows.
-sv_status batch_stats_enqueue(sv_state *st, double *part, double *res) {
-    int nb;
+sv_status stats_rows_enqueue(sv_state *st, double *part, int *nrows) {
     uint64_t chunk;
-    stats_grid(st->n, &nb, &chunk);
+    stats_grid(st->n, nrows, &chunk);
     if (st->dt == SV_C64)
-        hipLaunchKernelGGL((k_stats<float, true>), dim3(nb), dim3(RB), 0, st->stream,
+        hipLaunchKernelGGL((k_stats<float, true>), dim3(*nrows), dim3(RB), 0, st->stream,
                            (const cpx<float> *)st->data, chunk, std::ldexp(1.0, st->n), part);
     else
-        hipLaunchKernelGGL((k_stats<double, true>), dim3(nb), dim3(RB), 0, st->stream,
+        hipLaunchKernelGGL((k_stats<double, true>), dim3(*nrows), dim3(RB), 0, st->stream,
                            (const cpx<double> *)st->data, chunk, std::ldexp(1.0, st->n), part);
     SV_HIP(hipGetLastError());
+    return SV_OK;
+}
+
+sv_status batch_stats_enqueue(sv_state *st, double *part, double *res) {
+    int nb;
+    SV_TRY(stats_rows_enqueue(st, part, &nb));
     hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, nb, NSTAT + 1, res);
+    SV_HIP(hipGetLastError());
+    return SV_OK;
+}
+
+__global__ __launch_bounds__(CMB_THREADS) void k_combine_lists(const double *__restrict__ part, size_t stride,
+                                                               const int *__restrict__ rows,
+                                                               double *__restrict__ res) {
+    __shared__ double red[2 * 64 * 16];
+    combine_rows_wg(part + stride * blockIdx.x, rows[blockIdx.x], NSTAT + 1, res + 16 * (uint64_t)blockIdx.x, red);
+}
+
+sv_status combine_lists_enqueue(sv_state *st, const double *part, size_t stride, const int *dev_rows, int64_t count,
+                                double *res) {
+    if (count == 0) return SV_OK;
+    hipLaunchKernelGGL(k_combine_lists, dim3((unsigned)count), dim3(CMB_THREADS), 0, st->stream, part, stride,
+                       dev_rows, res);
     SV_HIP(hipGetLastError());
     return SV_OK;
 }

@@ -169,3 +169,21 @@ def test_pair_histogram_slots(n, nbins, zmin, zmax, dtype):
     for k, v in want.items():
         for got in (d[k], d0[k]):
             assert (np.isnan(v) and np.isnan(got)) or got == v or abs(got - v) <= 1e-11 * max(1.0, abs(v)), k
+
+
+@pytest.mark.parametrize("rows,cols,tile", [(3, 6, 1), (3, 6, 2), (3, 6, 3), (3, 6, 4), (3, 6, 5), (1, 19, 5), (4, 5, 4),
+                                            (2, 10, 0)])
+def test_cycle_statistics_formed_in_the_sweeps(rows, cols, tile):
+    # complex128 from 18 qubits up: one to many tiles per wavefront
+    circ = C.make_circuit(rows, cols, 14, seed=23)
+    st = sv.State(circ.n, "c128")
+    got = st.cycle_moments(circ, "regtile", tile)
+    psi = st.amplitudes()
+    st.close()
+    want = oracle.cycle_stats(circ)
+    assert np.linalg.norm(psi - oracle.apply_circuit(circ)) <= 1e-11
+    assert len(got) == len(want)
+    for g, w in zip(got, want):
+        # the bound of the per-cycle parity tests on the state's own error
+        assert abs(g["norm"] - w["norm"]) <= 1e-11 and abs(g["entropy"] - w["entropy"]) <= 1e-9
+        np.testing.assert_allclose(g["moments"], w["moments"], rtol=1e-9)
