@@ -56,8 +56,9 @@ struct BRound {                         // one (instance, sweep) run of items
     int32_t vb;                         // register qubits; 0 for statistics
     int32_t need;                       // items of the instance that precede it
     int32_t nitems;
-    int32_t tpi;                        // register tiles per item (multiple of 4)
-    int32_t pad;
+    int32_t tpi;                        // register tiles per item (multiple of 4
+                                        // for tiles of one wavefront)
+    int32_t wide;                       // tiles of four wavefronts
 };
 
 struct BInst {
@@ -81,9 +82,19 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 
 // One item: up to R.tpi register tiles (R.tpi / 4 per wave), or one
 // statistics chunk written as a partial row of the instance.
+// xlds: the exchange words of wide tiles.
 template <int VB>
 __device__ __forceinline__ void run_item(const BRound &R, const BInst &I, uint64_t chunk, int lane, int wave,
-                                         double *red, unsigned long long *zred, LnEntry *tab) {
+                                         double *red, unsigned long long *zred, LnEntry *tab, float *xlds) {
+    if (R.wide) {
+#pragma unroll 1
+        for (int i = 0; i < R.tpi; i++) {
+            const uint64_t tile = chunk * (uint64_t)R.tpi + i;
+            if (tile >= R.ntiles) break;   // the same for every wavefront
+            regtile_apply<float, VB, true>(I.psi, R.prog, tile, lane, nullptr, wave, xlds);
+        }
+        return;
+    }
     if (R.vb > 0) {
 #pragma unroll 1
         for (int i = 0; i < R.tpi / 4; i++) {
@@ -140,7 +151,10 @@ __device__ __forceinline__ double combine_rows(const BInst &I, int q) {
     return sum + c;
 }
 
-// Round schedule: items [item0, item0 + gridDim.x), one per workgroup.  The
+// Round schedule: items [item0, item0 + gridDim.x), one per workgroup.  Each
+// tile of four wavefronts is an item (4 an item: 16 instances of 15 to 25 qubits
+// 6.81 ms against 6.67, two instances 0.89 against 0.72; all sweeps on tiles of
+// one wavefront 7.83 and 0.97).  The
 // launch bound keeps the 6-qubit tiles at 3 wavefronts per SIMD (168
 // registers; at 169 and 2 wavefronts an ensemble of 16 took 8.9 ms instead of
 // 8.0) and narrower ones at 4.
@@ -151,12 +165,13 @@ __global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_round(const BR
     __shared__ double red[4 * NSTAT];
     __shared__ unsigned long long zred[4];
     __shared__ LnEntry tab[LN_BINS];
+    __shared__ float xlds[XCHG_WORDS<VB>];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t item = item0 + blockIdx.x;
     const BRound &R = rounds[item_round[item]];
     const BInst I = insts[R.inst];
-    run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab);
+    run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab, xlds);
 }
 
 // One workgroup per instance.  (One thread per quantity walking the rows took
@@ -170,7 +185,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_batch_combine(const BInst *__re
 
 // Persistent schedule.
 template <int VB>
-__global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_persistent(const BRound *__restrict__ rounds,
+__global__ __launch_bounds__(BLOCK) void k_batch_persistent(const BRound *__restrict__ rounds,
                                                             const uint32_t *__restrict__ item_round,
                                                             uint64_t total, const BInst *__restrict__ insts,
                                                             unsigned long long *head, unsigned *err,
@@ -181,6 +196,7 @@ __global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_persistent(con
     __shared__ double red[4 * NSTAT];
     __shared__ unsigned long long zred[4];
     __shared__ LnEntry tab[LN_BINS];
+    __shared__ float xlds[XCHG_WORDS<VB>];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (;;) {
@@ -210,7 +226,7 @@ __global__ __launch_bounds__(BLOCK, VB == 6 ? 3 : 4) void k_batch_persistent(con
         __threadfence();   // acquire for every wave of the workgroup
         if (!__builtin_amdgcn_readfirstlane(s_flag)) continue;   // item given up (error raised)
         const BInst I = insts[inst];
-        run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab);
+        run_item<VB>(R, I, item - R.first, lane, wave, red, zred, tab, xlds);
         __threadfence();   // release this item's writes
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -300,8 +316,10 @@ static sv_status build_ensemble(sv_state **sts, const std::vector<std::shared_pt
                 const Op &op = p.ops[r];
                 R.vb = op.vbits;
                 R.prog = (const uint8_t *)p.dprog + op.prog_off;
-                R.ntiles = (1ull << sts[i]->n) >> (LANE_BITS + op.vbits);
-                R.nitems = (int32_t)((R.ntiles + tpi - 1) / tpi);
+                R.wide = op.wide;
+                R.ntiles = (1ull << sts[i]->n) >> (LANE_BITS + op.vbits + (op.wide ? 2 : 0));
+                if (op.wide) R.tpi = persistent ? tpi / 4 : 1;
+                R.nitems = (int32_t)((R.ntiles + R.tpi - 1) / R.tpi);
             } else if (r == p.ops.size()) {
                 R.vb = 0;
                 R.prog = nullptr;
@@ -437,7 +455,6 @@ extern "C" sv_status sv_apply_batch(sv_state **sts, const sv_circuit *cs, int64_
             rq.tile = vb;
             rq.from_zero = true;
             rq.force_zero = true;
-            rq.narrow = true;
             SV_TRY(get_plan(sts[i], &cs[i], rq, &plans[i]));
             for (const Op &op : plans[i]->ops)
                 if (op.type != OP_REGTILE || op.vbits != vb) {

@@ -59,7 +59,8 @@ struct TileStats {
 // and one row of partial sums per workgroup.  The statistics take about 45
 // VALU issues per amplitude, which the sweep's memory time covers (a per-cycle
 // sweep has few gates): 24 qubits complex128 one point took 87 us for the
-// sweep and 47 us for a pass of its own over the state.
+// sweep and 47 us for a pass of its own over the state; the series of 39 points
+// went from 5.73 to 5.14 ms, that of 28 qubits from 89.8 to 74.1.
 template <typename T, int VB>
 __global__ __launch_bounds__(BLOCK, 3) void k_regtile_stats(
     cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog, uint64_t ntiles, double Nd,

@@ -287,7 +287,6 @@ struct PlanRequest {
                          // replaced by the uniform initialisation
     bool force_zero;     // the plan must itself start from |0..0>
     bool no_mfma;        // k >= 4 blocks on the VALU
-    bool narrow;         // REGTILE: tiles of one wavefront only (ensembles)
 };
 
 // Validate the circuit and produce the specialised gate list in order.

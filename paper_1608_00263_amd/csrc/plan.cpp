@@ -1445,7 +1445,7 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         // 28 qubits complex128 10 in 17.0 ms against 14 in 22.2.  With equal
         // counts the exchanges only cost (12 qubits complex128, 3 register
         // qubits: 44.7 against 40.9 us).
-        if (!rq.narrow && vb >= 2 && rq.n >= vb + LANE_BITS + 2) {
+        if (vb >= 2 && rq.n >= vb + LANE_BITS + 2) {
             auto w = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true, true);
             if (!w.empty() && w.size() < sweeps.size()) sweeps.swap(w);
         }

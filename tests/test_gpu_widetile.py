@@ -31,3 +31,24 @@ def test_wide_tiles_match_reference(n, tile, dtype):
         st.apply(chain, "regtile", 0, tile, from_zero=True, budget=budget)
         assert np.linalg.norm(st.amplitudes() - want_c) <= tol, budget
         st.close()
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+@pytest.mark.parametrize("tile", [3, 4, 6])
+def test_ensembles_of_wide_and_narrow_plans(tile, persistent):
+    # one tile per state up to several per item; a depth of 3 needs one sweep
+    # and stays on tiles of one wavefront, in the same launches
+    shapes = [(2, 7, 30), (4, 4, 20), (3, 6, 24), (4, 5, 20), (3, 5, 3)]
+    circs = [C.make_circuit(r, c, d, seed=700 + i) for i, (r, c, d) in enumerate(shapes)]
+    states = [sv.State(c.n, "c64") for c in circs]
+    for _ in range(2):   # built and replayed
+        res = sv.apply_batch(states, circs, mode="regtile", tile=tile, persistent=persistent)
+        for c, st, r in zip(circs, states, res):
+            ref = oracle.apply_circuit(c)
+            want = oracle.stats(oracle.probs(ref))
+            # the bounds of the ensembles' parity tests
+            assert np.linalg.norm(st.amplitudes() - ref) <= 1e-4
+            assert abs(r["entropy"] - want["entropy"]) < 1e-4
+            assert abs(r["norm"] - 1.0) < 1e-5
+    for st in states:
+        st.close()
