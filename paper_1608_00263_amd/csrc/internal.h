@@ -320,6 +320,21 @@ struct Workspace {
     ~Workspace();
 };
 
+// Pinned host memory that the last kernel of a synchronous call writes its
+// result block to, instead of a copy from device memory after it (a launch of
+// its own and 6-8 us of a call of 40).  A process-wide block of 16 slots of
+// 4 KB, allocated once for all devices and kept until the process ends; ptr is
+// null when the result is larger, every slot is taken or there is no pinned
+// memory, and the call copies.  release() after the stream was waited for: a
+// call that fails before that leaves its slot out, as its kernel may still
+// write to it.
+struct ResultSlot {
+    static constexpr int COUNT = 16, BYTES = 4096;
+    void *ptr = nullptr;
+    explicit ResultSlot(size_t need);
+    void release();
+};
+
 }  // namespace svi
 
 namespace svi {

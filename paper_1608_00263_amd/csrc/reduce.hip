@@ -121,6 +121,18 @@ static void stats_grid(int n, int *nblocks, uint64_t *chunk) {
     *chunk = N / nb;
 }
 
+// Waits for the stream; the result block res (the slot's, or device memory) is
+// then in dst.
+static sv_status fetch_result(ResultSlot &slot, void *dst, const void *res, size_t bytes, hipStream_t s) {
+    if (!slot.ptr) SV_HIP(hipMemcpyAsync(dst, res, bytes, hipMemcpyDeviceToHost, s));
+    SV_HIP(hipStreamSynchronize(s));
+    if (slot.ptr) {
+        std::memcpy(dst, slot.ptr, bytes);
+        slot.release();
+    }
+    return SV_OK;
+}
+
 template <typename T, bool FULL>
 static sv_status stats_typed(sv_state *st, const void *psi, double *host16) {
     int nb;
@@ -128,14 +140,14 @@ static sv_status stats_typed(sv_state *st, const void *psi, double *host16) {
     stats_grid(st->n, &nb, &chunk);
     SV_TRY(st->ws.reserve((size_t)(nb + 1) * 16 * sizeof(double)));
     double *part = (double *)st->ws.ptr;
-    double *res = part + (size_t)nb * 16;
+    ResultSlot slot(16 * sizeof(double));
+    double *res = slot.ptr ? (double *)slot.ptr : part + (size_t)nb * 16;
     hipLaunchKernelGGL((k_stats<T, FULL>), dim3(nb), dim3(RB), 0, st->stream, (const cpx<T> *)psi,
                        chunk, std::ldexp(1.0, st->n), part);
     SV_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, nb, FULL ? NSTAT + 1 : 1, res);
     SV_HIP(hipGetLastError());
-    SV_HIP(hipMemcpyAsync(host16, res, 16 * sizeof(double), hipMemcpyDeviceToHost, st->stream));
-    SV_HIP(hipStreamSynchronize(st->stream));
+    SV_TRY(fetch_result(slot, host16, res, 16 * sizeof(double), st->stream));
     return SV_OK;
 }
 
@@ -439,11 +451,12 @@ sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, double zmin, doubl
     }
 #undef PAIR_LAUNCH
     SV_HIP(hipGetLastError());
+    std::vector<uint64_t> host((size_t)16 + nwords);
+    ResultSlot slot(host.size() * 8);
+    if (slot.ptr) res = (decltype(res))slot.ptr;
     hipLaunchKernelGGL(k_pair_finish, dim3(1 + hcols / 16), dim3(CMB_THREADS), 0, s, part, rows, hcols, nwords, nb, res);
     SV_HIP(hipGetLastError());
-    std::vector<uint64_t> host((size_t)16 + nwords);
-    SV_HIP(hipMemcpyAsync(host.data(), res, host.size() * 8, hipMemcpyDeviceToHost, s));
-    SV_HIP(hipStreamSynchronize(s));
+    SV_TRY(fetch_result(slot, host.data(), res, host.size() * 8, s));
     std::memcpy(sums16, host.data(), (NPAIR + 1) * sizeof(double));
     if (nwords) std::memcpy(host_hist, host.data() + 16, (size_t)nwords * 8);
     return SV_OK;
@@ -663,16 +676,18 @@ __global__ __launch_bounds__(RB) void k_pass(const S *__restrict__ src, uint64_t
 // first sums the chunks of each group (cg = 2^k <= 64 chunks) and forms the
 // exclusive prefix off[0..ng] of the ng = nb / cg groups, the total W and its
 // status (check: from the exact sums of the check rows).  The loads of the
-// chunk sums are coalesced rows, four in flight per wavefront.
+// chunk sums are coalesced rows, four in flight per wavefront.  The status and
+// the statistics go to copy (host memory, or res itself).
 __global__ __launch_bounds__(CMB_THREADS) void k_finish_pass(const unsigned long long *__restrict__ csum, uint64_t nb,
                                                              int cg, const double *__restrict__ part, int nrows,
                                                              int check, unsigned long long *__restrict__ off,
-                                                             PassResult *__restrict__ res) {
+                                                             PassResult *__restrict__ res,
+                                                             PassResult *__restrict__ copy) {
     __shared__ unsigned long long lds[MAX_GROUPS];
     __shared__ unsigned long long wtot[16];
     __shared__ unsigned long long chk[16 * 5];
     if (blockIdx.x == 1) {
-        combine_rows_wg(part, nrows, NSTAT + 1, res->stats, (double *)lds);
+        combine_rows_wg(part, nrows, NSTAT + 1, copy->stats, (double *)lds);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -738,6 +753,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_finish_pass(const unsigned long
         off[ng] = W;
         res->W = W;
         res->status = status;
+        if (copy != res) copy->status = status;
     }
 }
 
@@ -907,7 +923,7 @@ static SampleLayout sample_layout(int n) {
 // src holds N = 2^n entries, or (explicit distributions, which are checked)
 // any N in (2^{n-1}, 2^n], the entries beyond N counting as weight 0.
 // host_out, when not null, receives a copy of the samples.  Synchronises: one
-// wait at the end, after the copies of the result block and the samples.
+// wait at the end, for the result block and the samples.
 template <typename S>
 static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *src, int n, const uint64_t *words,
                              uint64_t seed, int64_t k, uint64_t *dev_out, uint64_t *host_out,
@@ -924,6 +940,7 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
     auto *sub = (unsigned long long *)(w + L.o_sub);
     double *part = (double *)(w + L.o_part);
     auto *res = (PassResult *)(w + L.o_res);
+    ResultSlot slot(scr.fixed ? SIZE_MAX : sizeof(PassResult));   // the no-allocation call copies
     const double Nd = std::ldexp(1.0, n);
     if constexpr (!CHECK) {
         if (stats16)
@@ -937,7 +954,7 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
                            part, csum, sub);
     }
     hipLaunchKernelGGL(k_finish_pass, dim3(stats16 ? 2 : 1), dim3(CMB_THREADS), 0, s, csum, L.nb, L.cg, part,
-                       stats16 ? L.blocks : 0, CHECK ? L.blocks : 0, off, res);
+                       stats16 ? L.blocks : 0, CHECK ? L.blocks : 0, off, res, slot.ptr ? (PassResult *)slot.ptr : res);
     SV_HIP(hipGetLastError());
     if (k > 0) {
         const unsigned rg = (unsigned)((k + RB / 64 - 1) / (RB / 64));
@@ -951,9 +968,8 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
         SV_HIP(hipGetLastError());
     }
     PassResult host;
-    SV_HIP(hipMemcpyAsync(&host, res, sizeof host, hipMemcpyDeviceToHost, s));
     if (k > 0 && host_out) SV_HIP(hipMemcpyAsync(host_out, dev_out, (size_t)k * 8, hipMemcpyDeviceToHost, s));
-    SV_HIP(hipStreamSynchronize(s));
+    SV_TRY(fetch_result(slot, &host, res, sizeof host, s));
     if (stats16)
         for (int i = 0; i < 16; i++) stats16[i] = i <= NSTAT ? host.stats[i] : 0.0;
     if (host.status == PASS_BAD)
@@ -1100,7 +1116,8 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
     const int64_t nb = (k + per - 1) / per;
     SV_TRY(st->ws.reserve((size_t)(nb + 1) * 16 * sizeof(double)));
     double *part = (double *)st->ws.ptr;
-    double *res = part + (size_t)nb * 16;
+    ResultSlot slot(2 * sizeof(double));
+    double *res = slot.ptr ? (double *)slot.ptr : part + (size_t)nb * 16;
     if (st->dt == SV_C64)
         hipLaunchKernelGGL(k_ce<float>, dim3((unsigned)nb), dim3(RB), 0, st->stream,
                            (const cpx<float> *)psi, dev_samples, k, per, part);
@@ -1109,9 +1126,9 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
                            (const cpx<double> *)psi, dev_samples, k, per, part);
     SV_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_combine, dim3(1), dim3(CMB_THREADS), 0, st->stream, part, (int)nb, 2, res);
+    SV_HIP(hipGetLastError());
     double r[2];
-    SV_HIP(hipMemcpyAsync(r, res, 2 * sizeof(double), hipMemcpyDeviceToHost, st->stream));
-    SV_HIP(hipStreamSynchronize(st->stream));
+    SV_TRY(fetch_result(slot, r, res, sizeof r, st->stream));
     *sum_log = r[0];
     *zeros = (int64_t)r[1];
     return SV_OK;

@@ -187,3 +187,35 @@ def test_cycle_statistics_formed_in_the_sweeps(rows, cols, tile):
         # the bound of the per-cycle parity tests on the state's own error
         assert abs(g["norm"] - w["norm"]) <= 1e-11 and abs(g["entropy"] - w["entropy"]) <= 1e-9
         np.testing.assert_allclose(g["moments"], w["moments"], rtol=1e-9)
+
+
+@pytest.mark.parametrize("nbins", [163, 164])
+def test_pair_results_at_the_slot_size(nbins):
+    # 505 words fit a 4 KB result slot of 512, 164 bins (514 words) do not
+    n = 12
+    a, b = (C.random_state(n, s, dtype=np.complex128) for s in (3, 4))
+    sa, sb_ = (sv.State(n, "c128", tensor=torch.from_numpy(x).to("cuda")) for x in (a, b))
+    _, h = sv.pair_stats(sa, sb_, nbins, -12.0, 4.0)
+    sa.close()
+    sb_.close()
+    np.testing.assert_array_equal(h, oracle.pair_stats(a, b, nbins, -12.0, 4.0)[1])
+
+
+def test_results_of_more_threads_than_slots():
+    # 24 threads for 16 slots, each on a state of its own: exact repeats
+    from concurrent.futures import ThreadPoolExecutor
+
+    psis = [C.random_state(10, 40 + i, dtype=np.complex128) for i in range(24)]
+    states = [sv.State(10, "c128", tensor=torch.from_numpy(p).to("cuda")) for p in psis]
+    alone = [(st.moments()["entropy"], st.sample(50, 5)) for st in states]
+
+    def work(i):
+        return [(states[i].moments()["entropy"], states[i].sample(50, 5)) for _ in range(20)]
+
+    with ThreadPoolExecutor(24) as ex:
+        for i, rows in enumerate(ex.map(work, range(24))):
+            for e, xs in rows:
+                assert e == alone[i][0]
+                np.testing.assert_array_equal(xs, alone[i][1])
+    for st in states:
+        st.close()
