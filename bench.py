@@ -2,8 +2,8 @@
 
 One step = the whole path over one synthetic input: simulate the 5x6-grid,
 30-qubit, depth-40 random circuit of Sec. IV from |0...0> in complex64
-with register tiles of 6 qubits at sweep budget 160 (the autotuner's usual
-choice here; --mode auto runs its choice, made once before the warm-up, and
+with register tiles of 6 qubits over four wavefronts at sweep budget 160
+(--mode auto runs the autotuner's choice, made once before the warm-up, and
 the circuit_s section times AUTO beside the fixed plans), compute the
 output statistics (entropy,
 uniform cross entropy, moments 1..10), draw 10^5 samples and evaluate
@@ -20,7 +20,7 @@ circuit_s  = seconds of the same circuit per planning mode (plain per-gate,
              specialised per-gate, fused 2^k blocks, LDS tiles, register
              tiles) in complex64 and complex128;
 roofline_c128 = the same for the complex128 register-tile sweep
-             (k_regtile<double,5>) on the same circuit, as the
+             (k_widetile<double,5>) on the same circuit, as the
              autotuner plans it (--c128-budget pins a sweep budget);
 grad       = adjoint gradient time over forward time on the 5x5, depth-30
              parametrised circuit (10^4 samples) for checkpoint intervals;
@@ -44,7 +44,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBPS = 8000.0
 # the library's register-tile sweep budget when the options leave it 0
-DEFAULT_SWEEP_BUDGET = {"c64": 250, "c128": 220}
+DEFAULT_SWEEP_BUDGET = {"c64": 300, "c128": 220}
 PEAK_FP32_MFMA_TFLOPS = 157.3   # dense FP32 matrix peak of the MI355X
 PEAK_FP64_MFMA_TFLOPS = 78.6    # dense FP64 matrix peak of the MI355X
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_regtile_c2_traffic.txt")
@@ -322,7 +322,7 @@ def main():
         "sweep_frac_of_peak": round(sweep_bytes[-1] / (np.mean(sweep_ms) / 1e3) / 1e9 / PEAK_HBM_GBPS, 4),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": measured_traffic(rt_tile, rt_budget),
-                     "kernel": "k_regtile<float,%d>" % rt_tile,
+                     "kernel": "k_widetile<float,%d>" % rt_tile,
                      "launch_avg_ms": round(dom_ms / max(dom_launches, 1), 4),
                      "bytes_per_launch": round(dom_bytes / max(dom_launches, 1), 1),
                      "valu_frac": measured_valu_frac(rt_tile, rt_budget),
@@ -429,7 +429,7 @@ def roofline_c128(sv, C, circ, torch, budget=0, reps=5):
     tb = cbudget or DEFAULT_SWEEP_BUDGET["c128"]
     return {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": measured_traffic(tile, tb, TRAFFIC_FILE_C128),
-            "valu_frac": measured_valu_frac(tile, tb, TRAFFIC_FILE_C128), "kernel": "k_regtile<double,%d>" % tile,
+            "valu_frac": measured_valu_frac(tile, tb, TRAFFIC_FILE_C128), "kernel": "k_widetile<double,%d>" % tile,
             "choice": choice,
             "launches": nl, "launch_avg_ms": round(dom_ms / nl, 4), "bytes_per_launch": round(dom_by / nl, 1),
             "circuit_ms": round(tot, 3), "workload": "5x6 grid, 30 qubits, depth 40, complex128 (16 GiB)"}
