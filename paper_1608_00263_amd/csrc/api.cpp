@@ -3,6 +3,7 @@
 // stream; functions returning host scalars synchronise it.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <limits>
 #include <cstdio>
@@ -535,26 +536,41 @@ sv_status sv_cycle_moments(sv_state *st, const sv_circuit *c, const sv_opts *opt
     if (cap < nc) return fail(SV_ERANGE, "per-cycle statistics: cap is smaller than the number of cycles");
     int64_t nrows = 0;
     for (const Op &op : plan->ops) nrows += op.type == OP_STATS || op.stat >= 0;
-    // partial rows of every point, combined by one launch at the end
+    // Partial rows of up to 64 points (256 KiB each), combined by one launch:
+    // a launch per point took 36 us of a 24-qubit point, and all points at once
+    // would let the workspace grow with the depth.
+    constexpr int64_t WINDOW = 64;
     const size_t stride = (size_t)STATS_BLOCKS * 16;
     const size_t cnt = ((size_t)nrows * sizeof(int) + 255) & ~(size_t)255;
-    SV_TRY(st->ws.reserve(cnt + ((size_t)nrows * stride + (size_t)nrows * 16) * sizeof(double)));
+    const size_t lists = (size_t)std::min(nrows, WINDOW);
+    SV_TRY(st->ws.reserve(cnt + (lists * stride + (size_t)nrows * 16) * sizeof(double)));
     int *dev_rows = (int *)st->ws.ptr;
     double *part = (double *)((uint8_t *)st->ws.ptr + cnt);
-    double *res = part + (size_t)nrows * stride;
+    double *res = part + lists * stride;
     std::vector<int> counts((size_t)nrows, 0);
+    int64_t first = 0, next = 0;   // points [first, next) are in part
+    auto combine = [&]() -> sv_status {
+        if (next == first) return SV_OK;
+        SV_HIP(hipMemcpyAsync(dev_rows + first, &counts[(size_t)first], (size_t)(next - first) * sizeof(int),
+                              hipMemcpyHostToDevice, st->stream));
+        SV_TRY(combine_lists_enqueue(st, part, stride, dev_rows + first, next - first, res + 16 * first));
+        first = next;
+        return SV_OK;
+    };
     st->ck_key.clear();
     for (const Op &op : plan->ops) {
-        if (op.type == OP_STATS)
-            SV_TRY(stats_rows_enqueue(st, part + stride * (size_t)op.q0, &counts[(size_t)op.q0]));
-        else if (op.stat >= 0)
-            SV_TRY(launch_stat_sweep(st, *plan, op, part + stride * (size_t)op.stat, &counts[(size_t)op.stat]));
-        else
+        if (op.type != OP_STATS && op.stat < 0) {
             SV_TRY(launch_op(st, *plan, op, st->data));
+            continue;
+        }
+        if (next - first == WINDOW) SV_TRY(combine());
+        double *list = part + stride * (size_t)(next - first);
+        if (op.type == OP_STATS) SV_TRY(stats_rows_enqueue(st, list, &counts[(size_t)next]));
+        else SV_TRY(launch_stat_sweep(st, *plan, op, list, &counts[(size_t)next]));
+        next++;   // the points come in the order of their rows
     }
     st->known_zero = false;
-    SV_HIP(hipMemcpyAsync(dev_rows, counts.data(), counts.size() * sizeof(int), hipMemcpyHostToDevice, st->stream));
-    SV_TRY(combine_lists_enqueue(st, part, stride, dev_rows, nrows, res));
+    SV_TRY(combine());
     std::vector<double> host((size_t)nrows * 16);
     SV_HIP(hipMemcpyAsync(host.data(), res, host.size() * sizeof(double), hipMemcpyDeviceToHost, st->stream));
     SV_HIP(hipStreamSynchronize(st->stream));

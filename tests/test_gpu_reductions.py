@@ -219,3 +219,19 @@ def test_results_of_more_threads_than_slots():
                 np.testing.assert_array_equal(xs, alone[i][1])
     for st in states:
         st.close()
+
+
+@pytest.mark.parametrize("rows,cols,depth,dtype", [(2, 3, 63, "c128"), (2, 3, 64, "c64"), (2, 3, 150, "c128"),
+                                                   (1, 18, 80, "c128")])
+def test_cycle_series_across_the_combined_lists(rows, cols, depth, dtype):
+    # 64 points are combined at a time: one list less, one full, several
+    circ = C.make_circuit(rows, cols, depth, seed=31)
+    st = sv.State(circ.n, dtype)
+    got = st.cycle_moments(circ, "regtile")
+    st.close()
+    want = oracle.cycle_stats(circ)
+    assert len(got) == len(want)
+    tol = 1e-9 if dtype == "c128" else 1e-4   # the per-cycle parity bounds
+    for g, w in zip(got, want):
+        assert abs(g["entropy"] - w["entropy"]) <= tol
+        np.testing.assert_allclose(g["moments"][:5], w["moments"][:5], rtol=tol if dtype == "c128" else 1e-3)
