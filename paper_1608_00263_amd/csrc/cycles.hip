@@ -22,7 +22,7 @@ struct TileStats {
     int lane;
     template <int NR>
     __device__ __forceinline__ void operator()(const cplx<T> (&a)[NR]) const {
-        constexpr int K = NR < 4 ? NR : 4;
+        constexpr int K = NR < 2 ? NR : 2;
         double p[NR];
 #pragma unroll
         for (int r = 0; r < NR; r++) {
@@ -60,9 +60,11 @@ struct TileStats {
 // VALU issues per amplitude, which the sweep's memory time covers (a per-cycle
 // sweep has few gates): 24 qubits complex128 one point took 87 us for the
 // sweep and 47 us for a pass of its own over the state; the series of 39 points
-// went from 5.73 to 5.14 ms, that of 28 qubits from 89.8 to 74.1.
+// went from 5.73 to 4.54 ms, that of 28 qubits from 89.8 to 69.9.  (With four
+// probabilities at a time and the lane's constants held across the tiles, 62
+// registers spilled at 5 register qubits: 5.11 and 74.1 ms.)
 template <typename T, int VB>
-__global__ __launch_bounds__(BLOCK, 3) void k_regtile_stats(
+__global__ __launch_bounds__(BLOCK, VB == 4 ? 4 : 3) void k_regtile_stats(
     cplx<T> *__restrict__ psi, const uint8_t *__restrict__ prog, uint64_t ntiles, double Nd,
     double *__restrict__ part) {
     __shared__ LnEntry tab[LN_BINS];
@@ -82,8 +84,15 @@ __global__ __launch_bounds__(BLOCK, 3) void k_regtile_stats(
     after.lane = lane;
     const uint64_t stride = (uint64_t)gridDim.x * (BLOCK / 64);
 #pragma unroll 1
-    for (uint64_t tile = (uint64_t)blockIdx.x * (BLOCK / 64) + wave; tile < ntiles; tile += stride)
-        regtile_apply<T, VB>(psi, prog, tile, lane, nullptr, 0, (T *)nullptr, after);
+    for (uint64_t tile = (uint64_t)blockIdx.x * (BLOCK / 64) + wave; tile < ntiles; tile += stride) {
+        // opaque copies: what a tile derives from its lane and program is formed
+        // anew (a few instructions) instead of being held across the loop
+        // beside the tile and the sums
+        const uint8_t *pr = prog;
+        int ln = lane;
+        asm volatile("" : "+s"(pr), "+v"(ln));
+        regtile_apply<T, VB>(psi, pr, tile, ln, nullptr, 0, (T *)nullptr, after);
+    }
     __syncthreads();
     double *row = part + (uint64_t)blockIdx.x * 16;
     if (threadIdx.x < NSTAT) row[threadIdx.x] = (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
@@ -96,11 +105,11 @@ sv_status launch_stat_sweep(sv_state *st, const Plan &plan, const Op &op, double
     const uint8_t *prog = (const uint8_t *)plan.dprog + op.prog_off;
     const uint64_t ntiles = (1ull << st->n) >> (LANE_BITS + op.vbits);
     const uint64_t groups = (ntiles + BLOCK / 64 - 1) / (BLOCK / 64);
-    // as many workgroups as are resident (3 per CU at 168 registers): with more,
-    // the last round of a 28-qubit sweep ran on a fraction of the chip
-    constexpr uint64_t RESIDENT = 768;
-    static_assert(RESIDENT <= STATS_BLOCKS, "a list of partial rows holds STATS_BLOCKS");
-    *nrows = (int)(groups < RESIDENT ? groups : RESIDENT);
+    // as many workgroups as are resident (3 per CU at 168 registers, 4 at 128):
+    // with more, the last round of a 28-qubit sweep ran on a fraction of the chip
+    const uint64_t resident = op.vbits == 4 ? 1024 : 768;
+    static_assert(STATS_BLOCKS >= 1024, "a list of partial rows holds STATS_BLOCKS");
+    *nrows = (int)(groups < resident ? groups : resident);
     const double Nd = std::ldexp(1.0, st->n);
 #define STAT_CASE(VB)                                                                                         \
     case VB:                                                                                                  \
