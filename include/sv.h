@@ -92,7 +92,8 @@ typedef struct {
  *                   0..3 and two gathered ones across the 64 lanes of a
  *                   wavefront, a few gathered qubits in registers, two more
  *                   across the four wavefronts of a workgroup where that saves
- *                   a sweep), diagonal gates folded;
+ *                   a sweep, except for complex64 circuits with rotation
+ *                   offsets), diagonal gates folded;
  *  SV_MODE_AUTO     time candidate plans once per circuit shape and keep
  *                   the fastest (autotuner; results cached per process). */
 enum {

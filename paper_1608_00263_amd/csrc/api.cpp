@@ -131,7 +131,7 @@ static void keep_choice(const std::string &key, const sv_opts &o) {
     g_tuned[key] = o;
 }
 
-static std::vector<sv_opts> tune_candidates(const sv_state *st) {
+static std::vector<sv_opts> tune_candidates(const sv_state *st, const sv_circuit *circ) {
     std::vector<sv_opts> c;
     auto add = [&](int mode, int k, int t, int budget = 0) { c.push_back(sv_opts{mode, k, t, 0, budget, 0}); };
     if (st->n >= 10) {
@@ -141,9 +141,10 @@ static std::vector<sv_opts> tune_candidates(const sv_state *st) {
         // is faster depends on the circuit: at 30 qubits complex64 three
         // circuits took 35.2, 37.2, 37.5 ms at 160 and 36.1, 35.8, 35.6 at the
         // default)
-        const int wmax = st->n > 20 ? (st->dt == SV_C64 ? 6 : 5) : (st->dt == SV_C64 ? 5 : 4);
+        const bool large = st->n > 20 || keeps_rounding(circ, st->dt);
+        const int wmax = large ? (st->dt == SV_C64 ? 6 : 5) : (st->dt == SV_C64 ? 5 : 4);
         for (int w = wmax - 2; w <= wmax; w++) add(SV_MODE_REGTILE, 0, w);
-        if (st->n > 20) add(SV_MODE_REGTILE, 0, wmax, st->dt == SV_C64 ? 160 : 140);
+        if (large) add(SV_MODE_REGTILE, 0, wmax, st->dt == SV_C64 ? 160 : 140);
         add(SV_MODE_FUSED, 2, 0);
         add(SV_MODE_FUSED, 3, 0);
         // complex64 LDS tiles of dense 8x8 blocks are bound by the FP32 VALU
@@ -205,7 +206,7 @@ static sv_status resolve_auto(sv_state *st, const sv_circuit *c, bool from_zero,
     *explore = -1;
     const std::string key = tune_key(st, c, from_zero);
     if (tuned_choice(key, out)) return SV_OK;
-    std::vector<sv_opts> cand = tune_candidates(st);
+    std::vector<sv_opts> cand = tune_candidates(st, c);
     if (cand.size() == 1) { keep_choice(key, cand[0]); *out = cand[0]; return SV_OK; }
     const size_t bytes = (size_t)state_bytes(st->n, st->dt);
     size_t freeb = 0, total = 0;

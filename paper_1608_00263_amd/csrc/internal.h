@@ -421,5 +421,8 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
                             int64_t k, double S, double *sum_log, int64_t *zeros);
 
 std::string plan_key(const sv_circuit *c, const PlanRequest &rq);
+// true where register-tile plans stay on tiles of one wavefront so that results
+// keep their rounding (complex64 circuits with rotation offsets)
+bool keeps_rounding(const sv_circuit *c, int dtype);
 
 }  // namespace svi

@@ -1374,6 +1374,21 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
     return sw;
 }
 
+// Circuits with rotation offsets in complex64 run on tiles of one wavefront at
+// the widths 4 to 6, also where wide tiles are faster.  A training step divides
+// by p(x) of its samples, so the gradient magnifies the rounding of the output
+// state by sqrt(sum 1/z^2 / sum 1/z), z = N p(x) (8 to 50 at 25 qubits), and
+// two plans that round in another order differ by that much: up to 1.1e-5 over
+// six data sets of a 25-qubit, depth-30 circuit, 6.9e-5 on another.  Against
+// FP64 the six gradients are off by 1.9e-6 to 9.1e-6 on these plans and by
+// 1.8e-6 to 1.0e-5 after a forward on wide tiles (worse in four of them).
+bool keeps_rounding(const sv_circuit *c, int dtype) {
+    if (dtype != SV_C64) return false;
+    for (int64_t i = 0; i < c->ngates; i++)
+        if (c->gates[i].param >= 0) return true;
+    return false;
+}
+
 // Register qubits of a tile when the caller names none.  Large states take
 // the widest tile that keeps 3 wavefronts per SIMD; small ones are bound by
 // the time one wavefront needs for its operations (their code comes from
@@ -1383,7 +1398,8 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
 // 22 qubits 181, 141, 139, 166; 25 qubits 1419, 884, 731, 716; complex128 16
 // qubits 62, 71, 91; 20 qubits 105, 111, 132; 22 qubits 231, 185, 194; 25
 // qubits 1679, 1525, 1433.
-static int default_width(int n, int dtype) {
+static int default_width(int n, int dtype, bool keep_rounding) {
+    if (keep_rounding) return 6;
     return dtype == SV_C64 ? std::max(3, std::min(6, (n - 12) / 2)) : std::max(3, std::min(5, (n - 14) / 2));
 }
 
@@ -1435,7 +1451,8 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         plan_per_gate(c, g, r2, plan);
     } else if (mode == SV_MODE_REGTILE) {
         fold_diagonals(&g, rq.n, false, true);
-        int vb = rq.tile > 0 ? rq.tile : default_width(rq.n, rq.dtype);
+        const bool keep = keeps_rounding(c, rq.dtype);
+        int vb = rq.tile > 0 ? rq.tile : default_width(rq.n, rq.dtype, keep);
         vb = std::max(1, std::min(vb, rq.dtype == SV_C64 ? 6 : 5));
         vb = std::min(vb, rq.n - LANE_BITS);
         const double budget = rq.budget > 0 ? (double)rq.budget : -1.0;
@@ -1445,7 +1462,7 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         // 28 qubits complex128 10 in 17.0 ms against 14 in 22.2.  With equal
         // counts the exchanges only cost (12 qubits complex128, 3 register
         // qubits: 44.7 against 40.9 us).
-        if (vb >= 2 && rq.n >= vb + LANE_BITS + 2) {
+        if (vb >= 2 && rq.n >= vb + LANE_BITS + 2 && !keep) {
             auto w = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true, true);
             if (!w.empty() && w.size() < sweeps.size()) sweeps.swap(w);
         }
