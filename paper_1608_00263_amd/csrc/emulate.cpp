@@ -1,5 +1,6 @@
 // Host replay of sweep plans (include/sv_host.h): interprets the tile
-// programs byte for byte as the GPU kernels do, in double precision.
+// programs byte for byte as the GPU kernels do, in double precision (with the
+// range of FP32 for complex64).
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -36,6 +37,19 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
     std::vector<cx> all((size_t)nw * 64 * nr);
     const bool f32 = plan.dtype == SV_C64;
     auto rnd = [&](cx v) { return f32 ? cx((float)v.real(), (float)v.imag()) : v; };
+    // complex64: what leaves the range of FP32 is lost as on the GPU (infinite,
+    // or zero), without its rounding
+    auto held = [&](double v) {
+        const double m = std::fabs(v);
+        if (m >= 3.4028235677973366e38) return std::copysign(HUGE_VAL, v);
+        return m < std::ldexp(1.0, -126) ? (double)(float)v : v;
+    };
+    auto in_range = [&](cx &v) {
+        if (f32) v = cx(held(v.real()), held(v.imag()));
+    };
+    const double sc = std::ldexp(1.0, h->sexp) * (h->shalf ? 1.0 / std::sqrt(2.0) : 1.0) * h->fscale;
+    const double sc_in = h->gen_n > 0 ? sc : 1.0;    // a generated start value carries the factor
+    const double sc_out = h->gen_n > 0 ? 1.0 : sc;
     for (uint64_t tile = 0; tile < ntiles; tile++) {
         uint64_t tbase = tile << 4;
         for (int i = 0; i < ntq; i++) tbase = ins0(tbase, h->tq[i]);
@@ -68,7 +82,7 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                     if (h->gen_n > 0) {
                         double v = std::ldexp(1.0, -(h->gen_n / 2));
                         if (h->gen_n & 1) v /= std::sqrt(2.0);
-                        cx x = v;
+                        cx x = v * sc_in;
                         if (gp) {
                             x *= gtile;
                             for (int b = 0; b < 6; b++)
@@ -119,6 +133,8 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                             if (r & (1 << p.a)) continue;
                             cx &x = a[l * nr + r], &y = a[l * nr + (r | (1 << p.a))];
                             cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
+                            in_range(nx);
+                            in_range(ny);
                             x = nx;
                             y = ny;
                         }
@@ -129,6 +145,8 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                         for (int r = 0; r < nr; r++) {
                             cx &x = a[l * nr + r], &y = a[l1 * nr + r];
                             cx nx = u[0] * x + u[1] * y, ny = u[2] * x + u[3] * y;
+                            in_range(nx);
+                            in_range(ny);
                             x = nx;
                             y = ny;
                         }
@@ -146,7 +164,10 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                             } else {
                                 cx v = rnd(cx(d.val[0], d.val[1]));
                                 for (int r = 0; r < nr; r++)
-                                    if ((d.regset >> r) & 1) a[l * nr + r] *= v;
+                                    if ((d.regset >> r) & 1) {
+                                        a[l * nr + r] *= v;
+                                        in_range(a[l * nr + r]);
+                                    }
                             }
                         }
                         for (int r = 0; r < nr; r++)
@@ -155,11 +176,11 @@ static void emulate_regtile(const Plan &plan, const Op &op, int n, cx *psi) {
                 }
             }
         }
-        const double sc = std::ldexp(1.0, h->sexp) * (h->shalf ? 1.0 / std::sqrt(2.0) : 1.0) * h->fscale;
+        const double f_out = rnd(cx(sc_out)).real();
         for (int w = 0; w < nw; w++)
             for (int l = 0; l < 64; l++)
                 for (int r = 0; r < nr; r++)
-                    psi[wbase[w] + roff[r] + loff[l]] = all[((size_t)w * 64 + l) * nr + r] * sc;
+                    psi[wbase[w] + roff[r] + loff[l]] = all[((size_t)w * 64 + l) * nr + r] * f_out;
     }
 }
 

@@ -487,7 +487,8 @@ struct RTProgram {
     RTHeader h{};
     std::vector<RTOp> ops;
     std::vector<DiagTerm> terms;
-    std::vector<double> opc;   // cosine taken out of each op (1: none)
+    std::vector<double> opc;   // factor taken out of each op (1: none): a tangent
+                               // form's cosine, a settling term's power of two
     bool gen_phases = false;   // diagonals folded into the generated state
     RTGenPhases gp{};
     std::vector<RTGenOut> gout;
@@ -654,10 +655,19 @@ static void wide_layout(const std::vector<SGate> &g, int vbits, int n, Sweep *sw
     }
 }
 
+// Powers of two by which the scaled forms may let a sweep's amplitudes grow
+// before a term takes them back (exact).  An add-only form counts 1/2, a tangent
+// form log2(1/c) <= 1.  A generated first sweep starts that much below the
+// uniform value, and the adjoint's gradient sums hold products of two grown
+// states, so 2^(2 x 40) and 2^-17.5 must fit FP32 with room.  Default budgets
+// stay below it for the lattice circuits (at most 35 up to 35 qubits and depth
+// 200); without it a 14-qubit, depth-130 circuit at budget 2000 grows by 2^152.
+static double growth_limit(int dtype) { return dtype == SV_C64 ? 40.0 : 400.0; }
+
 // gen: the sweep starts from the uniform state (generated in its registers);
 // single-qubit diagonals without a gradient slot that act before any dense
 // gate on their qubit are then folded into the generated values.
-static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int vbits, int n,
+static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int vbits, int n, int dtype,
                                bool cheap = false, int *ncheap = nullptr, bool gen = false) {
     RTProgram P;
     RTHeader &h = P.h;
@@ -737,6 +747,7 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
         return t;
     };
     int nc = 0;
+    double grown = 0.0;   // log2 of the growth since the last settling term
     std::vector<int> wnow = wide ? sw.wq : std::vector<int>();   // qubits on the wave bits
     const std::vector<int> order = wide ? sw.order : batch_diagonals(g, sw.items);
     std::vector<char> fold(order.size(), 0);
@@ -827,6 +838,23 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
             if (s.kind == SG_DENSE && tangent_form(&o, &c)) h.fscale *= c;
             ops.push_back(o);
             P.opc.push_back(c);
+            if (s.kind == SG_DENSE) grown += form_scaled(o.form) ? 0.5 : -std::log2(std::fabs(c));
+            if (grown >= growth_limit(dtype)) {
+                const int m = (int)grown;
+                DiagTerm t = term_for(0);
+                t.val[0] = std::ldexp(1.0, -m);
+                RTOp o2{};
+                o2.kind = RT_PHASE;
+                o2.a = (int)terms.size();
+                o2.nterms = 1;
+                o2.slot = -1;
+                o2.gscale = 1.0;
+                terms.push_back(t);
+                ops.push_back(o2);
+                P.opc.push_back(std::ldexp(1.0, m));
+                h.fscale *= std::ldexp(1.0, m);
+                grown -= m;
+            }
         } else if (s.kind == SG_CZ) {
             DiagTerm t = term_for(bit64(s.q0) | bit64(s.q1));
             if (!ops.empty() && ops.back().kind == RT_SIGNS &&
@@ -917,14 +945,16 @@ static RTProgram build_regtile(const std::vector<SGate> &g, const Sweep &sw, int
                 RTOp c = ops[u];
                 c.a = (int)nterms.size();
                 c.nterms = 0;
+                double oc = 1.0;
                 for (size_t w = u; w < j; w++)
                     if (!used[w - i] && terms[ops[w].a].regset == rs) {
                         used[w - i] = 1;
                         nterms.push_back(terms[ops[w].a]);
                         c.nterms++;
+                        oc *= P.opc[w];
                     }
                 nops.push_back(c);
-                nopc.push_back(1.0);
+                nopc.push_back(oc);
             }
             i = j;
         }
@@ -1017,7 +1047,7 @@ static void push_regtile(const RTProgram &P, int n, int dtype, OpType type, std:
 static void emit_regtile(const std::vector<SGate> &g, const Sweep &sw, int vbits, int n, int dtype,
                          Plan *plan, std::vector<std::pair<size_t, int>> *scales, bool gen = false) {
     int nc = 0;
-    RTProgram P = build_regtile(g, sw, vbits, n, true, &nc, gen);
+    RTProgram P = build_regtile(g, sw, vbits, n, dtype, true, &nc, gen);
     push_regtile(P, n, dtype, OP_REGTILE, &plan->ops, plan);
     scales->push_back({plan->ops.back().prog_off, nc});
 }
@@ -1701,7 +1731,7 @@ sv_status build_adjoint_plan(const sv_circuit *c, const PlanRequest &rq, int che
     std::vector<RTProgram> progs;
     progs.reserve(m);
     for (int j2 = 0; j2 < m; j2++) {
-        progs.push_back(build_regtile(g, sweeps[j2], vb, rq.n));
+        progs.push_back(build_regtile(g, sweeps[j2], vb, rq.n, rq.dtype));
         push_regtile(progs.back(), rq.n, rq.dtype, OP_REGTILE, &plan->ops, plan);
         plan->ops.back().q1 = ck_after[j2];
         if (ck_after[j2] >= 0) plan->ops.back().bytes += state_bytes(rq.n, rq.dtype);
