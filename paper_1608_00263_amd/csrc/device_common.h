@@ -555,25 +555,36 @@ __device__ __forceinline__ void xchg_get(cplx<T> (&a)[1 << VB], lptr<T> lds, int
             else a[(W ^ x) * NL + i].re = v;
         }
 }
-template <typename T, int VB, int W>
-__device__ __forceinline__ void xchg_wave(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane) {
-    __syncthreads();   // the words are free (an earlier exchange has been read)
-    xchg_put<T, VB, W, false>(a, lds, lane);
-    __syncthreads();
-    xchg_get<T, VB, W, false>(a, lds, lane);
-    __syncthreads();
-    xchg_put<T, VB, W, true>(a, lds, lane);
-    __syncthreads();
-    xchg_get<T, VB, W, true>(a, lds, lane);
+template <typename T, int VB, bool IM>
+__device__ __forceinline__ void xchg_put(const cplx<T> (&a)[1 << VB], lptr<T> lds, int lane, int wave) {
+    switch (wave) {
+    case 0: xchg_put<T, VB, 0, IM>(a, lds, lane); break;
+    case 1: xchg_put<T, VB, 1, IM>(a, lds, lane); break;
+    case 2: xchg_put<T, VB, 2, IM>(a, lds, lane); break;
+    default: xchg_put<T, VB, 3, IM>(a, lds, lane); break;
+    }
 }
+template <typename T, int VB, bool IM>
+__device__ __forceinline__ void xchg_get(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane, int wave) {
+    switch (wave) {
+    case 0: xchg_get<T, VB, 0, IM>(a, lds, lane); break;
+    case 1: xchg_get<T, VB, 1, IM>(a, lds, lane); break;
+    case 2: xchg_get<T, VB, 2, IM>(a, lds, lane); break;
+    default: xchg_get<T, VB, 3, IM>(a, lds, lane); break;
+    }
+}
+// The wavefronts choose their registers inside the steps and meet outside them:
+// every barrier is one program point for the whole workgroup.
 template <typename T, int VB>
 __device__ __forceinline__ void wave_exchange(cplx<T> (&a)[1 << VB], lptr<T> lds, int lane, int wave) {
-    switch (wave) {
-    case 0: xchg_wave<T, VB, 0>(a, lds, lane); break;
-    case 1: xchg_wave<T, VB, 1>(a, lds, lane); break;
-    case 2: xchg_wave<T, VB, 2>(a, lds, lane); break;
-    default: xchg_wave<T, VB, 3>(a, lds, lane); break;
-    }
+    __syncthreads();   // the words are free (an earlier exchange has been read)
+    xchg_put<T, VB, false>(a, lds, lane, wave);
+    __syncthreads();
+    xchg_get<T, VB, false>(a, lds, lane, wave);
+    __syncthreads();
+    xchg_put<T, VB, true>(a, lds, lane, wave);
+    __syncthreads();
+    xchg_get<T, VB, true>(a, lds, lane, wave);
 }
 
 // The exchange and the arrangement after it: the slots' address bits bq, the
