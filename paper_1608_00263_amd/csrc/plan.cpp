@@ -21,6 +21,7 @@
 #include <cmath>
 #include <cstdio>
 #include <functional>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <set>
@@ -315,172 +316,218 @@ struct Sweep {
 // Qubit sets are 64-bit masks.  The cost of an item depends on whether its
 // first qubit is in the tile.
 using CostFn = std::function<double(int, bool)>;
-static std::vector<Sweep> group_sweeps_once(bool lookahead, int nfixed, int nitems, int n, int cap,
-                                            const std::function<bool(int)> &diag,
-                                            const std::function<std::vector<int>(int)> &qubits, const CostFn &cost,
-                                            double budget, int beam = 1) {
-    std::vector<Sweep> out;
-    std::vector<char> done0(nitems, 0);
-    const std::vector<char> *cur = &done0;   // the items already taken
-    int left = nitems;
-    std::vector<std::vector<int>> qs_of(nitems);
-    std::vector<uint64_t> mask(nitems, 0), first_bit(nitems, 0);
-    std::vector<char> is_diag(nitems);
-    std::vector<double> cost_in(nitems, 0.0), cost_out(nitems, 0.0);
-    for (int i = 0; i < nitems; i++) {
-        qs_of[i] = qubits(i);
-        for (int q : qs_of[i]) mask[i] |= bit64(q);
-        if (!qs_of[i].empty()) first_bit[i] = bit64(qs_of[i][0]);
-        is_diag[i] = diag(i) ? 1 : 0;
-        if (cost) {
-            cost_in[i] = cost(i, true);
-            cost_out[i] = cost(i, false);
-        }
-    }
-    const bool costed = (bool)cost;
-    const uint64_t everything = bit64(n) - 1;
-    int first_left = 0;   // no item before it is left
-    // one sweep from the current state; fixed != null: the gathered set is
-    // given, else it grows greedily
-    auto simulate = [&](const std::vector<char> *fixed, Sweep *sw) {
-        uint64_t block_all = 0, block_dense = 0, in_tile = bit64(std::min(n, nfixed)) - 1;
-        int ngather = 0;
-        if (fixed)
-            for (int q = nfixed; q < n; q++)
-                if ((*fixed)[q]) { in_tile |= bit64(q); sw->tile.push_back(q); ngather++; }
+
+struct Grouping {
+    int nitems, n, nfixed, cap;
+    double budget;
+    bool costed;
+    // per item
+    std::vector<uint64_t> mask, first_bit;
+    std::vector<char> diag;
+    std::vector<double> cost_in, cost_out;
+
+    // A sweep from some state: the gathered qubits and the items taken.
+    struct Taken {
+        uint64_t set = 0;
+        std::vector<int> items;
+    };
+    uint64_t fixed_bits() const { return bit64(std::min(n, nfixed)) - 1; }
+
+    // One sweep of the items left (ascending); gathered: the gathered set is
+    // `set`, else it grows greedily.
+    void simulate(const std::vector<int> &left, bool gathered, uint64_t set, Taken *out) const {
+        const uint64_t everything = bit64(n) - 1, fixed = fixed_bits();
+        uint64_t block_all = 0, block_dense = 0, in_tile = fixed | set;
         double spent = 0;
-        for (int i = first_left; i < nitems && block_all != everything; i++) {
-            if ((*cur)[i]) continue;
+        out->items.clear();
+        for (int i : left) {
+            if (block_all == everything) break;
             const uint64_t qm = mask[i];
-            const bool d = is_diag[i];
+            const bool d = diag[i];
             bool ok = !(qm & block_all) && (d || !(qm & block_dense));
-            if (ok && !d) {
-                const int need = __builtin_popcountll(qm & ~in_tile);
-                if (need && (fixed || ngather + need > cap)) ok = false;
-            }
+            if (ok && !d && (qm & ~in_tile))
+                ok = !gathered && __builtin_popcountll((in_tile | qm) & ~fixed) <= cap;
             // arithmetic budget of a sweep (the first item always fits)
-            if (ok && costed && !sw->items.empty() &&
+            if (ok && costed && !out->items.empty() &&
                 spent + (!d || (first_bit[i] & in_tile) ? cost_in[i] : cost_out[i]) > budget)
                 ok = false;
             if (ok) {
                 if (costed) spent += first_bit[i] & in_tile ? cost_in[i] : cost_out[i];
-                if (!d)
-                    for (int q : qs_of[i])
-                        if (!(in_tile & bit64(q))) { in_tile |= bit64(q); sw->tile.push_back(q); ngather++; }
-                sw->items.push_back(i);
+                if (!d) in_tile |= qm;
+                out->items.push_back(i);
             } else if (d) {
                 block_dense |= qm;
             } else {
                 block_all |= qm;
             }
         }
-        std::sort(sw->tile.begin(), sw->tile.end());
-    };
-    // candidate sweeps from the current state: the greedy one and, with
-    // look-ahead, one per window W
-    auto candidates = [&](const std::vector<int> &windows) {
-        std::vector<Sweep> cs(1);
-        first_left = 0;
-        while (first_left < nitems && (*cur)[first_left]) first_left++;
-        simulate(nullptr, &cs[0]);
+        out->set = in_tile & ~fixed;
+    }
+
+    // Candidate sweeps: the greedy one and one per look-ahead window
+    // (ascending); their number.
+    int candidates(const std::vector<int> &left, const std::vector<int> &windows, std::vector<Taken> *cs) const {
+        size_t m = 0;
+        auto next = [&]() -> Taken * {
+            if (cs->size() == m) cs->emplace_back();
+            return &(*cs)[m++];
+        };
+        simulate(left, false, 0, next());
         std::vector<uint64_t> tried;
+        std::vector<int> count(n, 0), first(n, nitems), cand;
+        size_t seen = 0;
         for (int W : windows) {
-            std::vector<int> count(n, 0), first(n, nitems);
-            int seen = 0;
-            for (int i = 0; i < nitems && seen < W; i++) {
-                if ((*cur)[i]) continue;
-                seen++;
-                if (is_diag[i]) continue;
-                for (int q : qs_of[i])
-                    if (q >= nfixed) {
-                        count[q]++;
-                        first[q] = std::min(first[q], i);
-                    }
+            for (; seen < left.size() && (int)seen < W; seen++) {
+                const int i = left[seen];
+                if (diag[i]) continue;
+                for (uint64_t r = mask[i] & ~(bit64(nfixed) - 1); r; r &= r - 1) {
+                    const int q = __builtin_ctzll(r);
+                    count[q]++;
+                    first[q] = std::min(first[q], i);
+                }
             }
-            std::vector<int> cand;
+            cand.clear();
             for (int q = nfixed; q < n; q++)
                 if (count[q] > 0) cand.push_back(q);
             std::sort(cand.begin(), cand.end(), [&](int a, int b) {
                 return count[a] != count[b] ? count[a] > count[b] : first[a] < first[b];
             });
             if ((int)cand.size() > cap) cand.resize(cap);
-            std::vector<char> fixed(n, 0);
             uint64_t set = 0;
-            for (int q : cand) { fixed[q] = 1; set |= bit64(q); }
-            if (std::find(tried.begin(), tried.end(), set) != tried.end()) continue;   // the same sweep again
-            tried.push_back(set);
-            Sweep sw;
-            simulate(&fixed, &sw);
-            cs.push_back(sw);
+            for (int q : cand) set |= bit64(q);
+            if (std::find(tried.begin(), tried.end(), set) == tried.end()) {   // else the same sweep again
+                tried.push_back(set);
+                simulate(left, true, set, next());
+            }
+            if (seen == left.size()) break;   // wider windows see the same items
         }
-        return cs;
-    };
-    if (beam <= 1) {
-        std::vector<int> windows;
-        if (lookahead) windows = {24, 48, 96, 192};
-        while (left > 0) {
-            std::vector<Sweep> cs = candidates(windows);
-            Sweep best = cs[0];
-            for (size_t c = 1; c < cs.size(); c++)
-                if (cs[c].items.size() > best.items.size()) best = cs[c];
-            // an item that fits no sweep (wider than the tile) would never be
-            // taken: no grouping
-            if (best.items.empty()) return {};
-            for (int i : best.items) done0[i] = 1;
-            left -= (int)best.items.size();
-            out.push_back(best);
+        return (int)m;
+    }
+
+    static std::vector<int> without(const std::vector<int> &left, const std::vector<int> &items) {
+        std::vector<int> out;
+        out.reserve(left.size() - items.size());
+        std::set_difference(left.begin(), left.end(), items.begin(), items.end(), std::back_inserter(out));
+        return out;
+    }
+    Sweep sweep(const Taken &t) const {
+        Sweep sw;
+        for (uint64_t r = t.set; r; r &= r - 1) sw.tile.push_back(__builtin_ctzll(r));
+        sw.items = t.items;
+        return sw;
+    }
+    std::vector<int> all_items() const {
+        std::vector<int> v(nitems);
+        for (int i = 0; i < nitems; i++) v[i] = i;
+        return v;
+    }
+
+    // One sweep after the other, each the candidate with the most items; none
+    // if an item fits no sweep (wider than the tile) or if it takes `fewer`
+    // sweeps or more.
+    std::vector<Sweep> one_by_one(const std::vector<int> &windows, size_t fewer) const {
+        std::vector<Sweep> out;
+        std::vector<int> left = all_items();
+        std::vector<Taken> cs;
+        while (!left.empty()) {
+            if (out.size() + 1 >= fewer) return {};
+            const int m = candidates(left, windows, &cs);
+            int best = 0;
+            for (int c = 1; c < m; c++)
+                if (cs[c].items.size() > cs[best].items.size()) best = c;
+            if (cs[best].items.empty()) return {};
+            left = without(left, cs[best].items);
+            out.push_back(sweep(cs[best]));
         }
         return out;
     }
-    struct State {
-        std::vector<char> done;
-        std::vector<Sweep> sweeps;
-        int left;
-    };
-    std::vector<State> states(1);
-    states[0].done.assign(nitems, 0);
-    states[0].left = nitems;
-    const std::vector<int> windows = {12, 24, 36, 48, 72, 96, 144, 192, 288};
-    for (;;) {
-        for (const State &st : states)
-            if (st.left == 0) return st.sweeps;
-        std::vector<State> next;
-        for (const State &st : states) {
-            cur = &st.done;
-            for (const Sweep &sw : candidates(windows)) {
-                if (sw.items.empty()) continue;
-                State c;
-                c.done = st.done;
-                for (int i : sw.items) c.done[i] = 1;
-                bool dup = false;
-                for (const State &o : next)
-                    if (o.done == c.done) { dup = true; break; }
-                if (dup) continue;
-                c.sweeps = st.sweeps;
-                c.sweeps.push_back(sw);
-                c.left = st.left - (int)sw.items.size();
-                next.push_back(std::move(c));
+
+    // Beam search for fewer than `fewer` sweeps, given up at the depth where
+    // there are none.
+    std::vector<Sweep> beam_search(int beam, size_t fewer) const {
+        struct Node {
+            int parent;
+            Taken taken;
+        };
+        struct State {
+            std::vector<int> left;
+            int node;
+        };
+        const std::vector<int> windows = {12, 24, 36, 48, 72, 96, 144, 192, 288};
+        std::vector<Node> nodes;
+        std::vector<State> states(1), next;
+        std::vector<Taken> cs;
+        states[0].left = all_items();
+        states[0].node = -1;
+        for (size_t depth = 0;; depth++) {
+            for (const State &st : states)
+                if (st.left.empty()) {
+                    std::vector<Sweep> out;
+                    for (int k = st.node; k >= 0; k = nodes[k].parent) out.push_back(sweep(nodes[k].taken));
+                    std::reverse(out.begin(), out.end());
+                    return out;
+                }
+            if (depth + 1 >= fewer) return {};
+            next.clear();
+            for (const State &st : states) {
+                const int m = candidates(st.left, windows, &cs);
+                for (int c = 0; c < m; c++) {
+                    if (cs[c].items.empty()) continue;
+                    State nx;
+                    nx.left = without(st.left, cs[c].items);
+                    bool dup = false;
+                    for (const State &o : next)
+                        if (o.left == nx.left) { dup = true; break; }
+                    if (dup) continue;
+                    nx.node = (int)nodes.size();
+                    nodes.push_back({st.node, cs[c]});
+                    next.push_back(std::move(nx));
+                }
             }
+            if (next.empty()) return {};
+            std::stable_sort(next.begin(), next.end(),
+                             [](const State &a, const State &b) { return a.left.size() < b.left.size(); });
+            if ((int)next.size() > beam) next.resize(beam);
+            states.swap(next);
         }
-        if (next.empty()) return {};
-        std::stable_sort(next.begin(), next.end(), [](const State &a, const State &b) { return a.left < b.left; });
-        if ((int)next.size() > beam) next.resize(beam);
-        states.swap(next);
     }
-}
+};
 
 // nfixed: qubits 0..nfixed-1 are always in the sweep's set (the lanes).
+// fewer: only a grouping of fewer sweeps is of use (none is returned
+// otherwise), so the searches stop where they cannot give one.
 static std::vector<Sweep> group_sweeps(int nitems, int n, int cap, const std::function<bool(int)> &diag,
                                        const std::function<std::vector<int>(int)> &qubits,
                                        const CostFn &cost = nullptr,
-                                       double budget = 0, int nfixed = LANE_BITS) {
-    std::vector<Sweep> a = group_sweeps_once(false, nfixed, nitems, n, cap, diag, qubits, cost, budget);
-    std::vector<Sweep> b = group_sweeps_once(true, nfixed, nitems, n, cap, diag, qubits, cost, budget);
-    if (a.empty() || b.empty()) return a.empty() ? b : a;   // empty: some item fits no sweep
-    std::vector<Sweep> best = b.size() < a.size() ? b : a;
-    std::vector<Sweep> c = group_sweeps_once(true, nfixed, nitems, n, cap, diag, qubits, cost, budget, 6);
-    if (!c.empty() && c.size() < best.size()) best = c;
-    return best;
+                                       double budget = 0, int nfixed = LANE_BITS, size_t fewer = SIZE_MAX) {
+    Grouping G;
+    G.nitems = nitems;
+    G.n = n;
+    G.nfixed = nfixed;
+    G.cap = cap;
+    G.budget = budget;
+    G.costed = (bool)cost;
+    G.mask.assign(nitems, 0);
+    G.first_bit.assign(nitems, 0);
+    G.diag.resize(nitems);
+    G.cost_in.assign(nitems, 0.0);
+    G.cost_out.assign(nitems, 0.0);
+    for (int i = 0; i < nitems; i++) {
+        const std::vector<int> qs = qubits(i);
+        for (int q : qs) G.mask[i] |= bit64(q);
+        if (!qs.empty()) G.first_bit[i] = bit64(qs[0]);
+        G.diag[i] = diag(i) ? 1 : 0;
+        if (cost) {
+            G.cost_in[i] = cost(i, true);
+            G.cost_out[i] = cost(i, false);
+        }
+    }
+    std::vector<Sweep> best = G.one_by_one({}, fewer);
+    std::vector<Sweep> b = G.one_by_one({24, 48, 96, 192}, fewer);
+    if (!b.empty() && (best.empty() || b.size() < best.size())) best.swap(b);
+    if (best.empty() && fewer == SIZE_MAX) return best;   // some item fits no sweep
+    std::vector<Sweep> c = G.beam_search(6, best.empty() ? fewer : best.size());
+    return c.empty() ? best : c;
 }
 
 struct RTProgram {
@@ -518,35 +565,25 @@ static void put_mat(double *dst, const M2 &m) {
 // and every ready dense item, where an item is ready when no earlier
 // remaining item shares a qubit with it (two diagonal items always commute).
 static std::vector<int> batch_diagonals(const std::vector<SGate> &g, const std::vector<int> &items) {
-    std::vector<int> rem(items), out;
-    auto qubits = [&](int i, int *q) {
-        q[0] = g[i].q0;
-        q[1] = g[i].kind == SG_CZ ? g[i].q1 : -1;
-    };
+    std::vector<int> rem(items), keep, out;
     auto diag = [&](int i) { return g[i].kind != SG_DENSE; };
     bool want_diag = true;
     int idle = 0;
     while (!rem.empty()) {
-        std::vector<int> keep;
-        bool took = false;
-        for (size_t a = 0; a < rem.size(); a++) {
-            int i = rem[a];
-            bool ready = diag(i) == want_diag;
-            int qi[2];
-            qubits(i, qi);
-            for (size_t b = 0; ready && b < a; b++) {
-                int j = rem[b];
-                if (j < 0) continue;   // taken in this pass
-                if (diag(i) && diag(j)) continue;
-                int qj[2];
-                qubits(j, qj);
-                for (int x = 0; x < 2; x++)
-                    for (int y = 0; y < 2; y++)
-                        if (qi[x] >= 0 && qi[x] == qj[y]) ready = false;
+        keep.clear();
+        uint64_t on_diag = 0, on_dense = 0;   // qubits of the earlier items kept
+        for (int i : rem) {
+            const uint64_t qm = bit64(g[i].q0) | (g[i].kind == SG_CZ ? bit64(g[i].q1) : 0);
+            const bool d = diag(i);
+            if (d == want_diag && !(qm & on_dense) && (d || !(qm & on_diag))) {
+                out.push_back(i);
+                continue;
             }
-            // items already moved out of rem no longer block anything
-            if (ready) { out.push_back(i); took = true; rem[a] = -1; }
+            keep.push_back(i);
+            if (d) on_diag |= qm;
+            else on_dense |= qm;
         }
+        const bool took = keep.size() < rem.size();
         if (want_diag) {
             // within a diagonal batch: the CZ sign flips first (one run), then
             // the single-qubit phases
@@ -555,8 +592,6 @@ static std::vector<int> batch_diagonals(const std::vector<SGate> &g, const std::
             std::stable_partition(out.begin() + first, out.end(),
                                   [&](int i) { return g[i].kind == SG_CZ; });
         }
-        for (int i : rem)
-            if (i >= 0) keep.push_back(i);
         rem.swap(keep);
         want_diag = !want_diag;
         idle = took ? 0 : idle + 1;
@@ -592,33 +627,28 @@ static void wide_layout(const std::vector<SGate> &g, int vbits, int n, Sweep *sw
     std::vector<int> R;   // vbits + 2 qubits, fewest dense gates first
     for (int q : G)
         if (!has(lq, q)) R.push_back(q);
-    const int m = (int)sw->items.size();
-    std::vector<char> done(m);
-    // exchanges needed with the pairs (w0, w1) on the wave bits and (a0, a1)
-    // in the top slots at the load; with out, the items of each stretch too
-    auto run = [&](int w0, int w1, int a0, int a1, int limit, std::vector<std::vector<int>> *out) {
-        std::fill(done.begin(), done.end(), 0);
-        int left = m, count = 0;
-        for (;;) {
-            uint64_t all = 0, densely = 0, away = bit64(count % 2 ? a0 : w0) | bit64(count % 2 ? a1 : w1);
-            if (out) out->emplace_back();
-            for (int k = 0; k < m; k++) {
-                if (done[k]) continue;
-                const SGate &s = g[sw->items[k]];
-                const uint64_t qs = bit64(s.q0) | (s.kind == SG_CZ ? bit64(s.q1) : 0);
-                const bool d = s.kind != SG_DENSE;
-                if (!(qs & all) && (d || !(qs & (densely | away)))) {
-                    done[k] = 1;
-                    left--;
-                    if (out) out->back().push_back(sw->items[k]);
-                } else if (d) {
-                    densely |= qs;
-                } else {
-                    all |= qs;
-                }
+    struct Item {
+        uint64_t qs;
+        int idx;
+        bool diag;
+    };
+    std::vector<Item> all;
+    all.reserve(sw->items.size());
+    for (int i : sw->items)
+        all.push_back({bit64(g[i].q0) | (g[i].kind == SG_CZ ? bit64(g[i].q1) : 0), i, g[i].kind != SG_DENSE});
+    // one stretch between exchanges, with the qubits of `away` on the wave bits:
+    // the items that run (into out, if any) and those that are left
+    auto stretch = [](const std::vector<Item> &in, uint64_t away, std::vector<Item> *left, std::vector<int> *out) {
+        uint64_t block = 0, densely = 0;
+        left->clear();
+        for (const Item &t : in) {
+            if (!(t.qs & block) && (t.diag || !(t.qs & (densely | away)))) {
+                if (out) out->push_back(t.idx);
+                continue;
             }
-            if (!left || count >= limit) return count;
-            count++;
+            if (t.diag) densely |= t.qs;
+            else block |= t.qs;
+            left->push_back(t);
         }
     };
     int best = 1 << 20, bp[4] = {0, 1, 2, 3};
@@ -626,19 +656,36 @@ static void wide_layout(const std::vector<SGate> &g, int vbits, int n, Sweep *sw
     int used = 0;   // qubits that need a register at some time
     for (int q : R) used += dense[q] > 0;
     const int least = used > vbits ? 1 : 0;
+    std::vector<Item> first, cur, rest;
     for (int i = 0; i < r && best > least; i++)
-        for (int j = i + 1; j < r && best > least; j++)
+        for (int j = i + 1; j < r && best > least; j++) {
+            const uint64_t w = bit64(R[i]) | bit64(R[j]);
+            stretch(all, w, &first, nullptr);   // the same for every (k, l)
             for (int k = 0; k < r && best > least; k++)
                 for (int l = k + 1; l < r && best > least; l++) {
                     if (k == i || k == j || l == i || l == j) continue;
-                    const int c = run(R[i], R[j], R[k], R[l], best, nullptr);
+                    const uint64_t a = bit64(R[k]) | bit64(R[l]);
+                    int c = 0;
+                    cur = first;
+                    while (!cur.empty() && c < best) {
+                        c++;
+                        stretch(cur, c % 2 ? a : w, &rest, nullptr);
+                        cur.swap(rest);
+                    }
                     if (c < best) {
                         best = c;
                         bp[0] = i; bp[1] = j; bp[2] = k; bp[3] = l;
                     }
                 }
+        }
     std::vector<std::vector<int>> parts;
-    run(R[bp[0]], R[bp[1]], R[bp[2]], R[bp[3]], 1 << 20, &parts);
+    cur = all;
+    do {
+        const bool odd = parts.size() % 2;
+        parts.emplace_back();
+        stretch(cur, odd ? bit64(R[bp[2]]) | bit64(R[bp[3]]) : bit64(R[bp[0]]) | bit64(R[bp[1]]), &rest, &parts.back());
+        cur.swap(rest);
+    } while (!cur.empty());
     sw->lq = lq;
     sw->wq = {R[bp[0]], R[bp[1]]};
     sw->rq.clear();
@@ -1350,7 +1397,7 @@ static void plan_per_gate(const sv_circuit *c, const std::vector<SGate> &g, cons
 // flex: lane bits 4 and 5 may take any qubit (the sweep gathers vb + 2
 // qubits above 3) instead of qubits 4 and 5.
 static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
-                                         double budget, bool flex, bool wide) {
+                                         double budget, bool flex, bool wide, size_t fewer) {
     (void)dtype;
     const int nfixed = flex ? 4 : LANE_BITS;
     auto cost = [&](int i, bool in_tile) -> double {
@@ -1370,24 +1417,26 @@ static std::vector<Sweep> find_regtile_sweeps(const std::vector<SGate> &g, int n
             if (g[i].kind == SG_CZ) q.push_back(g[i].q1);
             return q;
         },
-        cost, budget, nfixed);
+        cost, budget, nfixed, fewer);
     if (wide)
         for (Sweep &sw : sweeps) wide_layout(g, vb, n, &sw);
     return sweeps;
 }
 
 // The grouping depends on the gates' kinds, forms and qubits only, not on
-// their angles, and takes most of a plan's time (the beam search: about 5 ms
-// for 600 gates).  A program that trains rotation offsets plans a new set of
+// their angles, and takes most of a plan's time (about 3 ms for 600 gates, the
+// searches for both kinds of tiles).  A program that trains rotation offsets plans a new set of
 // angles every step, so the last groupings are kept, found by their whole
 // input.
 static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int vb, int dtype,
-                                         double budget = -1, bool flex = false, bool wide = false) {
+                                         double budget = -1, bool flex = false, bool wide = false,
+                                         size_t fewer = SIZE_MAX) {
     // the wide default: 30 qubits complex64, three circuits, 35.6-36.1 ms at 300
     // against 35.5-38.9 at 250 and 35.2-37.5 at 160; complex128 flat from 200
     if (budget < 0) budget = dtype == SV_C64 ? (wide ? 300.0 : 250.0) : 220.0;
-    std::vector<int32_t> key = {n, vb, (flex ? 1 : 0) | (wide ? 2 : 0), (int32_t)(budget * 256.0)};
-    key.reserve(4 + 4 * g.size());
+    std::vector<int32_t> key = {n, vb, (flex ? 1 : 0) | (wide ? 2 : 0), (int32_t)(budget * 256.0),
+                                (int32_t)std::min<size_t>(fewer, INT32_MAX)};
+    key.reserve(5 + 4 * g.size());
     for (const SGate &s : g) key.insert(key.end(), {s.kind, s.form, s.q0, s.q1});
     constexpr size_t KEPT = 64;
     static std::mutex *mu = new std::mutex();
@@ -1397,7 +1446,7 @@ static std::vector<Sweep> regtile_sweeps(const std::vector<SGate> &g, int n, int
         auto it = kept->find(key);
         if (it != kept->end()) return it->second;
     }
-    std::vector<Sweep> sw = find_regtile_sweeps(g, n, vb, dtype, budget, flex, wide);
+    std::vector<Sweep> sw = find_regtile_sweeps(g, n, vb, dtype, budget, flex, wide, fewer);
     std::lock_guard<std::mutex> lock(*mu);
     if (kept->size() >= KEPT) kept->clear();
     (*kept)[std::move(key)] = sw;
@@ -1491,10 +1540,15 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         // sweep: 30 qubits complex64 10 sweeps in 35.0 ms against 13 in 40.4,
         // 28 qubits complex128 10 in 17.0 ms against 14 in 22.2.  With equal
         // counts the exchanges only cost (12 qubits complex128, 3 register
-        // qubits: 44.7 against 40.9 us).
-        if (vb >= 2 && rq.n >= vb + LANE_BITS + 2 && !keep) {
-            auto w = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true, true);
-            if (!w.empty() && w.size() < sweeps.size()) sweeps.swap(w);
+        // qubits: 44.7 against 40.9 us).  The second search looks for fewer
+        // sweeps only and stops where there are none: planning a new circuit
+        // takes 0.11 ms at 12 qubits, 0.48 at 16, 1.4 at 25 and 3.3 at 30 (one
+        // search for tiles of one wavefront alone: 0.13, 0.65, 2.2 and 4.8
+        // before the item tables and masks; both searches in full 0.24 to 0.39,
+        // 0.9 to 1.5, 2.4 and 5.6).
+        if (vb >= 2 && rq.n >= vb + LANE_BITS + 2 && !keep && sweeps.size() > 1) {
+            auto w = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true, true, sweeps.size());
+            if (!w.empty()) sweeps.swap(w);
         }
         std::vector<std::pair<size_t, int>> scales;
         // the uniform initialisation is generated inside the first sweep's
