@@ -487,6 +487,7 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t i) {
 constexpr int UNIT_BITS = 10, UNIT = 1 << UNIT_BITS;
 constexpr int PASS_BLOCKS = 2048;      // workgroups of a pass at most
 constexpr int MAX_GROUPS = 8192;
+constexpr int64_t RESOLVE_SLICE = (int64_t)1 << 25;   // samples per launch
 
 template <int CTRL, int ROWS>
 __device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
@@ -757,7 +758,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_finish_pass(const unsigned long
     }
 }
 
-// One wavefront per sample: t = floor(r W / 2^64), then x = min{j : C_j > t}
+// One wavefront per sample first, first + 1, ... < k: t = floor(r W / 2^64), then x = min{j : C_j > t}
 // by one 64-wide step per level (group prefix in two, chunks, sub-buckets,
 // the four consecutive entries of a lane).  Five dependent loads, and nothing
 // is read twice: bound by their latency over the resident wavefronts.  (A
@@ -770,11 +771,11 @@ __global__ __launch_bounds__(RB) void k_resolve(const S *__restrict__ src, uint6
                                                 const unsigned long long *__restrict__ csum,
                                                 const unsigned long long *__restrict__ subsum,
                                                 const PassResult *__restrict__ res, const uint64_t *__restrict__ words,
-                                                uint64_t seed, int64_t k, uint64_t *__restrict__ out) {
+                                                uint64_t seed, int64_t first, int64_t k, uint64_t *__restrict__ out) {
     constexpr int sb = G == 1 ? 8 : G == 2 ? 9 : 10;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t i = (int64_t)blockIdx.x * (RB / 64) + wave;
+    const int64_t i = first + (int64_t)blockIdx.x * (RB / 64) + wave;
     if (i >= k || res->status != PASS_OK) return;
     const int ng = (int)(nb / (uint64_t)cg);
     const uint64_t r = words ? words[i] : splitmix64(seed, (uint64_t)i);
@@ -956,11 +957,13 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
     hipLaunchKernelGGL(k_finish_pass, dim3(stats16 ? 2 : 1), dim3(CMB_THREADS), 0, s, csum, L.nb, L.cg, part,
                        stats16 ? L.blocks : 0, CHECK ? L.blocks : 0, off, res, slot.ptr ? (PassResult *)slot.ptr : res);
     SV_HIP(hipGetLastError());
-    if (k > 0) {
-        const unsigned rg = (unsigned)((k + RB / 64 - 1) / (RB / 64));
+    // a launch holds fewer than 2^32 threads: 2^25 samples take 2^31 of them
+    for (int64_t first = 0; first < k; first += RESOLVE_SLICE) {
+        const int64_t m = std::min(k - first, RESOLVE_SLICE);
+        const unsigned rg = (unsigned)((m + RB / 64 - 1) / (RB / 64));
 #define RESOLVE(G)                                                                                                 \
     hipLaunchKernelGGL((k_resolve<S, G>), dim3(rg), dim3(RB), 0, s, src, N, L.bs, L.nb, L.cg, off, csum, sub, res, \
-                       words, seed, k, dev_out)
+                       words, seed, first, first + m, dev_out)
         if (L.sb == 8) RESOLVE(1);
         else if (L.sb == 9) RESOLVE(2);
         else RESOLVE(4);
