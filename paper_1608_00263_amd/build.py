@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsv.so")
 ROOT = os.path.dirname(HERE)
 
-SOURCES = ["api.cpp", "plan.cpp", "emulate.cpp", "sweeps.hip", "reduce.hip", "cycles.hip",
+SOURCES = ["api.cpp", "slots.cpp", "plan.cpp", "emulate.cpp", "sweeps.hip", "reduce.hip", "cycles.hip",
            "adjoint.hip", "batch.hip"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

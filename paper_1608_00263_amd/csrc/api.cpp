@@ -52,35 +52,6 @@ Workspace::~Workspace() {
     if (ptr) (void)hipFree(ptr);
 }
 
-static std::mutex g_slot_mu;
-static uint8_t *g_slots = nullptr;
-static bool g_slots_tried = false;
-static uint32_t g_slots_free = (1u << ResultSlot::COUNT) - 1;
-
-ResultSlot::ResultSlot(size_t need) {
-    if (need > (size_t)BYTES) return;
-    std::lock_guard<std::mutex> lock(g_slot_mu);
-    if (!g_slots_tried) {
-        g_slots_tried = true;
-        void *p = nullptr;
-        if (hipHostMalloc(&p, (size_t)COUNT * BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-            g_slots = (uint8_t *)p;
-        else
-            (void)hipGetLastError();   // the calls copy
-    }
-    if (!g_slots || !g_slots_free) return;
-    const int i = __builtin_ctz(g_slots_free);
-    g_slots_free &= ~(1u << i);
-    ptr = g_slots + (size_t)i * BYTES;
-}
-
-void ResultSlot::release() {
-    if (!ptr) return;
-    std::lock_guard<std::mutex> lock(g_slot_mu);
-    g_slots_free |= 1u << (((uint8_t *)ptr - g_slots) / BYTES);
-    ptr = nullptr;
-}
-
 static int max_qubits(sv_dtype dt) { return dt == SV_C64 ? 35 : 34; }
 
 static sv_status check_state(sv_state *st) {

@@ -326,13 +326,17 @@ struct Workspace {
 // its own and 6-8 us of a call of 40).  A process-wide block of 16 slots of
 // 4 KB, allocated once for all devices and kept until the process ends; ptr is
 // null when the result is larger, every slot is taken or there is no pinned
-// memory, and the call copies.  release() after the stream was waited for: a
-// call that fails before that leaves its slot out, as its kernel may still
-// write to it.
+// memory, and the call copies.  release() after the stream was waited for; a
+// call that fails before that waits at its end, and only where the wait fails
+// too does its slot stay out, as its kernel may still write to it.
 struct ResultSlot {
     static constexpr int COUNT = 16, BYTES = 4096;
     void *ptr = nullptr;
-    explicit ResultSlot(size_t need);
+    hipStream_t stream;
+    ResultSlot(size_t need, hipStream_t s);
+    ResultSlot(const ResultSlot &) = delete;
+    ResultSlot &operator=(const ResultSlot &) = delete;
+    ~ResultSlot();
     void release();
 };
 

@@ -140,7 +140,7 @@ static sv_status stats_typed(sv_state *st, const void *psi, double *host16) {
     stats_grid(st->n, &nb, &chunk);
     SV_TRY(st->ws.reserve((size_t)(nb + 1) * 16 * sizeof(double)));
     double *part = (double *)st->ws.ptr;
-    ResultSlot slot(16 * sizeof(double));
+    ResultSlot slot(16 * sizeof(double), st->stream);
     double *res = slot.ptr ? (double *)slot.ptr : part + (size_t)nb * 16;
     hipLaunchKernelGGL((k_stats<T, FULL>), dim3(nb), dim3(RB), 0, st->stream, (const cpx<T> *)psi,
                        chunk, std::ldexp(1.0, st->n), part);
@@ -452,7 +452,7 @@ sv_status run_pair_stats(sv_state *a, sv_state *b, int nbins, double zmin, doubl
 #undef PAIR_LAUNCH
     SV_HIP(hipGetLastError());
     std::vector<uint64_t> host((size_t)16 + nwords);
-    ResultSlot slot(host.size() * 8);
+    ResultSlot slot(host.size() * 8, s);
     if (slot.ptr) res = (decltype(res))slot.ptr;
     hipLaunchKernelGGL(k_pair_finish, dim3(1 + hcols / 16), dim3(CMB_THREADS), 0, s, part, rows, hcols, nwords, nb, res);
     SV_HIP(hipGetLastError());
@@ -941,7 +941,7 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
     auto *sub = (unsigned long long *)(w + L.o_sub);
     double *part = (double *)(w + L.o_part);
     auto *res = (PassResult *)(w + L.o_res);
-    ResultSlot slot(scr.fixed ? SIZE_MAX : sizeof(PassResult));   // the no-allocation call copies
+    ResultSlot slot(scr.fixed ? SIZE_MAX : sizeof(PassResult), s);   // the no-allocation call copies
     const double Nd = std::ldexp(1.0, n);
     if constexpr (!CHECK) {
         if (stats16)
@@ -1119,7 +1119,7 @@ sv_status run_cross_entropy(sv_state *st, const void *psi, const uint64_t *dev_s
     const int64_t nb = (k + per - 1) / per;
     SV_TRY(st->ws.reserve((size_t)(nb + 1) * 16 * sizeof(double)));
     double *part = (double *)st->ws.ptr;
-    ResultSlot slot(2 * sizeof(double));
+    ResultSlot slot(2 * sizeof(double), st->stream);
     double *res = slot.ptr ? (double *)slot.ptr : part + (size_t)nb * 16;
     if (st->dt == SV_C64)
         hipLaunchKernelGGL(k_ce<float>, dim3((unsigned)nb), dim3(RB), 0, st->stream,
