@@ -923,8 +923,7 @@ static SampleLayout sample_layout(int n) {
 // may be 0).
 // src holds N = 2^n entries, or (explicit distributions, which are checked)
 // any N in (2^{n-1}, 2^n], the entries beyond N counting as weight 0.
-// host_out, when not null, receives a copy of the samples.  Synchronises: one
-// wait at the end, for the result block and the samples.
+// host_out, when not null, receives a copy of the samples.  Synchronises.
 template <typename S>
 static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *src, int n, const uint64_t *words,
                              uint64_t seed, int64_t k, uint64_t *dev_out, uint64_t *host_out,
@@ -971,7 +970,6 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
         SV_HIP(hipGetLastError());
     }
     PassResult host;
-    if (k > 0 && host_out) SV_HIP(hipMemcpyAsync(host_out, dev_out, (size_t)k * 8, hipMemcpyDeviceToHost, s));
     SV_TRY(fetch_result(slot, &host, res, sizeof host, s));
     if (stats16)
         for (int i = 0; i < 16; i++) stats16[i] = i <= NSTAT ? host.stats[i] : 0.0;
@@ -980,6 +978,11 @@ static sv_status sample_impl(const ScratchSource &scr, hipStream_t s, const S *s
     if (host.status == PASS_OVERFLOW)
         return fail(SV_ERANGE, "sv_sample_from: the weights floor(p 2^62) sum to 2^64 or more (sum p >= 4)");
     if (k > 0 && host.status == PASS_ZERO) return fail(SV_ESTATE, "sampler: every probability rounds to weight 0");
+    // only now: a call that fails leaves the caller's array as it was
+    if (k > 0 && host_out) {
+        SV_HIP(hipMemcpyAsync(host_out, dev_out, (size_t)k * 8, hipMemcpyDeviceToHost, s));
+        SV_HIP(hipStreamSynchronize(s));
+    }
     return SV_OK;
 }
 
