@@ -399,9 +399,12 @@ static sv_status build_ensemble(sv_state **sts, const std::vector<std::shared_pt
                            (unsigned long long *)ctl, g->err, ctl + 4, ctl + 4 + count, g->res, 1u << 22);
     } else {
         for (const auto &L : launches) {
-            // grids of at most 2^31 - 1 workgroups
-            for (uint64_t a = L.first; a < L.second; a += 0x7fffffffull) {
-                const uint64_t nb = std::min<uint64_t>(L.second - a, 0x7fffffffull);
+            // a launch holds fewer than 2^32 threads (one 35-qubit instance on
+            // wide tiles of 3 register qubits has 2^24 items)
+            constexpr uint64_t SLICE = 1ull << 23;
+            static_assert(SLICE * BLOCK < (1ull << 32), "threads of a launch");
+            for (uint64_t a = L.first; a < L.second; a += SLICE) {
+                const uint64_t nb = std::min<uint64_t>(L.second - a, SLICE);
                 hipLaunchKernelGGL(kr, dim3((unsigned)nb), dim3(BLOCK), 0, g->stream, d_rounds, d_items, a,
                                    d_insts);
             }
