@@ -147,8 +147,10 @@ struct RTHeader {           // 160 bytes
     int32_t gen_n;          // > 0: do not load; start from the uniform state
                             // 2^{-gen_n/2} of gen_n qubits (Hadamard layer)
     double fscale;          // store: amplitudes also scaled by fscale (the
-                            // product of the cosines of the F_TRX/F_TRY ops and
-                            // of the powers of two taken back inside the sweep)
+                            // product of the cosines of the F_TRX/F_TRY ops, of
+                            // the powers of two taken back inside the sweep and,
+                            // in one sweep of a wide complex64 plan, of the norm
+                            // that its rounded coefficients lose)
     int32_t lq[2];          // qubits on lane bits 4 and 5 (lane bits 0..3 are
                             // qubits 0..3); 4 and 5 give contiguous rows
     int32_t tq[10];         // the tile's qubits above 3 (lane, wave and register

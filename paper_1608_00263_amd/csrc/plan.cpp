@@ -1029,6 +1029,37 @@ static void assign_scales(Plan *plan, const std::vector<std::pair<size_t, int>> 
     }
 }
 
+// Mean change of ln |psi| by rounding a complex64 sweep's coefficients to FP32,
+// over states whose qubits are evenly mixed: half the change of ln tr U+ U per
+// gate, the share 2^-bits of ln |v| per phase term.  A T gate's (1 + i) / sqrt2
+// rounds to a modulus of 1 - 1.7e-8, so 100 of them shrink the state by 8e-7,
+// more than all other rounding of such a circuit adds.
+static double norm_drift(const RTProgram &P) {
+    auto f32 = [](double v) { return (double)(float)v; };
+    double d = 0.0;
+    for (const RTOp &o : P.ops) {
+        if (o.kind == RT_REG || o.kind == RT_LANE) {
+            if (form_scaled(o.form)) continue;   // entries 0, +-1, +-i
+            double t32 = 0.0, t64 = 0.0;
+            for (double v : o.u) {
+                t32 += f32(v) * f32(v);
+                t64 += v * v;
+            }
+            if (t64 > 0.0) d += 0.5 * std::log(t32 / t64);
+        } else if (o.kind == RT_PHASE) {
+            for (int t = o.a; t < o.a + o.nterms; t++) {
+                const DiagTerm &m = P.terms[t];
+                const double m32 = f32(m.val[0]) * f32(m.val[0]) + f32(m.val[1]) * f32(m.val[1]);
+                const double m64 = m.val[0] * m.val[0] + m.val[1] * m.val[1];
+                const double share = std::ldexp((double)__builtin_popcountll(m.regset),
+                                                -P.h.vbits - __builtin_popcountll(m.outside) - __builtin_popcount(m.lanemask));
+                if (m64 > 0.0) d += 0.5 * share * std::log(m32 / m64);
+            }
+        }
+    }
+    return d;
+}
+
 // The adjoint of a register-tile program: ops reversed, matrices and phases
 // conjugate-transposed; gradient slots and generators stay with their ops.
 static RTProgram reverse_regtile(const RTProgram &F) {
@@ -1092,9 +1123,11 @@ static void push_regtile(const RTProgram &P, int n, int dtype, OpType type, std:
 }
 
 static void emit_regtile(const std::vector<SGate> &g, const Sweep &sw, int vbits, int n, int dtype,
-                         Plan *plan, std::vector<std::pair<size_t, int>> *scales, bool gen = false) {
+                         Plan *plan, std::vector<std::pair<size_t, int>> *scales, bool gen = false,
+                         double *drift = nullptr) {
     int nc = 0;
     RTProgram P = build_regtile(g, sw, vbits, n, dtype, true, &nc, gen);
+    if (drift) *drift += norm_drift(P);
     push_regtile(P, n, dtype, OP_REGTILE, &plan->ops, plan);
     scales->push_back({plan->ops.back().prog_off, nc});
 }
@@ -1537,8 +1570,9 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         const double budget = rq.budget > 0 ? (double)rq.budget : -1.0;
         auto sweeps = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true);
         // Tiles of four wavefronts where their two more gathered qubits save a
-        // sweep: 30 qubits complex64 10 sweeps in 35.0 ms against 13 in 40.4,
-        // 28 qubits complex128 10 in 17.0 ms against 14 in 22.2.  With equal
+        // sweep: 30 qubits complex64 10 sweeps in 35.0 to 36.7 ms against 13 in
+        // 40.4 to 42.6, 28 qubits complex128 10 in 16.8 to 17.8 ms against 14 in
+        // 21.5 to 22.2 (three cards).  With equal
         // counts the exchanges only cost (12 qubits complex128, 3 register
         // qubits: 44.7 against 40.9 us).  The second search looks for fewer
         // sweeps only and stops where there are none: planning a new circuit
@@ -1555,9 +1589,20 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         // registers instead of being written and read back (with the
         // diagonals that act on it folded into the generated values)
         const bool gen = plan->ops.size() == 1 && plan->ops[0].type == OP_INIT_UNIFORM && !sweeps.empty();
+        const bool take_back = !sweeps.empty() && !sweeps[0].rq.empty() && rq.dtype == SV_C64;
+        double drift = 0.0;
         for (size_t i = 0; i < sweeps.size(); i++)
-            emit_regtile(g, sweeps[i], vb, rq.n, rq.dtype, plan, &scales, gen && i == 0);
+            emit_regtile(g, sweeps[i], vb, rq.n, rq.dtype, plan, &scales, gen && i == 0, take_back ? &drift : nullptr);
         assign_scales(plan, scales);
+        // Complex64 wide plans take the mean loss of norm back, in the start
+        // value of a generated state or the last sweep's factor: their error
+        // against FP64 was up to 8% above that of the narrow plans, all of it in
+        // the norm (24 qubits, depth 40: 9.1e-7 against 8.8e-7, of which 7.8e-7
+        // and 7.4e-7), and is 4.7e-7 with it.
+        if (drift != 0.0) {
+            RTHeader *h = reinterpret_cast<RTHeader *>(plan->prog.data() + scales[gen ? 0 : scales.size() - 1].first);
+            h->fscale *= std::exp(-drift);
+        }
         if (plan->ops.size() >= 2 && plan->ops[0].type == OP_INIT_UNIFORM &&
             plan->ops[1].type == OP_REGTILE) {
             RTHeader *h = reinterpret_cast<RTHeader *>(plan->prog.data() + plan->ops[1].prog_off);

@@ -1,0 +1,48 @@
+"""Complex64 plans on tiles of four wavefronts keep the norm: the mean effect of
+coefficients rounded to FP32 (a T gate's modulus is 1 - 1.7e-8) is taken back."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1608_00263_amd import circuits as C
+from paper_1608_00263_amd import sv
+
+CASES = [(2, 7, 100, 6), (2, 7, 60, 4), (4, 4, 40, 0), (3, 5, 60, 3), (1, 15, 90, 5)]
+
+
+def wide_circuit(rows, cols, depth, tile, from_zero):
+    circ = C.make_circuit(rows, cols, depth, seed=8)
+    assert "waves=[" in sv.host_plan_describe(circ, "c64", "regtile", 0, tile, from_zero=from_zero)
+    return circ
+
+
+@pytest.mark.parametrize("rows,cols,depth,tile", CASES)
+@pytest.mark.parametrize("from_zero", [True, False])
+def test_replayed_norm(rows, cols, depth, tile, from_zero):
+    # the replay rounds the coefficients and one factor, whose own rounding
+    # (2^-24) is what may remain; left alone the loss is 1.7e-8 a T gate
+    circ = wide_circuit(rows, cols, depth, tile, from_zero)
+    psi0 = oracle.zero_state(circ.n) if from_zero else C.random_state(circ.n, 5, dtype=np.complex128)
+    psi0 /= np.linalg.norm(psi0)
+    got = sv.host_emulate(circ, psi0, "c64", "regtile", 0, tile, from_zero=from_zero)
+    assert abs(np.vdot(got, got).real - 1) <= 4 * 2.0 ** -24
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,depth,tile", CASES + [(4, 6, 40, 6), (4, 6, 40, 4)])
+@pytest.mark.parametrize("from_zero", [True, False])
+def test_norm_against_double_precision(rows, cols, depth, tile, from_zero):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    circ = wide_circuit(rows, cols, depth, tile, from_zero)
+    psi0 = C.random_state(circ.n, 5, dtype=np.complex64)
+    ref = oracle.apply_circuit(circ) if from_zero else oracle.apply_circuit(circ, psi0.astype(np.complex128))
+    st = sv.State(circ.n, "c64", tensor=torch.from_numpy(psi0).to("cuda"))
+    st.apply(circ, "regtile", 0, tile, from_zero=from_zero)
+    got = st.amplitudes().astype(np.complex128)
+    st.close()
+    # one factor's rounding and that of phase products shared by many amplitudes
+    # (2^-25 each, a few a sweep)
+    loss = np.vdot(ref, got).real / np.vdot(ref, ref).real - 1
+    assert abs(loss) <= 8 * 2.0 ** -25
