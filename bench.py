@@ -20,7 +20,8 @@ circuit_s  = seconds of the same circuit per planning mode (plain per-gate,
              specialised per-gate, fused 2^k blocks, LDS tiles, register
              tiles) in complex64 and complex128;
 roofline_c128 = the same for the complex128 register-tile sweep
-             (k_widetile<double,5>) on the same circuit, as the
+             (k_widetile<double,5> where tiles of four wavefronts save a
+             sweep) on the same circuit, as the
              autotuner plans it (--c128-budget pins a sweep budget);
 grad       = adjoint gradient time over forward time on the 5x5, depth-30
              parametrised circuit (10^4 samples) for checkpoint intervals;
@@ -43,8 +44,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBPS = 8000.0
-# the library's register-tile sweep budget when the options leave it 0
-DEFAULT_SWEEP_BUDGET = {"c64": 300, "c128": 220}
 PEAK_FP32_MFMA_TFLOPS = 157.3   # dense FP32 matrix peak of the MI355X
 PEAK_FP64_MFMA_TFLOPS = 78.6    # dense FP64 matrix peak of the MI355X
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_regtile_c2_traffic.txt")
@@ -89,6 +88,22 @@ def profile_summary(tile, budget, path=TRAFFIC_FILE):
     except ValueError:
         return {}
     return kv if same else {}
+
+
+def wide_tiles(sv, circ, dtype, tile, budget):
+    """Whether the register-tile plan runs on tiles of four wavefronts."""
+    return "waves=[" in sv.host_plan_describe(circ, dtype, "regtile", 0, tile, budget=budget)
+
+
+def sweep_kernel(sv, circ, dtype, tile, budget):
+    """The kernel of that plan's sweeps."""
+    name = "k_widetile" if wide_tiles(sv, circ, dtype, tile, budget) else "k_regtile"
+    return "%s<%s,%d>" % (name, "float" if dtype == "c64" else "double", tile)
+
+
+def default_budget(sv, circ, dtype, tile):
+    """The library's register-tile sweep budget when the options leave it 0."""
+    return 220 if dtype == "c128" else 300 if wide_tiles(sv, circ, dtype, tile, 0) else 250
 
 
 def measured_traffic(tile, budget, path=TRAFFIC_FILE):
@@ -255,14 +270,15 @@ def main():
     # candidates on a scratch state), so no timed step includes tuning
     choice = None
     rt_tile = a.tile or 6
-    rt_budget = a.budget or DEFAULT_SWEEP_BUDGET["c64"]
+    rt_option = a.budget
     if a.mode == "auto":
         cname, ck, ctile, complete, cbudget = st.autotune(circ, from_zero=True)
         choice = {"mode": cname, "k_max": ck, "tile": ctile, "sweep_budget": cbudget, "complete": complete}
         if cname == "regtile":
             rt_tile = ctile or 6
-            rt_budget = cbudget or DEFAULT_SWEEP_BUDGET["c64"]
+            rt_option = cbudget
         log("autotuner: %s" % choice)
+    rt_budget = rt_option or default_budget(sv, circ, "c64", rt_tile)
 
     def step():
         ms, kinds, by = st.apply_timed(circ, a.mode, 0, a.tile, args=args, from_zero=True, budget=a.budget)
@@ -322,7 +338,7 @@ def main():
         "sweep_frac_of_peak": round(sweep_bytes[-1] / (np.mean(sweep_ms) / 1e3) / 1e9 / PEAK_HBM_GBPS, 4),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": measured_traffic(rt_tile, rt_budget),
-                     "kernel": "k_widetile<float,%d>" % rt_tile,
+                     "kernel": sweep_kernel(sv, circ, "c64", rt_tile, rt_option),
                      "launch_avg_ms": round(dom_ms / max(dom_launches, 1), 4),
                      "bytes_per_launch": round(dom_bytes / max(dom_launches, 1), 1),
                      "valu_frac": measured_valu_frac(rt_tile, rt_budget),
@@ -426,10 +442,10 @@ def roofline_c128(sv, C, circ, torch, budget=0, reps=5):
     torch.cuda.empty_cache()
     log("c128 register tiles: %.2f ms, %d sweeps, %.0f GB/s" % (tot, nl, achieved))
     tile = (ctile or 5) if cname == "regtile" else 5
-    tb = cbudget or DEFAULT_SWEEP_BUDGET["c128"]
+    tb = cbudget or default_budget(sv, circ, "c128", tile)
     return {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": measured_traffic(tile, tb, TRAFFIC_FILE_C128),
-            "valu_frac": measured_valu_frac(tile, tb, TRAFFIC_FILE_C128), "kernel": "k_widetile<double,%d>" % tile,
+            "valu_frac": measured_valu_frac(tile, tb, TRAFFIC_FILE_C128), "kernel": sweep_kernel(sv, circ, "c128", tile, cbudget),
             "choice": choice,
             "launches": nl, "launch_avg_ms": round(dom_ms / nl, 4), "bytes_per_launch": round(dom_by / nl, 1),
             "circuit_ms": round(tot, 3), "workload": "5x6 grid, 30 qubits, depth 40, complex128 (16 GiB)"}

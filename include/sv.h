@@ -130,7 +130,10 @@ typedef struct {
     int32_t k_max;        /* fused block width 1..5 (0 = default 4)           */
     int32_t tile_qubits;  /* TILED: 8..13 (0 = default 12 / 11); REGTILE:
                              register qubits 1..6 complex64, 1..5 complex128
-                             (0 = default: 3 for small states up to 6 / 5)    */
+                             (0 = default: sv_apply_circuit and ensembles of
+                             ordinary launches 3 for small states up to 6 / 5,
+                             complex64 circuits with rotation offsets and
+                             sv_cycle_moments 6 / 5; sv_backward see there)   */
     int32_t flags;        /* SV_FLAG_* bits                                   */
     int32_t sweep_budget; /* REGTILE: vector instructions per amplitude
                              register one sweep may spend on gates before a

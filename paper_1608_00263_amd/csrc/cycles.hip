@@ -60,7 +60,7 @@ struct TileStats {
 // VALU issues per amplitude, which the sweep's memory time covers (a per-cycle
 // sweep has few gates): 24 qubits complex128 one point took 87 us for the
 // sweep and 47 us for a pass of its own over the state; the series of 39 points
-// went from 5.73 to 4.54 ms, that of 28 qubits from 89.8 to 69.9.  (With four
+// went from 5.73 to 4.5-4.7 ms, that of 28 qubits from 89.8 to 69.9.  (With four
 // probabilities at a time and the lane's constants held across the tiles, 62
 // registers spilled at 5 register qubits: 5.11 and 74.1 ms.)
 template <typename T, int VB>
@@ -105,8 +105,11 @@ sv_status launch_stat_sweep(sv_state *st, const Plan &plan, const Op &op, double
     const uint8_t *prog = (const uint8_t *)plan.dprog + op.prog_off;
     const uint64_t ntiles = (1ull << st->n) >> (LANE_BITS + op.vbits);
     const uint64_t groups = (ntiles + BLOCK / 64 - 1) / (BLOCK / 64);
-    // as many workgroups as are resident (3 per CU at 168 registers, 4 at 128):
-    // with more, the last round of a 28-qubit sweep ran on a fraction of the chip
+    // no more workgroups than are resident at the widths that matter (3 per CU
+    // for 5 register qubits, 4 for 4): with more, the last round of a 28-qubit
+    // sweep ran on a fraction of the chip.  Narrower tiles could hold 6 to 8 per
+    // CU and run on 3 (24 qubits, 25 points: 5.16, 3.44 and 2.74 ms at 1, 2 and 3
+    // register qubits, 2.60 at 4 and 2.73 at 5).
     const uint64_t resident = op.vbits == 4 ? 1024 : 768;
     static_assert(STATS_BLOCKS >= 1024, "a list of partial rows holds STATS_BLOCKS");
     *nrows = (int)(groups < resident ? groups : resident);

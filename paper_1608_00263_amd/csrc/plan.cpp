@@ -1570,9 +1570,9 @@ sv_status build_plan(const sv_circuit *c, const PlanRequest &rq, Plan *plan) {
         const double budget = rq.budget > 0 ? (double)rq.budget : -1.0;
         auto sweeps = regtile_sweeps(g, rq.n, vb, rq.dtype, budget, true);
         // Tiles of four wavefronts where their two more gathered qubits save a
-        // sweep: 30 qubits complex64 10 sweeps in 35.0 to 36.7 ms against 13 in
-        // 40.4 to 42.6, 28 qubits complex128 10 in 16.8 to 17.8 ms against 14 in
-        // 21.5 to 22.2 (three cards).  With equal
+        // sweep: 30 qubits complex64 10 sweeps in 35.0 to 36.8 ms against 13 in
+        // 40.4 to 43.4, 28 qubits complex128 10 in 16.8 to 18.0 ms against 14 in
+        // 21.5 to 22.2 (several cards).  With equal
         // counts the exchanges only cost (12 qubits complex128, 3 register
         // qubits: 44.7 against 40.9 us).  The second search looks for fewer
         // sweeps only and stops where there are none: planning a new circuit

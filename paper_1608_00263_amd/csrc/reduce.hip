@@ -758,9 +758,9 @@ __global__ __launch_bounds__(CMB_THREADS) void k_finish_pass(const unsigned long
     }
 }
 
-// One wavefront per sample first, first + 1, ... < k: t = floor(r W / 2^64), then x = min{j : C_j > t}
-// by one 64-wide step per level (group prefix in two, chunks, sub-buckets,
-// the four consecutive entries of a lane).  Five dependent loads, and nothing
+// One wavefront per sample first, first + 1, ... < k: t = floor(r W / 2^64),
+// then x = min{j : C_j > t} by one 64-wide step per level (group prefix in two,
+// chunks, sub-buckets, the four consecutive entries of a lane).  Five dependent loads, and nothing
 // is read twice: bound by their latency over the resident wavefronts.  (A
 // binary search over the bucket prefix in a kernel of its own, then a serial
 // walk of the last 16 entries by one lane, took 0.6 ms for 10^5 samples at 30
