@@ -1036,6 +1036,8 @@ static void assign_scales(Plan *plan, const std::vector<std::pair<size_t, int>> 
 // more than all other rounding of such a circuit adds.
 static double norm_drift(const RTProgram &P) {
     auto f32 = [](double v) { return (double)(float)v; };
+    // matrices that FP32 cannot hold (to 0 or infinity) have no mean loss
+    auto in_range = [](double a, double b) { return a > 0.0 && b > 0.0 && std::isfinite(a) && std::isfinite(b); };
     double d = 0.0;
     for (const RTOp &o : P.ops) {
         if (o.kind == RT_REG || o.kind == RT_LANE) {
@@ -1045,7 +1047,7 @@ static double norm_drift(const RTProgram &P) {
                 t32 += f32(v) * f32(v);
                 t64 += v * v;
             }
-            if (t64 > 0.0) d += 0.5 * std::log(t32 / t64);
+            if (in_range(t32, t64)) d += 0.5 * std::log(t32 / t64);
         } else if (o.kind == RT_PHASE) {
             for (int t = o.a; t < o.a + o.nterms; t++) {
                 const DiagTerm &m = P.terms[t];
@@ -1053,7 +1055,7 @@ static double norm_drift(const RTProgram &P) {
                 const double m64 = m.val[0] * m.val[0] + m.val[1] * m.val[1];
                 const double share = std::ldexp((double)__builtin_popcountll(m.regset),
                                                 -P.h.vbits - __builtin_popcountll(m.outside) - __builtin_popcount(m.lanemask));
-                if (m64 > 0.0) d += 0.5 * share * std::log(m32 / m64);
+                if (in_range(m32, m64)) d += 0.5 * share * std::log(m32 / m64);
             }
         }
     }

@@ -46,3 +46,22 @@ def test_norm_against_double_precision(rows, cols, depth, tile, from_zero):
     # (2^-25 each, a few a sweep)
     loss = np.vdot(ref, got).real / np.vdot(ref, ref).real - 1
     assert abs(loss) <= 8 * 2.0 ** -25
+
+
+@pytest.mark.parametrize("scale", [1e-50, 1e50])
+def test_matrices_beyond_single_precision(scale):
+    # a matrix that FP32 holds as 0 (or infinity) gives a state of zeros (or no
+    # finite one), not the loss of norm of its rounding
+    circ = C.random_unitary_circuit(12, 200, seed=900)
+    u1 = [int(m) for k, m in zip(circ.gates["kind"], circ.gates["mat"]) if k == C.U1]
+    mats = np.array(circ.mats, copy=True)
+    mats[u1[0]] = mats[u1[0]] * scale
+    bad = C.Circuit(n=circ.n, gates=circ.gates, theta=circ.theta, mats=mats)
+    assert "waves=[" in sv.host_plan_describe(bad, "c64", "regtile", 0, 4, from_zero=False, budget=2000)
+    psi0 = C.random_state(circ.n, 6, dtype=np.complex128)
+    with np.errstate(all="ignore"):
+        got = sv.host_emulate(bad, psi0, "c64", "regtile", 0, 4, from_zero=False, budget=2000)
+    if scale < 1:
+        assert (got == 0).all()
+    else:
+        assert not np.isfinite(got).all()
